@@ -703,10 +703,16 @@ static int kr_row_tiles(int rpad) { return rpad <= 64 ? 2 : (rpad <= 128 ? 4 : 0
 //   qbuf  max(NR * ROWB, 4 * kHBins)        window queries; the B histogram after pass 2
 //   part  kKrWaves * NR float2              per-wave row partials (pass 1)
 //   nlc   NR floats                         -lse / c2 of each row (pass 2)
+//   wrw   NR ints                           window index of each row (W for pad rows)
+//   lqw   NR floats                         1 on last-query rows, else 0 (pass 2)
 //   cb    KPW floats                        B of the chunk's keys (fused)
+// The window indices are formed once per row: a lane's rows differ per
+// accumulator register, and a remainder by W per register costs a wave more
+// than its probabilities (a 16-query window, 112 rows of d = 64: pass 2 of
+// four short sequences 28.9 us per launch that way).
 int kr_lds_bytes(bool bf16, int head_dim, int rpad) {
   const int nr = 32 * kr_row_tiles(rpad), rowb = head_dim * (bf16 ? 2 : 4), kpw = kr_keys(bf16, head_dim);
-  return std::max(nr * rowb, 4 * kHBins) + 8 * kKrWaves * nr + 4 * nr + 4 * kpw;
+  return std::max(nr * rowb, 4 * kHBins) + 8 * kKrWaves * nr + 12 * nr + 4 * kpw;
 }
 
 // One workgroup of a key-register pass: chunk gchunk of the sequences' keys
@@ -729,7 +735,9 @@ __device__ __forceinline__ void krpass_body(const PassArgs &a, const SeqTable &s
   unsigned char *qbuf = smem;
   float2 *part = reinterpret_cast<float2 *>(smem + max(NR * C::ROWB, 4 * kHBins));
   float *nlc = reinterpret_cast<float *>(part + kKrWaves * NR);
-  float *cb = nlc + NR;
+  int *wrw = reinterpret_cast<int *>(nlc + NR);
+  float *lqw = reinterpret_cast<float *>(wrw + NR);
+  float *cb = lqw + NR;
 
   // ---- loads, in this order: the window queries, the row normalisers
   // (pass 2), the first key tile; once the first group is in LDS, the other
@@ -776,6 +784,11 @@ __device__ __forceinline__ void krpass_body(const PassArgs &a, const SeqTable &s
     // pad rows (and rows past Rpad) get lse = +inf: probability 0
     if (a.lse_in) lsev *= kLog2e;
     if (t < NR) nlc[t] = t < a.R ? -lsev / a.c2 : -INFINITY;
+  }
+  if (t < NR) {
+    const int w = t < a.R ? t % W : W;
+    wrw[t] = w;
+    lqw[t] = w == W - 1 ? 1.f : 0.f;
   }
 #pragma unroll
   for (int j = 0; j < QP; ++j) {
@@ -853,8 +866,7 @@ __device__ __forceinline__ void krpass_body(const PassArgs &a, const SeqTable &s
       } else {
 #pragma unroll
         for (int j = 0; j < NRT; ++j) {
-          const int r = j * 32 + l32;
-          const int tpos = wfirst + (r < a.R ? r % W : W - 1);
+          const int tpos = wfirst + min(wrw[j * 32 + l32], W - 1);
           float av[16];
 #pragma unroll
           for (int reg = 0; reg < 16; ++reg) {
@@ -897,19 +909,6 @@ __device__ __forceinline__ void krpass_body(const PassArgs &a, const SeqTable &s
     // The accumulators start at -lse / c2 of their rows, so exp2(c2 * acc) is
     // the softmax probability.
     constexpr int RG = NRT < 2 ? NRT : 2;                  // row tiles per MFMA group
-    // accumulator registers of the last query of each group, per row tile
-    uint32_t lastm[NRT];
-#pragma unroll
-    for (int j = 0; j < NRT; ++j) {
-      lastm[j] = 0;
-      if constexpr (!W32) {
-#pragma unroll
-        for (int reg = 0; reg < 16; ++reg) {
-          const int r = j * 32 + acc_row(reg, half);
-          if (r < a.R && (r % W) == W - 1) lastm[j] |= 1u << reg;
-        }
-      }
-    }
     const float inv_gw = 1.f / (float)(a.G * W), inv_g = 1.f / (float)a.G;
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
@@ -940,20 +939,30 @@ __device__ __forceinline__ void krpass_body(const PassArgs &a, const SeqTable &s
           float p[16];
 #pragma unroll
           for (int reg = 0; reg < 16; ++reg) p[reg] = __builtin_amdgcn_exp2f(acc[j][reg] * a.c2);
+          const int row0 = (j0 + j) * 32 + opaque(4 * half);   // the lane's rows: runs of four, 8 apart
           if (edge) {
 #pragma unroll
-            for (int reg = 0; reg < 16; ++reg) {
-              const int r = (j0 + j) * 32 + acc_row(reg, half);
-              const int wr = r < a.R ? r % W : W;
-              if (!(key < k1 && key - wfirst <= wr)) p[reg] = 0.f;
+            for (int i = 0; i < 4; ++i) {
+              const int4 wr = *reinterpret_cast<const int4 *>(wrw + row0 + 8 * i);
+              if (!(key < k1 && key - wfirst <= wr.x)) p[4 * i + 0] = 0.f;
+              if (!(key < k1 && key - wfirst <= wr.y)) p[4 * i + 1] = 0.f;
+              if (!(key < k1 && key - wfirst <= wr.z)) p[4 * i + 2] = 0.f;
+              if (!(key < k1 && key - wfirst <= wr.w)) p[4 * i + 3] = 0.f;
             }
           }
           bsum += tree_sum16(p);
           if constexpr (W32) {
             qsum += half ? p[15] : 0.f;
           } else {
+            // the rows' 0 / 1 weights: the last queries' probabilities in row order
 #pragma unroll
-            for (int reg = 0; reg < 16; ++reg) qsum += ((lastm[j0 + j] >> reg) & 1u) ? p[reg] : 0.f;
+            for (int i = 0; i < 4; ++i) {
+              const float4 lw = *reinterpret_cast<const float4 *>(lqw + row0 + 8 * i);
+              qsum = fmaf(p[4 * i + 0], lw.x, qsum);
+              qsum = fmaf(p[4 * i + 1], lw.y, qsum);
+              qsum = fmaf(p[4 * i + 2], lw.z, qsum);
+              qsum = fmaf(p[4 * i + 3], lw.w, qsum);
+            }
           }
         }
       };
