@@ -90,6 +90,9 @@ def kernel_bytes(name, wl, persist_m=4):
         return hist_reads
     if name == "final_topk":
         return 2 * 2 * kept_rows * Hkv * wl.head_dim * wl.elem_size + 4 * sum(wl.budgets) * Hkv
+    if name == "segment_select":                        # the four select jobs, one layer's worth of each
+        return sum(kernel_bytes(k, wl, persist_m)
+                   for k in ("segment_calib", "segment_score", "segment_cand", "final_topk"))
     if name == "segment_calib_cand":                    # calibration, the previous layer's lists,
         return sum(kernel_bytes(k, wl, persist_m)      # the next layer's normaliser merge
                    for k in ("segment_calib", "segment_cand", "lse_merge"))

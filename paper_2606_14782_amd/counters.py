@@ -38,6 +38,11 @@ _NAMES = [
     (r"bacon::k_krdual<", "window_score_calib_lse_kr"),
     (r"bacon::k_pass_dual<", "window_score_calib_lse"),
     (r"bacon::k_single<", "window_score_single"),
+    (r"bacon::k_sel\b", "segment_select"),
+    (r"bacon::k_sel_one<0>", "segment_score"),
+    (r"bacon::k_sel_one<1>", "final_topk"),
+    (r"bacon::k_sel_one<2>", "segment_calib"),
+    (r"bacon::k_sel_one<3>", "segment_cand"),
     (r"bacon::k_sel_a\b", "segment_calib_cand"),
     (r"bacon::k_sel_b\b", "segment_score_final"),
     (r"bacon::k_segcal\b", "segment_calib"),

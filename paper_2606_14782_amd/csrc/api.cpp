@@ -39,10 +39,23 @@ struct Layout {
   size_t ring, vec_b, vec_vp, vec_v, vec_pb, vec_pv, vec_s, hist_b, hist_s, list_bk, list_bp, list_bv,
       list_sk, list_sp, cnt_b, cnt_s, rec_b, rec_s, partials, lse2, lambda, hb, sb, sync, total;
   size_t sync_bytes;
-  size_t vec_s_stride, hist_b_stride, hist_s_stride, hb_stride, sb_stride;   // the two copies by layer parity
+  // distances between the copies that layers in flight take in turn
+  size_t vec_stride, hist_b_stride, hist_s_stride, list_stride, cnt_stride, rec_stride, hb_stride, sb_stride;
   int rpad, slots;
   int64_t chunks_cap;
 };
+
+// Copies of the buffers that pass between the select jobs.  In a prompt call
+// one select launch holds the calibration of layer l, the scores of l - 1,
+// the candidate lists of l - 2 and the final job of l - 3, so a layer's
+// buffer is free again
+//  * two launches on, where only the next job reads it (B, V and their pooled
+//    forms, the lists, their counts and records): two copies;
+//  * after the candidate job, which clears the B histogram that the next
+//    layer of its copy counts into: three;
+//  * after the final job (the S keys and histogram, which its whole-sequence
+//    path reads, and the budget tables): four.
+constexpr int kCopies2 = 2, kCopies3 = 3, kCopies4 = 4;
 
 bacon_status check_shape(const bacon_shape *s) {
   if (!s) return fail(BACON_ERR_INVALID, "shape is NULL");
@@ -102,18 +115,18 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.chunks_cap = (s->max_total_tokens + tk - 1) / tk + s->max_batch;
   const size_t vec = (size_t)s->num_kv_heads * (size_t)s->max_total_tokens * sizeof(float);
   size_t off = 0;
+  L.vec_stride = align256(vec);
   L.ring = off;     off += align256((size_t)L.slots * vec);
-  L.vec_b = off;    off += align256(vec);
-  L.vec_vp = off;   off += align256(vec);
-  L.vec_v = off;    off += align256(vec);
-  L.vec_pb = off;   off += align256(vec);
-  L.vec_pv = off;   off += align256(vec);
-  L.vec_s_stride = align256(vec);
-  L.vec_s = off;    off += 2 * L.vec_s_stride;                 // by layer parity
+  L.vec_b = off;    off += kCopies2 * L.vec_stride;
+  L.vec_vp = off;   off += L.vec_stride;
+  L.vec_v = off;    off += kCopies2 * L.vec_stride;
+  L.vec_pb = off;   off += kCopies2 * L.vec_stride;
+  L.vec_pv = off;   off += kCopies2 * L.vec_stride;
+  L.vec_s = off;    off += kCopies4 * L.vec_stride;
   const size_t hist = (size_t)s->max_batch * s->num_kv_heads * kHBins * sizeof(unsigned);
   L.hist_b_stride = align256(hist * kHCopies);
   L.hist_s_stride = align256(hist);
-  L.hist_b = off;   off += 2 * L.hist_b_stride;                // by layer parity
+  L.hist_b = off;   off += kCopies3 * L.hist_b_stride;
   // meeting words of the single-read pass (arrival and done counters per
   // (sequence, KV head) on lines of their own, the error word, the published
   // row normalisers), right after the B histograms so that one clearing
@@ -121,24 +134,30 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.sync_bytes = align256((size_t)(kSyncStride * s->max_batch * s->num_kv_heads + 1) * sizeof(unsigned)) +
                  align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(unsigned));
   L.sync = off;     off += L.sync_bytes;
-  L.hist_s = off;   off += 2 * L.hist_s_stride;
-  L.list_bk = off;  off += align256(vec);
-  L.list_bp = off;  off += align256(vec);
-  L.list_bv = off;  off += align256(vec);
-  L.list_sk = off;  off += align256(vec);
-  L.list_sp = off;  off += align256(vec);
+  L.hist_s = off;   off += kCopies4 * L.hist_s_stride;
+  // the lists of one copy lie one after the other: keys, positions, V for B
+  // (3 vectors) and keys, positions for S (2 vectors)
+  L.list_bk = off;
+  L.list_bp = off + L.vec_stride;
+  L.list_bv = off + 2 * L.vec_stride;
+  L.list_sk = off + 3 * L.vec_stride;
+  L.list_sp = off + 4 * L.vec_stride;
+  L.list_stride = 5 * L.vec_stride;
+  off += kCopies2 * L.list_stride;
   const int64_t segs_cap = (s->max_total_tokens + kSegLen - 1) / kSegLen + s->max_batch;
-  L.cnt_b = off;    off += align256((size_t)s->num_kv_heads * segs_cap * sizeof(int));
-  L.cnt_s = off;    off += align256((size_t)s->num_kv_heads * segs_cap * sizeof(int));
-  L.rec_b = off;    off += align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int4));
-  L.rec_s = off;    off += align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int4));
+  L.cnt_stride = align256((size_t)s->num_kv_heads * segs_cap * sizeof(int));
+  L.cnt_b = off;    off += kCopies2 * L.cnt_stride;
+  L.cnt_s = off;    off += kCopies2 * L.cnt_stride;
+  L.rec_stride = align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int4));
+  L.rec_b = off;    off += kCopies2 * L.rec_stride;
+  L.rec_s = off;    off += kCopies2 * L.rec_stride;
   L.partials = off; off += align256((size_t)s->num_kv_heads * L.chunks_cap * L.rpad * sizeof(float2));
   L.lse2 = off;     off += align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(float));
   L.lambda = off;   off += align256((size_t)s->max_batch * s->num_kv_heads * sizeof(float));
   L.hb_stride = align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int2));
-  L.hb = off;       off += 2 * L.hb_stride;                   // by layer parity
+  L.hb = off;       off += kCopies4 * L.hb_stride;
   L.sb_stride = align256((size_t)s->max_batch * sizeof(int4));
-  L.sb = off;       off += 2 * L.sb_stride;                   // by layer parity
+  L.sb = off;       off += kCopies4 * L.sb_stride;
   L.total = off;
   return L;
 }
@@ -148,11 +167,11 @@ const char *kKernelNames[] = {"window_lse",    "lse_merge",     "window_score", 
                               "final_topk",    "select_calib",  "select_topk",
                               "calib_elem",    "compact",       "window_lse_kr",
                               "window_score_calib_kr", "window_score_calib_lse_kr",
-                              "segment_calib_cand", "segment_score_final",
+                              "segment_select",
                               "window_score_calib_lse", "window_score_single", "head_alloc"};
 enum KernelId { KI_LSE, KI_MERGE, KI_SCORE, KI_FUSED, KI_SEGCAL, KI_SEGSCORE, KI_SEGCAND, KI_FINAL,
                 KI_SEL_CALIB, KI_SEL_TOPK, KI_ELEM, KI_COMPACT, KI_LSE_KR, KI_FUSED_KR, KI_DUAL_KR,
-                KI_SEL_A, KI_SEL_B, KI_DUAL, KI_SINGLE, KI_ALLOC, KI_COUNT };
+                KI_SEL, KI_DUAL, KI_SINGLE, KI_ALLOC, KI_COUNT };
 
 }  // namespace
 
@@ -370,11 +389,11 @@ PassArgs pass_args(const bacon_ctx *c, const SeqTable &st, int chunk, const void
 // within the sequence), or NULL with one budget per sequence.  The table rides
 // in the arguments of small kernels on the stream, ahead of the select.
 bacon_status head_table(bacon_ctx *c, const bacon_batch *bt, hipStream_t s, const int2 **out,
-                        int parity = 0) {
+                        int copy = 0) {
   *out = nullptr;
   if (!bt->head_budgets) return BACON_OK;
   const int hkv = c->shape.num_kv_heads;
-  int2 *dst = reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)parity * c->L.hb_stride);
+  int2 *dst = reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)copy * c->L.hb_stride);
   HbChunk ch{};
   const int n = bt->batch * hkv;
   int off = 0;
@@ -395,10 +414,10 @@ bacon_status head_table(bacon_ctx *c, const bacon_batch *bt, hipStream_t s, cons
 }
 
 // The per-sequence budget fields (budget, idx base, kept-row base) of a
-// layer's batch into the workspace table of its parity, for the launches
-// that hold the jobs of two layers with different budgets.
-bacon_status seq_table(bacon_ctx *c, const SeqTable &st, hipStream_t s, const int4 **out, int parity) {
-  int2 *dst = reinterpret_cast<int2 *>(c->ws + c->L.sb + (size_t)parity * c->L.sb_stride);
+// layer's batch into the workspace table of its copy, for the launches
+// that hold the jobs of several layers with different budgets.
+bacon_status seq_table(bacon_ctx *c, const SeqTable &st, hipStream_t s, const int4 **out, int copy) {
+  int2 *dst = reinterpret_cast<int2 *>(c->ws + c->L.sb + (size_t)copy * c->L.sb_stride);
   HbChunk ch{};
   for (int b = 0; b < st.batch; ++b) {
     ch.v[ch.n++] = make_int2(st.budget[b], st.idx_base[b]);
@@ -533,12 +552,11 @@ bacon_status bacon_begin_prompt(bacon_ctx *c, const bacon_batch *bt, void *strea
   TRY(check_batch(c, bt));
   c->cu.assign(bt->cu_seqlens, bt->cu_seqlens + bt->batch + 1);
 
-  // layer 0 reads no history; the B histogram of the select starts at zero
-  // (each layer's final kernel clears it for the next)
-  // (each layer's final kernel clears it for the next), and so do the
-  // meeting counters of the single-read pass
+  // layer 0 reads no history; the B histograms of the select start at zero
+  // (each layer's candidate job clears its copy for the layer that takes it
+  // next), and so do the meeting counters of the single-read pass
   const hipError_t e = launch_zero(reinterpret_cast<unsigned *>(c->ws + c->L.hist_b),
-                                   (int64_t)((2 * c->L.hist_b_stride + c->L.sync_bytes) / sizeof(unsigned)),
+                                   (int64_t)((kCopies3 * c->L.hist_b_stride + c->L.sync_bytes) / sizeof(unsigned)),
                                    static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "clear");
   c->prompt = true;
@@ -713,6 +731,7 @@ struct LayerRun {
   bool bf16 = false, w32 = false, kr = false, single = false;
   bool adaptive = false;   // head-wise budgets from the adaptive allocation
   int chunk = 0, kmax = 0;
+  int parts_alone = 1;     // final workgroups per (sequence, KV head) in a launch of their own
   SeqTable st{};
   PassArgs a{};
   SegArgs g{};
@@ -720,10 +739,9 @@ struct LayerRun {
 };
 
 // Checks one layer's arguments and builds its launch arguments; enqueues
-// nothing.  The layer order is the caller's to check.  Buffers that a layer
-// of the next pair may write while this layer's select is still in flight
-// (the B and S histograms and the score keys) alternate with the layer's
-// parity.
+// nothing.  The layer order is the caller's to check.  Buffers that later
+// layers may write while this layer's select is still in flight come in
+// copies that the layers take in turn (kCopies2, 3, 4).
 bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const void *d_q_win,
                         const void *d_k, const void *d_v, const float *d_lse, int32_t *d_idx,
                         void *d_k_out, void *d_v_out, LayerRun &r) {
@@ -782,13 +800,14 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   }
   if (final_lds_bytes(r.kmax, c->shape.window) > (size_t)kLdsBytes)
     return fail(BACON_ERR_UNSUPPORTED, "budget %d needs more LDS than a CU has", r.kmax);
-  const int par = layer & 1;
+  const size_t c2 = layer % kCopies2, c3 = layer % kCopies3, c4 = layer % kCopies4;
   const int64_t T = bt->cu_seqlens[bt->batch];
   PassArgs &a = r.a;
   a = pass_args(c, r.st, r.chunk, d_q_win, d_k);
   a.T = T;
   a.lse_in = d_lse;
-  a.hist_B += (size_t)par * c->L.hist_b_stride / sizeof(unsigned);
+  a.hist_B += c3 * c->L.hist_b_stride / sizeof(unsigned);
+  a.vec_B += c2 * c->L.vec_stride / sizeof(float);
   int ring_cnt = 0;
   ring_slots(c, layer, &a.ring_write, &ring_cnt);
   a.ring_stride = (int64_t)c->shape.num_kv_heads * T;
@@ -816,21 +835,22 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.ring_slots = c->L.slots;
   g.ring_slot = a.ring_write;
   g.ring_cnt = ring_cnt;
-  g.vec_V = reinterpret_cast<float *>(c->ws + c->L.vec_v);
-  g.vec_pB = reinterpret_cast<float *>(c->ws + c->L.vec_pb);
-  g.vec_pV = reinterpret_cast<float *>(c->ws + c->L.vec_pv);
-  g.vec_S = reinterpret_cast<unsigned *>(c->ws + c->L.vec_s + (size_t)par * c->L.vec_s_stride);
+  g.vec_V = reinterpret_cast<float *>(c->ws + c->L.vec_v + c2 * c->L.vec_stride);
+  g.vec_pB = reinterpret_cast<float *>(c->ws + c->L.vec_pb + c2 * c->L.vec_stride);
+  g.vec_pV = reinterpret_cast<float *>(c->ws + c->L.vec_pv + c2 * c->L.vec_stride);
+  g.vec_S = reinterpret_cast<unsigned *>(c->ws + c->L.vec_s + c4 * c->L.vec_stride);
   g.hist_B = a.hist_B;
-  g.hist_S = reinterpret_cast<unsigned *>(c->ws + c->L.hist_s + (size_t)par * c->L.hist_s_stride);
-  g.listB_key = reinterpret_cast<unsigned *>(c->ws + c->L.list_bk);
-  g.listB_pos = reinterpret_cast<int *>(c->ws + c->L.list_bp);
-  g.listB_v = reinterpret_cast<float *>(c->ws + c->L.list_bv);
-  g.listS_key = reinterpret_cast<unsigned *>(c->ws + c->L.list_sk);
-  g.listS_pos = reinterpret_cast<int *>(c->ws + c->L.list_sp);
-  g.cntB = reinterpret_cast<int *>(c->ws + c->L.cnt_b);
-  g.cntS = reinterpret_cast<int *>(c->ws + c->L.cnt_s);
-  g.recB = reinterpret_cast<int4 *>(c->ws + c->L.rec_b);
-  g.recS = reinterpret_cast<int4 *>(c->ws + c->L.rec_s);
+  g.hist_S = reinterpret_cast<unsigned *>(c->ws + c->L.hist_s + c4 * c->L.hist_s_stride);
+  char *lists = c->ws + c2 * c->L.list_stride;
+  g.listB_key = reinterpret_cast<unsigned *>(lists + c->L.list_bk);
+  g.listB_pos = reinterpret_cast<int *>(lists + c->L.list_bp);
+  g.listB_v = reinterpret_cast<float *>(lists + c->L.list_bv);
+  g.listS_key = reinterpret_cast<unsigned *>(lists + c->L.list_sk);
+  g.listS_pos = reinterpret_cast<int *>(lists + c->L.list_sp);
+  g.cntB = reinterpret_cast<int *>(c->ws + c->L.cnt_b + c2 * c->L.cnt_stride);
+  g.cntS = reinterpret_cast<int *>(c->ws + c->L.cnt_s + c2 * c->L.cnt_stride);
+  g.recB = reinterpret_cast<int4 *>(c->ws + c->L.rec_b + c2 * c->L.rec_stride);
+  g.recS = reinterpret_cast<int4 *>(c->ws + c->L.rec_s + c2 * c->L.rec_stride);
   g.lambda_ws = reinterpret_cast<float *>(c->ws + c->L.lambda);
   g.idx = d_idx;
   g.k = d_k;
@@ -839,11 +859,11 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.v_out = d_v_out;
   g.row_bytes = c->shape.head_dim * (r.bf16 ? 2 : 4);
   g.flat_heads = r.adaptive;
-  // final workgroups per (sequence, KV head): up to eight, but no more than
-  // keep the launch to the rounds over the CUs that one part per head needs
-  // (in a prompt call the score workgroups of the next layer share the
-  // launch, one 1024-thread workgroup per CU: a batch whose score
-  // workgroups alone fill the CUs takes more rounds with every part)
+  // final workgroups per (sequence, KV head): up to eight.  Beside the other
+  // jobs of a prompt call's select launch, no more than keep the launch to
+  // the rounds over the GPU that one part per head needs (two 1024-thread
+  // workgroups per CU): a batch whose other jobs fill it would take more
+  // rounds with every part.
   if (c->cus < 0) {
     int dev = 0;
     c->cus = 256;
@@ -854,9 +874,10 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   }
   {
     const int hkv = c->shape.num_kv_heads, heads = std::max(1, bt->batch * hkv);
-    const int score_wgs = r.st.total_segs * hkv;
-    auto rounds = [&](int p) { return (score_wgs + p * heads + c->cus - 1) / c->cus; };
+    const int others = 3 * r.st.total_segs * hkv;   // calibration, scores and candidate lists
+    auto rounds = [&](int p) { return (others + p * heads + 2 * c->cus - 1) / (2 * c->cus); };
     int p = std::max(1, std::min(8, c->cus / heads));
+    r.parts_alone = p;
     while (p > 1 && rounds(p) > rounds(1)) --p;
     g.parts = p;
   }
@@ -893,10 +914,10 @@ bacon_status stage_pass(bacon_ctx *c, const LayerRun &r, bool lse_merged, const 
   return BACON_OK;
 }
 
-// The adaptive allocation's budget table of a layer (by layer parity, where
-// given head budgets go otherwise).
+// The adaptive allocation's budget table of a layer (where given head
+// budgets go otherwise).
 int2 *alloc_table(bacon_ctx *c, int layer) {
-  return reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)(layer & 1) * c->L.hb_stride);
+  return reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)(layer % kCopies4) * c->L.hb_stride);
 }
 
 // Head-wise budgets of r's layer from its window score (adaptive allocation
@@ -919,26 +940,30 @@ bacon_status stage_alloc(bacon_ctx *c, const LayerRun &r, hipStream_t s) {
   return timed(c, KI_ALLOC, s, [&] { return launch_alloc(a, r.st, s); });
 }
 
-// Calibration of r's layer, with the previous layer's candidate lists and the
-// next layer's row normalisers in the same launch when given.
-bacon_status stage_a(bacon_ctx *c, const LayerRun &r, const LayerRun *prev, const PassArgs *next,
-                     hipStream_t s) {
-  if (!prev && !next) return timed(c, KI_SEGCAL, s, [&] { return launch_segcal(r.g, r.st, s); });
-  return timed(c, KI_SEL_A, s, [&] {
-    return launch_sel_a(r.g, prev ? &prev->g : nullptr, next, r.st, s);
-  });
-}
-
-// Scores of r's layer, with the previous layer's final top-K and compaction.
-bacon_status stage_b(bacon_ctx *c, const LayerRun &r, const LayerRun *prev, hipStream_t s) {
-  if (!prev) return timed(c, KI_SEGSCORE, s, [&] { return launch_segscore(r.g, r.st, s); });
-  return timed(c, KI_SEL_B, s, [&] { return launch_sel_b(r.g, &prev->g, r.st, prev->kmax, s); });
-}
-
-// Candidate lists, final top-K and compaction of r's layer.
-bacon_status stage_tail(bacon_ctx *c, const LayerRun &r, hipStream_t s) {
-  TRY(timed(c, KI_SEGCAND, s, [&] { return launch_segcand(r.g, r.st, s); }));
-  return timed(c, KI_FINAL, s, [&] { return launch_segfinal(r.g, r.st, r.kmax, s); });
+// One select launch: the jobs of up to four layers (NULL: none) and the next
+// layer's row normalisers (the layers share the sequences, so any of their
+// tables serves; the budgets come with each layer's own arguments).
+bacon_status stage_select(bacon_ctx *c, const LayerRun *cal, const LayerRun *score, const LayerRun *cand,
+                          const LayerRun *fin, const PassArgs *merge, hipStream_t s) {
+  SelJobs j;
+  SegArgs f;
+  j.cal = cal ? &cal->g : nullptr;
+  j.score = score ? &score->g : nullptr;
+  j.cand = cand ? &cand->g : nullptr;
+  j.merge = merge;
+  const bool alone = fin && !cal && !score && !cand;
+  if (fin) {
+    f = fin->g;
+    if (alone) f.parts = fin->parts_alone;
+    j.fin = &f;
+    j.fin_budget = fin->kmax;
+  }
+  const LayerRun *any = cal ? cal : score ? score : cand ? cand : fin;
+  if (!any) return BACON_OK;
+  const int njobs = (cal != nullptr) + (score != nullptr) + (cand != nullptr) + (fin != nullptr) + (merge != nullptr);
+  // (the table of the launch is the one its jobs without a budget table read)
+  const int kid = njobs > 1 ? KI_SEL : cal ? KI_SEGCAL : score ? KI_SEGSCORE : cand ? KI_SEGCAND : KI_FINAL;
+  return timed(c, kid, s, [&] { return launch_sel(j, any->st, s); });
 }
 
 // Test instrumentation: once r's layer has its lambda (after its score
@@ -969,14 +994,15 @@ bacon_status compress(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const 
   LayerRun r;
   TRY(plan_layer(c, layer, bt, d_q_win, d_k, d_v, d_lse, d_idx, d_k_out, d_v_out, r));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  TRY(head_table(c, bt, s, &r.g.hb, layer & 1));
+  TRY(head_table(c, bt, s, &r.g.hb, layer % kCopies4));
   if (r.adaptive) r.g.hb = alloc_table(c, layer);
   TRY(stage_pass(c, r, false, nullptr, s));
   TRY(stage_alloc(c, r, s));
-  TRY(stage_a(c, r, nullptr, nullptr, s));
-  TRY(stage_b(c, r, nullptr, s));
+  TRY(stage_select(c, &r, nullptr, nullptr, nullptr, nullptr, s));
+  TRY(stage_select(c, nullptr, &r, nullptr, nullptr, nullptr, s));
   TRY(stage_capture(c, r, bt, s));
-  TRY(stage_tail(c, r, s));
+  TRY(stage_select(c, nullptr, nullptr, &r, nullptr, nullptr, s));
+  TRY(stage_select(c, nullptr, nullptr, nullptr, &r, nullptr, s));
   c->next_layer = layer + 1;
   return BACON_OK;
 }
@@ -1032,41 +1058,35 @@ bacon_status bacon_compress_prompt(bacon_ctx *c, const bacon_batch *bt, int32_t 
     for (int i = 0; i < num_layers; ++i)
       if (!layer_batch[i]) return fail(BACON_ERR_INVALID, "layer_batch[%d] is NULL", i);
   std::vector<LayerRun> runs(num_layers);
-  int kmax = 0;
-  for (int i = 0; i < num_layers; ++i) {
+  for (int i = 0; i < num_layers; ++i)
     TRY(plan_layer(c, first_layer + i, lbt(i), d_q_win[i], d_k[i], d_v[i],
                    d_lse ? d_lse[i] : nullptr, d_idx[i], d_k_out[i], d_v_out[i], runs[i]));
-    kmax = std::max(kmax, runs[i].kmax);
-  }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // Layers in flight at once: layer l's candidate lists run in the launch of
-  // layer l+1's calibration, its final top-K and compaction in the launch of
-  // layer l+1's scores (when that launch's LDS fits), and layer l+1's pass 1
-  // in the launch of layer l's pass 2.  The per-head budget table of a
-  // layer (if any) alternates with its parity: it is written after the
-  // launch that held the final kernel of the layer two before.
-  const bool overlap = sel_b_lds_bytes(kmax, c->shape.window) <= (size_t)kLdsBytes;
+  // Layers in flight at once: the select launch that follows layer l's K
+  // passes holds its calibration, the scores of layer l - 1, the candidate
+  // lists of l - 2 and the final job of l - 3, and layer l + 1's pass 1 runs
+  // in the launch of layer l's pass 2.  The last three select launches have
+  // no K pass before them.
+  auto at = [&](int i) -> const LayerRun * { return i >= 0 && i < num_layers ? &runs[i] : nullptr; };
   bool merged = false;
-  for (int i = 0; i < num_layers; ++i) {
-    LayerRun &r = runs[i];
-    TRY(head_table(c, lbt(i), s, &r.g.hb, r.layer & 1));
-    if (r.adaptive) r.g.hb = alloc_table(c, r.layer);
-    if (layer_batch) TRY(seq_table(c, r.st, s, &r.g.sb, r.layer & 1));
-    const LayerRun *prev = (overlap && i > 0) ? &runs[i - 1] : nullptr;
-    // the next layer's pass 1 rides in this layer's pass-2 launch, unless the
-    // next layer reads K once (single-read pass) or has its normalisers given
-    const PassArgs *next = (!r.lse && !r.single && i + 1 < num_layers && !runs[i + 1].single)
-                               ? &runs[i + 1].a : nullptr;
-    TRY(stage_pass(c, r, merged, next, s));
-    TRY(stage_alloc(c, r, s));
-    TRY(stage_a(c, r, prev, next, s));
-    TRY(stage_b(c, r, prev, s));
-    TRY(stage_capture(c, r, lbt(i), s));
-    if (!overlap) TRY(stage_tail(c, r, s));
-    merged = next != nullptr;
-    c->next_layer = r.layer + 1;
+  for (int i = 0; i < num_layers + 3; ++i) {
+    const PassArgs *next = nullptr;
+    if (i < num_layers) {
+      LayerRun &r = runs[i];
+      TRY(head_table(c, lbt(i), s, &r.g.hb, r.layer % kCopies4));
+      if (r.adaptive) r.g.hb = alloc_table(c, r.layer);
+      if (layer_batch) TRY(seq_table(c, r.st, s, &r.g.sb, r.layer % kCopies4));
+      // the next layer's pass 1 rides in this layer's pass-2 launch, unless the
+      // next layer reads K once (single-read pass) or has its normalisers given
+      if (!r.lse && !r.single && i + 1 < num_layers && !runs[i + 1].single) next = &runs[i + 1].a;
+      TRY(stage_pass(c, r, merged, next, s));
+      TRY(stage_alloc(c, r, s));
+      merged = next != nullptr;
+      c->next_layer = r.layer + 1;
+    }
+    TRY(stage_select(c, at(i), at(i - 1), at(i - 2), at(i - 3), next, s));
+    if (i >= 1 && i <= num_layers) TRY(stage_capture(c, runs[i - 1], lbt(i - 1), s));
   }
-  if (overlap) TRY(stage_tail(c, runs[num_layers - 1], s));
   return BACON_OK;
 }
 

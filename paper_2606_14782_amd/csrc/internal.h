@@ -255,24 +255,17 @@ hipError_t launch_select(int mode, int max_len, const SelArgs &a, const SeqTable
                          hipStream_t s);
 hipError_t launch_elem(const ElemArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_lse_merge(const PassArgs &a, const SeqTable &st, hipStream_t s);
-hipError_t launch_segcal(const SegArgs &a, const SeqTable &st, hipStream_t s);
-// Launches with work of two or three layers of a prompt: the calibration of
-// g's layer with the previous layer's candidate lists (gp, may be NULL) and
-// the next layer's row normalisers (m, may be NULL); the scores of g's layer
-// with the previous layer's final top-K and compaction (gp, may be NULL).
-hipError_t launch_sel_a(const SegArgs &g, const SegArgs *gp, const PassArgs *m, const SeqTable &st,
-                       hipStream_t s);
-hipError_t launch_sel_b(const SegArgs &g, const SegArgs *gp, const SeqTable &st, int max_budget,
-                        hipStream_t s);
-// LDS of a k_sel_b workgroup (static of both jobs plus the row table).
-size_t sel_b_lds_bytes(int max_budget, int window);
-hipError_t launch_segscore(const SegArgs &a, const SeqTable &st, hipStream_t s);
-hipError_t launch_segcand(const SegArgs &a, const SeqTable &st, hipStream_t s);
+// The jobs of one select launch, each of its own layer (NULL: none).
+struct SelJobs {
+  const SegArgs *cal = nullptr, *score = nullptr, *cand = nullptr, *fin = nullptr;
+  const PassArgs *merge = nullptr;   // row normalisers to merge
+  int fin_budget = 0;                // largest budget of fin's layer
+};
+hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s);
 // LDS of the final workgroup for budgets up to max_budget.
 size_t final_lds_bytes(int max_budget, int window);
 size_t alloc_lds_bytes(int hkv);
 hipError_t launch_alloc(const AllocArgs &a, const SeqTable &st, hipStream_t s);
-hipError_t launch_segfinal(const SegArgs &a, const SeqTable &st, int max_budget, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_zero(unsigned *p, int64_t n, hipStream_t s);
 // Device address of the static scratch on the current device (looked up

@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <math.h>
 #include <stdint.h>
 
@@ -194,11 +195,11 @@ __device__ __forceinline__ int find_seq(const SeqTable &st, int chunk) {
 }
 
 // Dynamic LDS above 64 KiB has to be allowed per kernel before launch.
-template <typename Kern>
-static void allow_lds(Kern kernel, size_t bytes) {
-  static size_t granted = 0;
+template <auto Kern>
+static void allow_lds(size_t bytes) {
+  static std::atomic<size_t> granted{0};
   if (bytes > 64 * 1024 && bytes > granted) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(Kern),
                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     granted = bytes;
   }
@@ -555,7 +556,7 @@ static hipError_t launch_pass_dual_t(const PassArgs &a2, const PassArgs &a1, con
                            pass_lds_bytes(PASS_LSE, BF16, D, a1.Rpad, a1.chunk));
   if (lds > kLdsBytes || a1.Rpad != a2.Rpad || a1.chunk != a2.chunk) return hipErrorInvalidValue;
   dim3 grid(2 * st.total_chunks, a2.Hkv), block(64 * nw);
-  allow_lds(k_pass_dual<BF16, D, W32>, lds);
+  allow_lds<k_pass_dual<BF16, D, W32>>(lds);
   hipLaunchKernelGGL((k_pass_dual<BF16, D, W32>), grid, block, lds, s, a2, a1, st);
   return hipGetLastError();
 }
@@ -580,7 +581,7 @@ static hipError_t launch_pass_t(const PassArgs &a, const SeqTable &st, hipStream
   const int lds = pass_lds_bytes(MODE, BF16, D, a.Rpad, a.chunk);
   if (lds > kLdsBytes) return hipErrorInvalidValue;
   dim3 grid(st.total_chunks, a.Hkv), block(64 * nw);
-  allow_lds(k_pass<MODE, BF16, D, W32>, lds);
+  allow_lds<k_pass<MODE, BF16, D, W32>>(lds);
   hipLaunchKernelGGL((k_pass<MODE, BF16, D, W32>), grid, block, lds, s, a, st);
   return hipGetLastError();
 }
@@ -1060,8 +1061,8 @@ static hipError_t launch_dual_t(const PassArgs &a2, const PassArgs &a1, const Se
                                 hipStream_t s) {
   const int lds = kr_lds_bytes(true, D, a2.Rpad);
   if (lds > kLdsBytes) return hipErrorInvalidValue;
-  auto kern = k_krdual<D, W32, NRT>;
-  allow_lds(kern, lds);
+  constexpr auto kern = k_krdual<D, W32, NRT>;
+  allow_lds<kern>(lds);
   hipLaunchKernelGGL(kern, dim3(2 * st.total_chunks, a2.Hkv), dim3(64 * kKrWaves), lds, s, a2, a1,
                      st);
   return hipGetLastError();
@@ -1079,8 +1080,8 @@ template <int MODE, int D, bool W32, int NRT>
 static hipError_t launch_kr_t(const PassArgs &a, const SeqTable &st, hipStream_t s) {
   const int lds = kr_lds_bytes(true, D, a.Rpad);
   if (lds > kLdsBytes) return hipErrorInvalidValue;
-  auto kern = k_krpass<MODE, D, W32, NRT>;
-  allow_lds(kern, lds);
+  constexpr auto kern = k_krpass<MODE, D, W32, NRT>;
+  allow_lds<kern>(lds);
   hipLaunchKernelGGL(kern, dim3(st.total_chunks, a.Hkv), dim3(64 * kKrWaves), lds, s, a, st);
   return hipGetLastError();
 }
@@ -1675,8 +1676,8 @@ template <int D, bool W32, int NRT>
 static hipError_t launch_single_t(const PassArgs &a, const SeqTable &st, hipStream_t s) {
   const int lds = single_lds_bytes(D, a.Rpad);
   if (lds > kLdsBytes / 2) return hipErrorInvalidValue;
-  auto kern = k_single<D, W32, NRT>;
-  allow_lds(kern, lds);
+  constexpr auto kern = k_single<D, W32, NRT>;
+  allow_lds<kern>(lds);
   hipLaunchKernelGGL(kern, dim3(st.total_chunks * a.Hkv), dim3(64 * kKrWaves), lds, s, a, st);
   return hipGetLastError();
 }
@@ -2532,10 +2533,10 @@ hipError_t launch_select(int mode, int max_len, const SelArgs &a, const SeqTable
   const size_t lds = select_lds_bytes(mode, max_len) - sizeof(SelShared);
   if (lds + sizeof(SelShared) > kLdsBytes) return hipErrorInvalidValue;
   if (mode == SEL_CALIB) {
-    allow_lds(k_select<SEL_CALIB>, lds);
+    allow_lds<k_select<SEL_CALIB>>(lds);
     hipLaunchKernelGGL((k_select<SEL_CALIB>), grid, block, lds, s, a, st);
   } else {
-    allow_lds(k_select<SEL_TOPK>, lds);
+    allow_lds<k_select<SEL_TOPK>>(lds);
     hipLaunchKernelGGL((k_select<SEL_TOPK>), grid, block, lds, s, a, st);
   }
   return hipGetLastError();
@@ -2570,9 +2571,8 @@ hipError_t launch_select(int mode, int max_len, const SelArgs &a, const SeqTable
 //    the lists, the kept positions in ascending order, and each workgroup's
 //    share of the compacted cache rows.
 // Boundary bins of up to kSegCandCap entries are resolved on the lists
-// (large ones narrowed to a sub-bin first).  In a prompt call the four run
-// as two launches per layer that also carry the previous and next layers'
-// work (k_sel_a, k_sel_b).
+// (large ones narrowed to a sub-bin first).  In a prompt call one launch per layer
+// holds the four jobs, each of another layer (k_sel).
 constexpr int kSegPer = kSegLen / kSegThreads;             // positions per thread (strided)
 constexpr int kSegWin = kSegLen + 2 * kPoolHalo;           // segment plus pool halo
 constexpr int kSegWinJ = (kSegWin + kSegThreads - 1) / kSegThreads;
@@ -2784,6 +2784,58 @@ __device__ __forceinline__ void stream_threshold(const unsigned *gh, KeyF keyf, 
   lds_barrier();
 }
 
+// LDS of the select jobs.  The jobs of one launch share the dynamic LDS of
+// their workgroup (each takes the whole of it as its own struct), so that a
+// workgroup holds the largest job's LDS and not the sum of all of them: with
+// at most 80 KiB, two 1024-thread workgroups run per CU.
+extern __shared__ __align__(16) unsigned char sel_smem[];
+// zeroed slots past the end of the calibration's LDS windows: the
+// neighbourhood sums of the last window positions read E up to two slots
+// past its window (at the largest radius)
+constexpr int kSegTaps = 8;
+struct CalLds {
+  float Bs[kSegWin + kSegTaps], Vs[kSegWin + kSegTaps];
+  float Es[kSegE + kSegTaps];
+  SelSharedT<kSegThreads> ss;
+  unsigned pre[kSegPer * (kSegThreads / 64) + 1];
+};
+struct ScoreLds {
+  // the score histogram; before it is cleared and counted, the scratch of
+  // the moments
+  union {
+    unsigned hist[kHBins];
+    float2 mom[kMomChunk];
+    double sums[4 * kSegThreads];
+  };
+  // boundary-bin entries; after lambda, the score window of the max pool
+  union {
+    struct {
+      unsigned ckey[kSegCandCap];
+      int cpos[kSegCandCap];
+    };
+    float sw[kSegWin];
+  };
+  SelSharedT<kSegThreads> ss;
+  unsigned pre[kAllPer * (kSegThreads / 64) + 1];
+  int scnt[kMaxSegs];
+  float vref_s;
+};
+struct CandLds {
+  SelSharedT<kSegThreads> ss;
+  unsigned pre[kSegPer * (kSegThreads / 64) + 1];
+};
+struct FinalLds {
+  unsigned ckey[kSegCandCap];
+  int cpos[kSegCandCap];
+  SelSharedT<kSegThreads> ss;
+  unsigned pre[kAllPer * (kSegThreads / 64) + 1];
+  int scnt[kMaxSegs];
+  // the row table [K + W] follows
+};
+struct MergeLds {
+  float2 mrg[kSegThreads / kMergeThreads][kMergeParts][kMergeRows];
+};
+
 // The lists of the nseg segments of a (sequence, KV head) as one sequence of
 // entries e = t + j*NT: segment e / cap, slot e % cap.  `fits` is false when
 // a segment's count exceeds cap.
@@ -2795,14 +2847,11 @@ struct ListView {
 // Calibration kernel (segment_calib).
 __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st, int gs, int h, int b) {
   constexpr int NT = kSegThreads, PER = kSegPer, NW = NT / 64;
-  // zeroed slots past the end of the LDS windows: the neighbourhood sums of
-  // the last window positions read E up to two slots past its window (at
-  // the largest radius)
-  constexpr int TAPS = 8;
-  __shared__ float Bs[kSegWin + TAPS], Vs[kSegWin + TAPS];
-  __shared__ float Es[kSegE + TAPS];
-  __shared__ SelSharedT<NT> ss;
-  __shared__ unsigned pre[PER * NW + 1];
+  constexpr int TAPS = kSegTaps;
+  CalLds &lds = *reinterpret_cast<CalLds *>(sel_smem);
+  float *const Bs = lds.Bs, *const Vs = lds.Vs, *const Es = lds.Es;
+  SelSharedT<NT> &ss = lds.ss;
+  unsigned *const pre = lds.pre;
   const int t = threadIdx.x;
   const int wave = t >> 6;
   const int sg = gs - st.seg_base[b];
@@ -3016,10 +3065,6 @@ __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st
   if (sg == 0 && t == 0) a.recB[b * a.Hkv + h] = make_int4(beta, above, M - above, (int)cntb);
 }
 
-__global__ __launch_bounds__(kSegThreads) void k_segcal(SegArgs a, SeqTable st) {
-  segcal_body(a, st, blockIdx.x, blockIdx.y, find_seg(st, blockIdx.x));
-}
-
 // Loads the selection record and the segments' lists of a (sequence, KV
 // head) into registers as one sequence of entries e = t + j*NT in (segment,
 // slot) order, which is position order.  First round: kListSpec slots per
@@ -3157,6 +3202,7 @@ __device__ __forceinline__ void whole_topk_stream(const SegArgs &a, int64_t base
 // candidates in registers, the exact threshold over them; V is read for the
 // members only.  Kept out of line so that its registers do not weigh on the
 // list path of the calling kernel.
+template <bool ONE>
 __device__ __attribute__((noinline)) void whole_moments(const SegArgs &a, int64_t base, int nc, int M,
                                                          const unsigned *gh, SelSharedT<kSegThreads> &ss,
                                                          unsigned *ckey, int *cpos, unsigned *pre,
@@ -3207,19 +3253,18 @@ __device__ __attribute__((noinline)) void whole_moments(const SegArgs &a, int64_
 
 // Score kernel (segment_score).
 // (The select bodies take their arguments by value: a reference to a kernel
-// argument that reaches an out-of-line call costs a stack copy and spills.)
+// argument that reaches an out-of-line call costs a stack copy and spills.
+// ONE: for a launch of this job alone; the out-of-line functions take the
+// register bound of every kernel that calls them, so each bound has its own.)
+template <bool ONE>
 __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int gs, int h, int b) {
-  constexpr int NT = kSegThreads, PER = kSegPer, NW = NT / 64;
-  __shared__ unsigned hist[kHBins];
-  __shared__ unsigned ckey[kSegCandCap];
-  __shared__ int cpos[kSegCandCap];
-  __shared__ SelSharedT<NT> ss;
-  __shared__ unsigned pre[kAllPer * NW + 1];
-  __shared__ __align__(16) float2 mom[kMomChunk];
-  __shared__ __align__(16) int scnt[kMaxSegs];
-  __shared__ float vref_s;
+  constexpr int NT = kSegThreads, PER = kSegPer;
+  ScoreLds &lds = *reinterpret_cast<ScoreLds *>(sel_smem);
+  unsigned *const hist = lds.hist, *const ckey = lds.ckey, *const pre = lds.pre;
+  int *const cpos = lds.cpos, *const scnt = lds.scnt;
+  SelSharedT<NT> &ss = lds.ss;
+  float &vref_s = lds.vref_s;
   const int t = threadIdx.x;
-  const int wave = t >> 6;
   const int sg = gs - st.seg_base[b];
   const int n = st.cu[b + 1] - st.cu[b];
   const int nc = n - a.W;
@@ -3227,7 +3272,6 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
   const int ncand = max(0, min(i0 + kSegLen, nc) - i0);
   const int64_t base = (int64_t)h * a.T + st.cu[b];
   const int64_t hrow = ((int64_t)b * a.Hkv + h) * kHBins;
-  for (int q = t; q < kHBins; q += NT) hist[q] = 0u;
 
   // what the pooled score is made of does not depend on lambda: in flight
   // first.  Mean of S: the pooled B and V (pool(B + lambda V) = pool(B) +
@@ -3286,14 +3330,16 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
       if (nc > kAllPer * kSegThreads)
         whole_moments_stream(a, base, nc, M, a.hist_B + hrow * kHCopies, ss, part);
       else
-        whole_moments(a, base, nc, M, a.hist_B + hrow * kHCopies, ss, ckey, cpos, pre, mom, part);
+        whole_moments<ONE>(a, base, nc, M, a.hist_B + hrow * kHCopies, ss, ckey, cpos, pre, lds.mom, part);
       s0 = part[0]; s1 = part[1]; s2 = part[2]; s3 = part[3];
       bref_set = part[4];
     }
     // the moment scratch is free here (its fallback user is done)
     lam = block_lambda<NT>(s0, s1, s2, s3, M, bref_set, a.gamma, a.eps, a.b_floor,
-                           reinterpret_cast<double *>(mom), ss, &vref_s);
+                           lds.sums, ss, &vref_s);
   }
+  // the moment scratch is free: the histogram takes its place
+  for (int q = 4 * t; q < kHBins; q += 4 * NT) *reinterpret_cast<uint4 *>(hist + q) = make_uint4(0u, 0u, 0u, 0u);
   if (sg == 0 && t == 0) {
     a.lambda_ws[b * a.Hkv + h] = lam;
     if (a.out_lambda) a.out_lambda[b * a.Hkv + h] = lam;
@@ -3302,10 +3348,10 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
   // pooled score keys of the segment, and their histogram
   lds_barrier();
   if (max_s) {
-    // S over the segment widened by the pool halo in LDS (the moment scratch
-    // is free now), -inf outside the candidate set, then the max over each
+    // S over the segment widened by the pool halo in LDS (the boundary-bin
+    // entries are done with), -inf outside the candidate set, then the max over each
     // pool window
-    float *sw = reinterpret_cast<float *>(mom);
+    float *const sw = lds.sw;
     const int w0 = i0 - kPoolHalo;                   // position of window slot 0
     float wb[kSegWinJ], wv[kSegWinJ];
 #pragma unroll
@@ -3356,8 +3402,9 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
 // pooled score and the segment's list of entries at or above it.
 __device__ __forceinline__ void segcand_body(SegArgs a, const SeqTable &st, int gs, int h, int b) {
   constexpr int NT = kSegThreads, PER = kSegPer, NW = NT / 64;
-  __shared__ SelSharedT<NT> ss;
-  __shared__ unsigned pre[PER * NW + 1];
+  CandLds &lds = *reinterpret_cast<CandLds *>(sel_smem);
+  SelSharedT<NT> &ss = lds.ss;
+  unsigned *const pre = lds.pre;
   const int t = threadIdx.x;
   const int wave = t >> 6;
   const int sg = gs - st.seg_base[b];
@@ -3366,6 +3413,15 @@ __device__ __forceinline__ void segcand_body(SegArgs a, const SeqTable &st, int 
   const int i0 = sg * kSegLen;
   const int ncand = max(0, min(i0 + kSegLen, nc) - i0);
   const int64_t base = (int64_t)h * a.T + st.cu[b];
+  {
+    // clear this segment's slice of the B histogram for the layer that takes
+    // it next (its readers, the calibration and score jobs, are done)
+    const int nseg = st.seg_base[b + 1] - st.seg_base[b];
+    const int sl = 4 * ((kHCopies * kHBins / 4 + nseg - 1) / nseg);
+    unsigned *hb = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+    for (int q = sg * sl + 4 * t; q < min(kHCopies * kHBins, (sg + 1) * sl); q += 4 * NT)
+      *reinterpret_cast<u32x4 *>(hb + q) = u32x4{0u, 0u, 0u, 0u};
+  }
   const int kept = min(sel_head_budget(st, a.hb, a.Hkv, b, h, a.sb), nc);
   if (kept <= 0 || kept == nc) return;               // none or all kept: no list needed
   unsigned cb[kHPer];
@@ -3398,6 +3454,7 @@ __device__ __forceinline__ void segcand_body(SegArgs a, const SeqTable &st, int 
 // the pooled score keys of all candidates in registers, the exact threshold
 // over them, the kept positions in ascending order into tbl (and idx unless
 // it is null).  Kept out of line like whole_moments.
+template <bool ONE>
 __device__ __attribute__((noinline)) void whole_topk(const SegArgs &a, int64_t base, int nc, int kept,
                                                       const unsigned *gh, int32_t *idx, int *tbl,
                                                       SelSharedT<kSegThreads> &ss, unsigned *ckey,
@@ -3442,15 +3499,15 @@ __device__ __attribute__((noinline)) void whole_topk(const SegArgs &a, int64_t b
 // select the same top-K; part 0 writes the indices, each part gathers its
 // share of the compacted rows (kept positions, the W window rows, zero rows
 // up to K + W).
+template <bool ONE>
 __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int part, int b,
                                            int h) {
   constexpr int NT = kSegThreads, NW = NT / 64;
-  extern __shared__ __align__(16) int tbl[];         // [K + W] source position of each row
-  __shared__ unsigned ckey[kSegCandCap];
-  __shared__ int cpos[kSegCandCap];
-  __shared__ SelSharedT<NT> ss;
-  __shared__ unsigned pre[kAllPer * NW + 1];
-  __shared__ __align__(16) int scnt[kMaxSegs];
+  FinalLds &lds = *reinterpret_cast<FinalLds *>(sel_smem);
+  int *const tbl = reinterpret_cast<int *>(sel_smem + sizeof(FinalLds));   // [K + W] source position of each row
+  unsigned *const ckey = lds.ckey, *const pre = lds.pre;
+  int *const cpos = lds.cpos, *const scnt = lds.scnt;
+  SelSharedT<NT> &ss = lds.ss;
   const int t = threadIdx.x;
   const int wave = t >> 6;
   const int n = st.cu[b + 1] - st.cu[b];
@@ -3507,7 +3564,7 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
         whole_topk_stream(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins,
                           part == 0 ? idx : nullptr, tbl, ss);
       else
-        whole_topk(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins, part == 0 ? idx : nullptr,
+        whole_topk<ONE>(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins, part == 0 ? idx : nullptr,
                  tbl, ss, ckey, cpos, pre);
     }
   }
@@ -3516,16 +3573,6 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
   for (int w = t; w < a.W; w += NT) tbl[kept + w] = nc + w;
   for (int j = kept + a.W + t; j < C + a.W; j += NT) tbl[j] = -1;
   lds_barrier();
-
-  {
-    // clear this part's slice of the B histogram for the next layer (its
-    // readers, the calibration and score kernels, are done)
-    constexpr int HB = kHCopies * kHBins;
-    const int sl = 4 * ((HB / 4 + a.parts - 1) / a.parts);
-    unsigned *hb = a.hist_B + ((int64_t)b * a.Hkv + h) * HB;
-    for (int q = part * sl + 4 * t; q < min(HB, (part + 1) * sl); q += 4 * NT)
-      *reinterpret_cast<u32x4 *>(hb + q) = u32x4{0u, 0u, 0u, 0u};
-  }
 
   // this part's rows of the compacted cache
   const int rows = C + a.W;
@@ -3569,135 +3616,111 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
   }
 }
 
-__global__ __launch_bounds__(kSegThreads) void k_segscore(SegArgs a, SeqTable st) {
-  segscore_body(a, st, blockIdx.x, blockIdx.y, find_seg(st, blockIdx.x));
+// One select launch: any of the four jobs, each of a layer of its own, and the
+// next layer's row normalisers.  In a prompt call a launch holds the
+// calibration of layer l, the scores of layer l - 1, the candidate lists of
+// layer l - 2 and the final top-K with the gather of layer l - 3: each job is
+// a chain of dependent memory rounds and barriers of 4 to 9 us that keeps few
+// of a CU's units busy, so the four side by side take about as long as the
+// longest of them (32K-token prompt, 32/8 heads: one launch of 12.6 us per
+// layer where two of 8.2 and 9.9 us ran before; LLaVA-shaped 11.6 against 8.0
+// and 9.2, 128K tokens 34 against 22 and 40).
+// The jobs of one launch share no buffer (the host gives each layer in
+// flight its own copies).
+//
+// Jobs lie along blockIdx.y and KV heads along blockIdx.x, so that with eight
+// KV heads a head's workgroups share one XCD; the longest jobs come first.
+// 64 vector registers and at most 80 KiB of LDS (budgets up to about 13000):
+// two workgroups per CU.  A launch of one job has a kernel of its own
+// (k_sel_one), without the register bound, which costs the scores and the
+// final job spills: 7.8 against 9.1 us (four short sequences, 14/2 heads).
+enum SelJob { JOB_SCORE, JOB_FINAL, JOB_CAL, JOB_CAND };
+template <int JOB>
+__global__ __launch_bounds__(kSegThreads) void k_sel_one(SegArgs a, SeqTable st) {
+  const int h = blockIdx.x, x = blockIdx.y;
+  if constexpr (JOB == JOB_SCORE) segscore_body<true>(a, st, x, h, find_seg(st, x));
+  else if constexpr (JOB == JOB_FINAL) final_body<true>(a, st, x % a.parts, x / a.parts, h);
+  else if constexpr (JOB == JOB_CAL) segcal_body(a, st, x, h, find_seg(st, x));
+  else segcand_body(a, st, x, h, find_seg(st, x));
 }
 
-__global__ __launch_bounds__(kSegThreads) void k_segcand(SegArgs a, SeqTable st) {
-  segcand_body(a, st, blockIdx.x, blockIdx.y, find_seg(st, blockIdx.x));
-}
-
-__global__ __launch_bounds__(kSegThreads) void k_segfinal(SegArgs a, SeqTable st) {
-  final_body(a, st, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-// Launches that carry work of two or three layers (a prompt's layers in
-// flight at once; the jobs of one launch share no buffer, see the host's
-// schedule):
-//  * k_sel_a, jobs along blockIdx.y and KV heads along blockIdx.x: [0, nseg)
-//    the calibration of this layer (g), [nseg, nseg + ncand) the candidate
-//    lists of the previous layer (gp), then the next layer's row
-//    normalisers (m; each workgroup takes kSegThreads / kMergeThreads row
-//    groups of a sequence).  Workgroups are dispatched x first, so every
-//    head's calibration (the longest job) is dispatched before any shorter
-//    one, and a grid beyond one round of the CUs leaves short jobs waiting.
-//  * k_sel_b, jobs along blockIdx.x per KV head (blockIdx.y): [0, nfinal)
-//    the final top-K and compaction of the previous layer (parts per
-//    sequence), then the scores of this layer.
-__global__ __launch_bounds__(kSegThreads) void k_sel_a(SegArgs g, SegArgs gp, PassArgs m, SeqTable st,
-                                                      int ncand, int nmerge) {
-  const int h = blockIdx.x, job = blockIdx.y, nseg = st.total_segs;
-  if (job < nseg) {
-    segcal_body(g, st, job, h, find_seg(st, job));
+__global__ __launch_bounds__(kSegThreads, 2 * kSegThreads / 256) void k_sel(
+    SegArgs score, SegArgs fin, SegArgs cal, SegArgs cand, PassArgs m, SeqTable st, int nscore,
+    int nfinal, int ncal, int nmerge, int ncand) {
+  const int h = blockIdx.x;
+  int x = blockIdx.y;
+  if (x < nscore) {
+    segscore_body<false>(score, st, x, h, find_seg(st, x));
     return;
   }
-  const int x = job - nseg;
-  if (x < ncand) {
-    segcand_body(gp, st, x, h, find_seg(st, x));
-  } else if (x < ncand + nmerge) {
+  x -= nscore;
+  if (x < nfinal) {
+    final_body<false>(fin, st, x % fin.parts, x / fin.parts, h);
+    return;
+  }
+  x -= nfinal;
+  if (x < ncal) {
+    segcal_body(cal, st, x, h, find_seg(st, x));
+    return;
+  }
+  x -= ncal;
+  if (x < nmerge) {
     constexpr int groups = kSegThreads / kMergeThreads;
-    __shared__ float2 mrg[groups][kMergeParts][kMergeRows];
+    MergeLds &lds = *reinterpret_cast<MergeLds *>(sel_smem);
     const int per_seq = (m.Rpad / kMergeRows + groups - 1) / groups;
-    const int q = x - ncand, b = q / per_seq;
+    const int b = x / per_seq;
     const int grp = threadIdx.x / kMergeThreads;
-    const int rg = (q - b * per_seq) * groups + grp;
-    merge_rows(m, st, rg, b, h, threadIdx.x % kMergeThreads, mrg[grp], rg * kMergeRows < m.Rpad);
+    const int rg = (x - b * per_seq) * groups + grp;
+    merge_rows(m, st, rg, b, h, threadIdx.x % kMergeThreads, lds.mrg[grp], rg * kMergeRows < m.Rpad);
+    return;
   }
-}
-
-__global__ __launch_bounds__(kSegThreads) void k_sel_b(SegArgs g, SegArgs gp, SeqTable st, int nfinal) {
-  const int h = blockIdx.y, nseg = st.total_segs, batch = st.batch;
-  // both table words in one round of scalar loads (the job split below
-  // would otherwise wait for each in turn); a batch of one sequence takes a
-  // copy of the score body with b = 0, whose per-sequence table reads sit at
-  // fixed kernel-argument offsets and need no sequence search first.  (Not
-  // in k_sel_a: there the copies' scalar registers would cost the second
-  // workgroup per CU, and they did not pay.)
-  asm volatile("" ::"s"(nseg), "s"(batch));
-  if ((int)blockIdx.x < nseg) {
-    if (batch == 1)
-      segscore_body(g, st, blockIdx.x, h, 0);
-    else
-      segscore_body(g, st, blockIdx.x, h, find_seg(st, blockIdx.x));
-  } else {
-    const int x = blockIdx.x - nseg;
-    final_body(gp, st, x % gp.parts, x / gp.parts, h);
-  }
-  (void)nfinal;
+  x -= nmerge;
+  if (x < ncand) segcand_body(cand, st, x, h, find_seg(st, x));
 }
 
 size_t final_lds_bytes(int max_budget, int window) {
-  return (size_t)(max_budget + window) * sizeof(int) + 2 * kSegCandCap * sizeof(unsigned) +
-         sizeof(SelSharedT<kSegThreads>) + (kAllPer * (kSegThreads / 64) + 1) * sizeof(unsigned) +
-         kMaxSegs * sizeof(int);
+  return sizeof(FinalLds) + (size_t)(max_budget + window) * sizeof(int);
 }
 
-hipError_t launch_segcal(const SegArgs &a, const SeqTable &st, hipStream_t s) {
-  dim3 grid(st.total_segs, a.Hkv), block(kSegThreads);
-  hipLaunchKernelGGL(k_segcal, grid, block, 0, s, a, st);
+template <int JOB>
+static hipError_t launch_sel_one(const SegArgs &a, const SeqTable &st, int jobs, size_t lds, hipStream_t s) {
+  allow_lds<k_sel_one<JOB>>(lds);
+  hipLaunchKernelGGL(k_sel_one<JOB>, dim3(a.Hkv, jobs), dim3(kSegThreads), lds, s, a, st);
   return hipGetLastError();
 }
 
-hipError_t launch_sel_a(const SegArgs &g, const SegArgs *gp, const PassArgs *m, const SeqTable &st,
-                       hipStream_t s) {
+hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s) {
   constexpr int groups = kSegThreads / kMergeThreads;
-  int nmerge = 0;
-  if (m) {
-    if (m->Rpad % kMergeRows || m->Hkv != g.Hkv) return hipErrorInvalidValue;
-    nmerge = st.batch * ((m->Rpad / kMergeRows + groups - 1) / groups);
+  const SegArgs *any = j.score ? j.score : j.fin ? j.fin : j.cal ? j.cal : j.cand;
+  if (!any) return hipErrorInvalidValue;
+  int nmerge = 0, nfinal = 0;
+  size_t lds = sizeof(CandLds);
+  if (j.score) lds = std::max(lds, sizeof(ScoreLds));
+  if (j.cal) lds = std::max(lds, sizeof(CalLds));
+  if (j.merge) {
+    if (j.merge->Rpad % kMergeRows || j.merge->Hkv != any->Hkv) return hipErrorInvalidValue;
+    nmerge = st.batch * ((j.merge->Rpad / kMergeRows + groups - 1) / groups);
+    lds = std::max(lds, sizeof(MergeLds));
   }
-  const int ncand = gp ? st.total_segs : 0;
-  dim3 grid(g.Hkv, ncand + nmerge + st.total_segs), block(kSegThreads);
-  hipLaunchKernelGGL(k_sel_a, grid, block, 0, s, g, gp ? *gp : g, m ? *m : PassArgs{}, st, ncand,
-                     nmerge);
-  return hipGetLastError();
-}
-
-size_t sel_b_lds_bytes(int max_budget, int window) {
-  hipFuncAttributes fa{};
-  if (hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(k_sel_b)) != hipSuccess) return SIZE_MAX;
-  return fa.sharedSizeBytes + (size_t)(max_budget + window) * sizeof(int);
-}
-
-hipError_t launch_sel_b(const SegArgs &g, const SegArgs *gp, const SeqTable &st, int max_budget,
-                        hipStream_t s) {
-  const size_t lds = gp ? (size_t)(max_budget + g.W) * sizeof(int) : 0;
-  if (gp && (sel_b_lds_bytes(max_budget, g.W) > (size_t)kLdsBytes || gp->parts < 1))
-    return hipErrorInvalidValue;
-  const int nfinal = gp ? gp->parts * st.batch : 0;
-  allow_lds(k_sel_b, lds);
-  hipLaunchKernelGGL(k_sel_b, dim3(nfinal + st.total_segs, g.Hkv), dim3(kSegThreads), lds, s, g,
-                     gp ? *gp : g, st, nfinal);
-  return hipGetLastError();
-}
-
-hipError_t launch_segscore(const SegArgs &a, const SeqTable &st, hipStream_t s) {
-  dim3 grid(st.total_segs, a.Hkv), block(kSegThreads);
-  hipLaunchKernelGGL(k_segscore, grid, block, 0, s, a, st);
-  return hipGetLastError();
-}
-
-hipError_t launch_segcand(const SegArgs &a, const SeqTable &st, hipStream_t s) {
-  dim3 grid(st.total_segs, a.Hkv), block(kSegThreads);
-  hipLaunchKernelGGL(k_segcand, grid, block, 0, s, a, st);
-  return hipGetLastError();
-}
-
-hipError_t launch_segfinal(const SegArgs &a, const SeqTable &st, int max_budget, hipStream_t s) {
-  const size_t lds = (size_t)(max_budget + a.W) * sizeof(int);
-  if (final_lds_bytes(max_budget, a.W) > (size_t)kLdsBytes || a.parts < 1) return hipErrorInvalidValue;
-  allow_lds(k_segfinal, lds);
-  hipLaunchKernelGGL(k_segfinal, dim3(a.parts, st.batch, a.Hkv), dim3(kSegThreads), lds, s, a, st);
+  if (j.fin) {
+    if (j.fin->parts < 1) return hipErrorInvalidValue;
+    nfinal = j.fin->parts * st.batch;
+    lds = std::max(lds, final_lds_bytes(j.fin_budget, j.fin->W));
+  }
+  if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
+  const int nscore = j.score ? st.total_segs : 0, ncal = j.cal ? st.total_segs : 0,
+            ncand = j.cand ? st.total_segs : 0;
+  if ((j.score != nullptr) + (j.fin != nullptr) + (j.cal != nullptr) + (j.cand != nullptr) == 1 && !j.merge) {
+    if (j.score) return launch_sel_one<JOB_SCORE>(*j.score, st, nscore, lds, s);
+    if (j.fin) return launch_sel_one<JOB_FINAL>(*j.fin, st, nfinal, lds, s);
+    if (j.cal) return launch_sel_one<JOB_CAL>(*j.cal, st, ncal, lds, s);
+    return launch_sel_one<JOB_CAND>(*j.cand, st, ncand, lds, s);
+  }
+  allow_lds<k_sel>(lds);
+  hipLaunchKernelGGL(k_sel, dim3(any->Hkv, nscore + nfinal + ncal + nmerge + ncand), dim3(kSegThreads), lds, s,
+                     j.score ? *j.score : *any, j.fin ? *j.fin : *any, j.cal ? *j.cal : *any,
+                     j.cand ? *j.cand : *any, j.merge ? *j.merge : PassArgs{}, st, nscore, nfinal, ncal,
+                     nmerge, ncand);
   return hipGetLastError();
 }
 
@@ -3856,7 +3879,7 @@ __global__ __launch_bounds__(kAllocThreads) void k_alloc(AllocArgs a, SeqTable s
 hipError_t launch_alloc(const AllocArgs &a, const SeqTable &st, hipStream_t s) {
   if (a.Hkv < 1 || a.Hkv > kMaxAllocHeads || !a.vec_B || !a.vec_A || !a.hb) return hipErrorInvalidValue;
   const size_t lds = alloc_lds_bytes(a.Hkv);
-  allow_lds(k_alloc, lds);
+  allow_lds<k_alloc>(lds);
   hipLaunchKernelGGL(k_alloc, dim3(st.batch), dim3(kAllocThreads), lds, s, a, st);
   return hipGetLastError();
 }
