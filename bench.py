@@ -60,11 +60,11 @@ def algorithmic_bytes(wl, persist_m=4):
 # Kernels (library timing names) by what they complete of a layer's pass.
 # K passes that finish a layer's window score: its K read once, Q_win, E out.
 SCORE_PASSES = ("window_score_calib_lse_kr", "window_score_calib_lse", "window_score_calib_kr",
-                "window_score_calib", "window_score_single")
+                "window_score_calib", "window_score_single", "window_score_calib_wide")
 # Kernels whose work is only an intermediate of this design (a second read of
 # K for the normalisers, the normaliser merge, pooled vectors, score keys and
 # candidate lists): no algorithmic bytes of their own.
-DESIGN_ONLY = ("window_lse_kr", "window_lse", "lse_merge", "segment_score", "segment_cand")
+DESIGN_ONLY = ("window_lse_kr", "window_lse", "window_lse_wide", "lse_merge", "segment_score", "segment_cand")
 
 
 def kernel_bytes(name, wl, persist_m=4):
@@ -93,6 +93,8 @@ def kernel_bytes(name, wl, persist_m=4):
     if name == "segment_select":                        # the four select jobs, one layer's worth of each
         return sum(kernel_bytes(k, wl, persist_m)
                    for k in ("segment_calib", "segment_score", "segment_cand", "final_topk"))
+    if name == "layer_stages":                          # every stage, one layer's worth of each
+        return sum(kernel_bytes(k, wl, persist_m) for k in ("window_score_calib_wide", "segment_select"))
     if name == "segment_calib_cand":                    # calibration, the previous layer's lists,
         return sum(kernel_bytes(k, wl, persist_m)      # the next layer's normaliser merge
                    for k in ("segment_calib", "segment_cand", "lse_merge"))

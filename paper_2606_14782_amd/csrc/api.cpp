@@ -40,22 +40,29 @@ struct Layout {
       list_sk, list_sp, cnt_b, cnt_s, rec_b, rec_s, partials, lse2, lambda, hb, sb, sync, total;
   size_t sync_bytes;
   // distances between the copies that layers in flight take in turn
-  size_t vec_stride, hist_b_stride, hist_s_stride, list_stride, cnt_stride, rec_stride, hb_stride, sb_stride;
+  size_t vec_stride, hist_b_stride, hist_s_stride, list_stride, cnt_stride, rec_stride, hb_stride, sb_stride,
+      part_stride, lse_stride;
   int rpad, slots;
   int64_t chunks_cap;
 };
 
-// Copies of the buffers that pass between the select jobs.  In a prompt call
-// one select launch holds the calibration of layer l, the scores of l - 1,
-// the candidate lists of l - 2 and the final job of l - 3, so a layer's
-// buffer is free again
-//  * two launches on, where only the next job reads it (B, V and their pooled
-//    forms, the lists, their counts and records): two copies;
-//  * after the candidate job, which clears the B histogram that the next
-//    layer of its copy counts into: three;
-//  * after the final job (the S keys and histogram, which its whole-sequence
-//    path reads, and the budget tables): four.
-constexpr int kCopies2 = 2, kCopies3 = 3, kCopies4 = 4;
+// Copies of the buffers that pass between the stages of a layer.  In a prompt
+// call one launch holds stages of up to seven layers (pass 1 of layer l, its
+// normaliser merge a launch later, then pass 2, calibration, scores, candidate
+// lists, final job), so a layer's buffer is free again
+//  * two launches after it was written where only the next stage reads it
+//    (partials, normalisers, V and the pooled vectors, the lists, their counts
+//    and records): two copies;
+//  * after the scores, two stages on (B): three;
+//  * after the candidate job, three stages on, which clears the B histogram
+//    for the layer that counts into its copy next: four;
+//  * after the final job (the S keys and histogram, cleared by the
+//    calibration, which its whole-sequence path reads): four;
+//  * the budget tables, written before the layer's first launch and read until
+//    its last: eight.
+// The E history has a slot more than the layers a persistence term reads and
+// the one in flight.
+constexpr int kCopies2 = 2, kCopiesB = 3, kCopiesHistB = 4, kCopiesS = 4, kCopiesTab = 8;
 
 bacon_status check_shape(const bacon_shape *s) {
   if (!s) return fail(BACON_ERR_INVALID, "shape is NULL");
@@ -108,25 +115,25 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   Layout L{};
   const int G = s->num_q_heads / s->num_kv_heads;
   L.rpad = ((G * s->window + 31) / 32) * 32;
-  // E history: m + 1 slot vectors, so the slot a layer writes is never one of
-  // the m its persistence term reads
-  L.slots = p->persist_m + 1;
+  // E history: m + 2 slot vectors, so the slots that a layer and the next one
+  // write are never one of the m its persistence term reads
+  L.slots = p->persist_m + 2;
   const int tk = 32 * std::min(L.rpad / 32, 4);
   L.chunks_cap = (s->max_total_tokens + tk - 1) / tk + s->max_batch;
   const size_t vec = (size_t)s->num_kv_heads * (size_t)s->max_total_tokens * sizeof(float);
   size_t off = 0;
   L.vec_stride = align256(vec);
   L.ring = off;     off += align256((size_t)L.slots * vec);
-  L.vec_b = off;    off += kCopies2 * L.vec_stride;
+  L.vec_b = off;    off += kCopiesB * L.vec_stride;
   L.vec_vp = off;   off += L.vec_stride;
   L.vec_v = off;    off += kCopies2 * L.vec_stride;
   L.vec_pb = off;   off += kCopies2 * L.vec_stride;
   L.vec_pv = off;   off += kCopies2 * L.vec_stride;
-  L.vec_s = off;    off += kCopies4 * L.vec_stride;
+  L.vec_s = off;    off += kCopiesS * L.vec_stride;
   const size_t hist = (size_t)s->max_batch * s->num_kv_heads * kHBins * sizeof(unsigned);
   L.hist_b_stride = align256(hist * kHCopies);
   L.hist_s_stride = align256(hist);
-  L.hist_b = off;   off += kCopies3 * L.hist_b_stride;
+  L.hist_b = off;   off += kCopiesHistB * L.hist_b_stride;
   // meeting words of the single-read pass (arrival and done counters per
   // (sequence, KV head) on lines of their own, the error word, the published
   // row normalisers), right after the B histograms so that one clearing
@@ -134,7 +141,7 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.sync_bytes = align256((size_t)(kSyncStride * s->max_batch * s->num_kv_heads + 1) * sizeof(unsigned)) +
                  align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(unsigned));
   L.sync = off;     off += L.sync_bytes;
-  L.hist_s = off;   off += kCopies4 * L.hist_s_stride;
+  L.hist_s = off;   off += kCopiesS * L.hist_s_stride;
   // the lists of one copy lie one after the other: keys, positions, V for B
   // (3 vectors) and keys, positions for S (2 vectors)
   L.list_bk = off;
@@ -151,13 +158,15 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.rec_stride = align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int4));
   L.rec_b = off;    off += kCopies2 * L.rec_stride;
   L.rec_s = off;    off += kCopies2 * L.rec_stride;
-  L.partials = off; off += align256((size_t)s->num_kv_heads * L.chunks_cap * L.rpad * sizeof(float2));
-  L.lse2 = off;     off += align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(float));
+  L.part_stride = align256((size_t)s->num_kv_heads * L.chunks_cap * L.rpad * sizeof(float2));
+  L.partials = off; off += kCopies2 * L.part_stride;
+  L.lse_stride = align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(float));
+  L.lse2 = off;     off += kCopies2 * L.lse_stride;
   L.lambda = off;   off += align256((size_t)s->max_batch * s->num_kv_heads * sizeof(float));
   L.hb_stride = align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int2));
-  L.hb = off;       off += kCopies4 * L.hb_stride;
+  L.hb = off;       off += kCopiesTab * L.hb_stride;
   L.sb_stride = align256((size_t)s->max_batch * sizeof(int4));
-  L.sb = off;       off += kCopies4 * L.sb_stride;
+  L.sb = off;       off += kCopiesTab * L.sb_stride;
   L.total = off;
   return L;
 }
@@ -167,11 +176,11 @@ const char *kKernelNames[] = {"window_lse",    "lse_merge",     "window_score", 
                               "final_topk",    "select_calib",  "select_topk",
                               "calib_elem",    "compact",       "window_lse_kr",
                               "window_score_calib_kr", "window_score_calib_lse_kr",
-                              "segment_select",
+                              "segment_select", "layer_stages", "window_lse_wide", "window_score_calib_wide",
                               "window_score_calib_lse", "window_score_single", "head_alloc"};
 enum KernelId { KI_LSE, KI_MERGE, KI_SCORE, KI_FUSED, KI_SEGCAL, KI_SEGSCORE, KI_SEGCAND, KI_FINAL,
                 KI_SEL_CALIB, KI_SEL_TOPK, KI_ELEM, KI_COMPACT, KI_LSE_KR, KI_FUSED_KR, KI_DUAL_KR,
-                KI_SEL, KI_DUAL, KI_SINGLE, KI_ALLOC, KI_COUNT };
+                KI_SEL, KI_MEGA, KI_LSE_WIDE, KI_FUSED_WIDE, KI_DUAL, KI_SINGLE, KI_ALLOC, KI_COUNT };
 
 }  // namespace
 
@@ -187,6 +196,10 @@ struct bacon_ctx {
   int chunk_stages_override = 0;
   bool kr_off = false;   // key-register passes switched off (streaming passes only)
   int single_mode = -1;      // single-read pass: -1 where it pays, 0 never, 1 wherever it can run
+  // largest grid of the wide passes, in 512-key workgroups: on 246 (224 rows, 14/2
+  // heads) they take 176 against 178 us a prompt of three layers, on 440 to 512
+  // the key-register and streaming passes are a third faster (ragged batch)
+  int wide_limit = 256;
   int single_cap = -1;       // single-read workgroups the device holds at once (-1: not yet asked)
   int cus = -1;              // compute units of the device (-1: not yet asked)
   // test instrumentation (bacon_debug_capture): per-layer copies of B, V, lambda
@@ -535,6 +548,7 @@ bacon_status bacon_init(bacon_ctx **ctx, const bacon_shape *shape, const bacon_p
   c->L = L;
   if (const char *e = std::getenv("BACON_CHUNK_STAGES")) c->chunk_stages_override = std::atoi(e);
   if (const char *e = std::getenv("BACON_KEY_REGISTERS")) c->kr_off = std::atoi(e) == 0;
+  if (const char *e = std::getenv("BACON_WIDE")) c->wide_limit = std::atoi(e);
   if (const char *e = std::getenv("BACON_SINGLE")) c->single_mode = std::atoi(e) == 0 ? 0 : 1;
   *ctx = c;
   return BACON_OK;
@@ -556,7 +570,7 @@ bacon_status bacon_begin_prompt(bacon_ctx *c, const bacon_batch *bt, void *strea
   // (each layer's candidate job clears its copy for the layer that takes it
   // next), and so do the meeting counters of the single-read pass
   const hipError_t e = launch_zero(reinterpret_cast<unsigned *>(c->ws + c->L.hist_b),
-                                   (int64_t)((kCopies3 * c->L.hist_b_stride + c->L.sync_bytes) / sizeof(unsigned)),
+                                   (int64_t)((kCopiesHistB * c->L.hist_b_stride + c->L.sync_bytes) / sizeof(unsigned)),
                                    static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "clear");
   c->prompt = true;
@@ -729,19 +743,63 @@ namespace {
 struct LayerRun {
   int layer = 0;
   bool bf16 = false, w32 = false, kr = false, single = false;
+  bool wide = false;       // wide passes (small grids)
   bool adaptive = false;   // head-wise budgets from the adaptive allocation
   int chunk = 0, kmax = 0;
   int parts_alone = 1;     // final workgroups per (sequence, KV head) in a launch of their own
+  int parts_mega = 1;      // and beside every other stage
   SeqTable st{};
   PassArgs a{};
   SegArgs g{};
   const float *lse = nullptr;   // caller normalisers (pass 1 skipped)
 };
 
+// Whether a batch takes the wide passes, with how many row groups per
+// workgroup and chunks per workgroup.  The estimate of a launch that holds
+// both passes and the select jobs (us, from traces of 16 to 512 workgroups):
+// a workgroup takes 6 us plus 2.2 per further chunk and, per row tile of four
+// waves on a SIMD, 0.9 (bf16) or what its fp32 matrix instructions take; a select workgroup 8;
+// beyond one round of the CUs a launch takes the sum over the CUs and half a
+// workgroup more.
+bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) {
+  const bool bf16 = c->shape.dtype == BACON_BF16;
+  const int nrt = c->L.rpad / 32, hkv = c->shape.num_kv_heads;
+  const double tile = bf16 ? 0.9 : 0.053 * c->shape.head_dim;
+  int64_t segs = 0;
+  for (int b = 0; b < bt->batch; ++b) segs += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + kSegLen - 1) / kSegLen;
+  const double sel = (double)(3 * segs + bt->batch) * hkv;
+  double best = 1e30;
+  for (int s = 1; s <= 4; s *= 2) {
+    if (!wide_supported(bf16, c->shape.head_dim, c->L.rpad, s)) continue;
+    int64_t blocks = 0;
+    int nch = 0;
+    for (int b = 0; b < bt->batch; ++b) {
+      const int k = (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s);
+      blocks += k;
+      nch = std::max(nch, k);
+    }
+    if (nch > wide_max_chunks(c->L.rpad) || blocks * hkv > (int64_t)c->wide_limit * s) continue;
+    for (int p = 1; p <= 2; ++p) {
+      int64_t jobs = 0;
+      for (int b = 0; b < bt->batch; ++b)
+        jobs += ((bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s) + p - 1) / p;
+      const double t = 6.0 + 2.2 * (p - 1) + p * tile * std::max((double)nrt / s, 0.25 * ((nrt + s - 1) / s));
+      const double n = 2.0 * jobs * hkv + sel, cus = c->cus > 0 ? c->cus : 256;
+      const double est = n <= cus ? std::max(t, 8.0) : (2.0 * jobs * hkv * t + sel * 8.0) / cus + 0.5 * t;
+      if (est < best) {
+        best = est;
+        *split = s;
+        *cpw = p;
+      }
+    }
+  }
+  return best < 1e30;
+}
+
 // Checks one layer's arguments and builds its launch arguments; enqueues
 // nothing.  The layer order is the caller's to check.  Buffers that later
 // layers may write while this layer's select is still in flight come in
-// copies that the layers take in turn (kCopies2, 3, 4).
+// copies that the layers take in turn.
 bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const void *d_q_win,
                         const void *d_k, const void *d_v, const float *d_lse, int32_t *d_idx,
                         void *d_k_out, void *d_v_out, LayerRun &r) {
@@ -784,6 +842,22 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
     r.single = (int64_t)nmax * hkv <= c->single_cap &&
                (c->single_mode == 1 || (grid <= c->single_cap && 2 * grid >= c->single_cap));
   }
+  if (c->cus < 0) {
+    int dev = 0;
+    c->cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess) {
+      int n = 0;
+      if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) c->cus = n;
+    }
+  }
+  // small grids take the wide passes
+  const bool kr_shape = kr_supported(r.bf16, c->shape.head_dim, c->L.rpad);
+  int split = 1, cpw = 1;
+  if (!c->kr_off && !r.single) r.wide = wide_plan(c, bt, &split, &cpw);
+  if (r.wide) {
+    r.kr = false;
+    r.st = make_table(c, bt, &r.chunk, false, wide_keys(split));
+  }
   r.kmax = 0;
   for (int b = 0; b < bt->batch; ++b) r.kmax = std::max(r.kmax, batch_seq_rows(bt, c->shape.num_kv_heads, b));
   r.adaptive = c->params.head_alloc == BACON_ALLOC_ADAPTIVE;
@@ -800,14 +874,22 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   }
   if (final_lds_bytes(r.kmax, c->shape.window) > (size_t)kLdsBytes)
     return fail(BACON_ERR_UNSUPPORTED, "budget %d needs more LDS than a CU has", r.kmax);
-  const size_t c2 = layer % kCopies2, c3 = layer % kCopies3, c4 = layer % kCopies4;
+  const size_t c2 = layer % kCopies2, cS = layer % kCopiesS;
   const int64_t T = bt->cu_seqlens[bt->batch];
   PassArgs &a = r.a;
   a = pass_args(c, r.st, r.chunk, d_q_win, d_k);
   a.T = T;
   a.lse_in = d_lse;
-  a.hist_B += c3 * c->L.hist_b_stride / sizeof(unsigned);
-  a.vec_B += c2 * c->L.vec_stride / sizeof(float);
+  a.hist_B += layer % kCopiesHistB * c->L.hist_b_stride / sizeof(unsigned);
+  a.vec_B += layer % kCopiesB * c->L.vec_stride / sizeof(float);
+  a.partials += c2 * c->L.part_stride / sizeof(float2);
+  a.lse2 += c2 * c->L.lse_stride / sizeof(float);
+  a.kr_sums = kr_shape;
+  a.wide_split_log = split >> 1;   // 1, 2, 4
+  a.wide_cpw_log = cpw >> 1;       // 1, 2
+  a.row_log = wide_row_log(c->L.rpad);
+  a.w_magic = 65536u / (unsigned)a.W + 1u;
+  for (int b = 0; b < bt->batch; ++b) a.wide_jobs += (r.st.chunk_base[b + 1] - r.st.chunk_base[b] + cpw - 1) / cpw;
   int ring_cnt = 0;
   ring_slots(c, layer, &a.ring_write, &ring_cnt);
   a.ring_stride = (int64_t)c->shape.num_kv_heads * T;
@@ -838,9 +920,9 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.vec_V = reinterpret_cast<float *>(c->ws + c->L.vec_v + c2 * c->L.vec_stride);
   g.vec_pB = reinterpret_cast<float *>(c->ws + c->L.vec_pb + c2 * c->L.vec_stride);
   g.vec_pV = reinterpret_cast<float *>(c->ws + c->L.vec_pv + c2 * c->L.vec_stride);
-  g.vec_S = reinterpret_cast<unsigned *>(c->ws + c->L.vec_s + c4 * c->L.vec_stride);
+  g.vec_S = reinterpret_cast<unsigned *>(c->ws + c->L.vec_s + cS * c->L.vec_stride);
   g.hist_B = a.hist_B;
-  g.hist_S = reinterpret_cast<unsigned *>(c->ws + c->L.hist_s + c4 * c->L.hist_s_stride);
+  g.hist_S = reinterpret_cast<unsigned *>(c->ws + c->L.hist_s + cS * c->L.hist_s_stride);
   char *lists = c->ws + c2 * c->L.list_stride;
   g.listB_key = reinterpret_cast<unsigned *>(lists + c->L.list_bk);
   g.listB_pos = reinterpret_cast<int *>(lists + c->L.list_bp);
@@ -864,20 +946,18 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   // the rounds over the GPU that one part per head needs (two 1024-thread
   // workgroups per CU): a batch whose other jobs fill it would take more
   // rounds with every part.
-  if (c->cus < 0) {
-    int dev = 0;
-    c->cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      int n = 0;
-      if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) c->cus = n;
-    }
-  }
   {
     const int hkv = c->shape.num_kv_heads, heads = std::max(1, bt->batch * hkv);
     const int others = 3 * r.st.total_segs * hkv;   // calibration, scores and candidate lists
     auto rounds = [&](int p) { return (others + p * heads + 2 * c->cus - 1) / (2 * c->cus); };
     int p = std::max(1, std::min(8, c->cus / heads));
     r.parts_alone = p;
+    auto rounds_mega = [&](int q) {
+      return (others + 2 * r.a.wide_jobs * hkv + q * heads + c->cus - 1) / c->cus;
+    };
+    int pm = p;
+    while (pm > 1 && rounds_mega(pm) > rounds_mega(1)) --pm;
+    r.parts_mega = pm;
     while (p > 1 && rounds(p) > rounds(1)) --p;
     g.parts = p;
   }
@@ -893,6 +973,14 @@ bacon_status stage_pass(bacon_ctx *c, const LayerRun &r, bool lse_merged, const 
   const int d = c->shape.head_dim;
   if (r.single)
     return timed(c, KI_SINGLE, s, [&] { return launch_single(d, r.w32, r.a, r.st, s); });
+  if (r.wide) {
+    // a chunk per workgroup: nothing else shares the launch
+    PassArgs a = r.a;
+    a.wide_cpw_log = 0;
+    a.wide_jobs = r.st.total_chunks;
+    if (!r.lse) TRY(timed(c, KI_LSE_WIDE, s, [&] { return launch_wide(PASS_LSE, r.bf16, d, a, r.st, s); }));
+    return timed(c, KI_FUSED_WIDE, s, [&] { return launch_wide(PASS_FUSED, r.bf16, d, a, r.st, s); });
+  }
   if (r.kr) {
     if (!r.lse && !lse_merged) {
       TRY(timed(c, KI_LSE_KR, s, [&] { return launch_krpass(PASS_LSE, r.bf16, d, false, r.a, r.st, s); }));
@@ -917,7 +1005,7 @@ bacon_status stage_pass(bacon_ctx *c, const LayerRun &r, bool lse_merged, const 
 // The adaptive allocation's budget table of a layer (where given head
 // budgets go otherwise).
 int2 *alloc_table(bacon_ctx *c, int layer) {
-  return reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)(layer % kCopies4) * c->L.hb_stride);
+  return reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)(layer % kCopiesTab) * c->L.hb_stride);
 }
 
 // Head-wise budgets of r's layer from its window score (adaptive allocation
@@ -966,6 +1054,29 @@ bacon_status stage_select(bacon_ctx *c, const LayerRun *cal, const LayerRun *sco
   return timed(c, kid, s, [&] { return launch_sel(j, any->st, s); });
 }
 
+// One launch with any of the stages, each of its own layer (NULL: none).
+bacon_status stage_mega(bacon_ctx *c, const LayerRun *p1, const LayerRun *p2, const LayerRun *cal,
+                        const LayerRun *score, const LayerRun *cand, const LayerRun *fin, hipStream_t s) {
+  const LayerRun *any = nullptr;
+  for (const LayerRun *r : {p1, p2, cal, score, cand, fin})
+    if (r) any = r;
+  if (!any) return BACON_OK;
+  SelJobs j;
+  SegArgs f;
+  j.cal = cal ? &cal->g : nullptr;
+  j.score = score ? &score->g : nullptr;
+  j.cand = cand ? &cand->g : nullptr;
+  if (fin) {
+    f = fin->g;
+    f.parts = fin->parts_mega;
+    j.fin = &f;
+    j.fin_budget = fin->kmax;
+  }
+  return timed(c, KI_MEGA, s, [&] {
+    return launch_mega(any->bf16, c->shape.head_dim, j, p2 ? &p2->a : nullptr, p1 ? &p1->a : nullptr, any->st, s);
+  });
+}
+
 // Test instrumentation: once r's layer has its lambda (after its score
 // stage), copies B, V and lambda into the capture buffers, before a later
 // launch overwrites them.
@@ -994,7 +1105,7 @@ bacon_status compress(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const 
   LayerRun r;
   TRY(plan_layer(c, layer, bt, d_q_win, d_k, d_v, d_lse, d_idx, d_k_out, d_v_out, r));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  TRY(head_table(c, bt, s, &r.g.hb, layer % kCopies4));
+  TRY(head_table(c, bt, s, &r.g.hb, layer % kCopiesTab));
   if (r.adaptive) r.g.hb = alloc_table(c, layer);
   TRY(stage_pass(c, r, false, nullptr, s));
   TRY(stage_alloc(c, r, s));
@@ -1068,14 +1179,36 @@ bacon_status bacon_compress_prompt(bacon_ctx *c, const bacon_batch *bt, int32_t 
   // in the launch of layer l's pass 2.  The last three select launches have
   // no K pass before them.
   auto at = [&](int i) -> const LayerRun * { return i >= 0 && i < num_layers ? &runs[i] : nullptr; };
+  auto tables = [&](int i) -> bacon_status {
+    LayerRun &r = runs[i];
+    TRY(head_table(c, lbt(i), s, &r.g.hb, r.layer % kCopiesTab));
+    if (r.adaptive) r.g.hb = alloc_table(c, r.layer);
+    if (layer_batch) TRY(seq_table(c, r.st, s, &r.g.sb, r.layer % kCopiesTab));
+    return BACON_OK;
+  };
+  if (runs[0].wide) {   // (the layers share the sequences, so all of them are)
+    // Small grids: one launch per layer holds pass 1 of layer i, pass 2 of
+    // layer i - 1 (which merges the normalisers), and the four select jobs,
+    // each of the layer before.
+    const int lag2 = runs[0].lse ? 0 : 1;
+    for (int i = 0; i < num_layers + lag2 + 4; ++i) {
+      if (i < num_layers) {
+        TRY(tables(i));
+        c->next_layer = runs[i].layer + 1;
+      }
+      const int l2 = i - lag2;
+      TRY(stage_mega(c, lag2 > 0 ? at(i) : nullptr, at(l2), at(l2 - 1), at(l2 - 2), at(l2 - 3), at(l2 - 4), s));
+      if (at(l2)) TRY(stage_alloc(c, runs[l2], s));
+      if (at(l2 - 2)) TRY(stage_capture(c, runs[l2 - 2], lbt(l2 - 2), s));
+    }
+    return BACON_OK;
+  }
   bool merged = false;
   for (int i = 0; i < num_layers + 3; ++i) {
     const PassArgs *next = nullptr;
     if (i < num_layers) {
       LayerRun &r = runs[i];
-      TRY(head_table(c, lbt(i), s, &r.g.hb, r.layer % kCopies4));
-      if (r.adaptive) r.g.hb = alloc_table(c, r.layer);
-      if (layer_batch) TRY(seq_table(c, r.st, s, &r.g.sb, r.layer % kCopies4));
+      TRY(tables(i));
       // the next layer's pass 1 rides in this layer's pass-2 launch, unless the
       // next layer reads K once (single-read pass) or has its normalisers given
       if (!r.lse && !r.single && i + 1 < num_layers && !runs[i + 1].single) next = &runs[i + 1].a;

@@ -73,6 +73,13 @@ struct PassArgs {
   unsigned *sync;
   unsigned *bcast;
   int sync_groups;
+  // wide pass
+  int kr_sums;            // row sums in the key-register pass's order (else the streaming pass's)
+  int wide_split_log;     // log2 of the row groups S of a workgroup: 512 / S keys per chunk
+  int wide_cpw_log;       // log2 of the chunks per workgroup
+  int wide_jobs;          // workgroups per KV head
+  int row_log;            // log2 of the power of two that holds Rpad
+  unsigned w_magic;       // 65536 / W + 1: r / W is (r * w_magic) >> 16 for r < 256, W <= 256
 };
 
 enum SelMode { SEL_CALIB = 1, SEL_TOPK = 2 };
@@ -262,6 +269,17 @@ struct SelJobs {
   int fin_budget = 0;                // largest budget of fin's layer
 };
 hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s);
+// Wide passes (grids that do not fill the GPU): keys per workgroup, whether a
+// shape is covered, pass 1 (PASS_LSE) or the fused pass 2 (PASS_FUSED) alone,
+// and a launch with any of the select jobs (no merge) beside pass 2 of one
+// layer and pass 1 of another (NULL: none).
+int wide_keys(int split);
+int wide_row_log(int rpad);
+int wide_max_chunks(int rpad);
+bool wide_supported(bool bf16, int head_dim, int rpad, int split);
+hipError_t launch_wide(int mode, bool bf16, int head_dim, const PassArgs &a, const SeqTable &st, hipStream_t s);
+hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs *p2, const PassArgs *p1,
+                       const SeqTable &st, hipStream_t s);
 // LDS of the final workgroup for budgets up to max_budget.
 size_t final_lds_bytes(int max_budget, int window);
 size_t alloc_lds_bytes(int hkv);

@@ -194,6 +194,18 @@ __device__ __forceinline__ int find_seq(const SeqTable &st, int chunk) {
   return b;
 }
 
+// Workgroup barrier for LDS traffic: waits for this wave's LDS operations
+// only.  The fence of __syncthreads also waits for every global load and
+// store the wave has in flight, which the wide passes and the select
+// kernels never need: none of them reads global memory another of its threads
+// wrote in the same launch; their threads exchange data through LDS only.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Dynamic LDS above 64 KiB has to be allowed per kernel before launch.
 template <auto Kern>
 static void allow_lds(size_t bytes) {
@@ -1112,6 +1124,431 @@ hipError_t launch_krpass(int mode, bool bf16, int head_dim, bool w32, const Pass
   return head_dim == 128 ? launch_kr_d<PASS_FUSED, 128>(w32, a, st, s) : launch_kr_d<PASS_FUSED, 64>(w32, a, st, s);
 }
 
+// ---------------------------------------------------------------- wide pass
+// The K passes of grids that do not fill the GPU (bf16 and fp32 keys, up to
+// 256 window rows): a workgroup of 16 waves takes 512 / S keys of one KV head, a
+// wave one 32-key tile and every S-th of the 32-row tiles (S = 1, 2 or 4; with
+// fewer row tiles than S the other waves only help with the loads), where the key-register passes give a wave four key tiles and all rows in turn.  On
+// such grids a launch takes as long as one of its workgroups.  The host picks S
+// and the chunks per workgroup (wide_plan): more row tiles, or fp32's slower
+// matrix instructions, are spread over more workgroups as long as the GPU has
+// CUs for them.  The workgroup's threads are those of the select jobs, so that
+// both kinds can share a launch (k_mega).
+//
+// The window queries sit in LDS, swizzled as in the key-register passes; a
+// wave's keys sit in registers in the MFMA operand layout; a further chunk's
+// keys are requested when the row tiles of the one before are done.
+//  * PASS_LSE: D = K Q^T (a lane per query row); each wave's (max, sum) per
+//    row, merged through LDS into the chunk's partial.
+//  * PASS_FUSED: the row normalisers merged from the chunks' partials, D = Q K^T
+//    (a lane per key); B and Q in-lane over the rows of a tile, the tiles' sums
+//    through LDS; E to the history, B out, and the B histogram in LDS, added to
+//    memory once per workgroup.
+// The sums follow the order of the pass that covers the shape on larger grids
+// (a.kr_sums: the key-register pass, else the streaming pass), so that B and Q
+// given the normalisers do not depend on the grid's size.
+constexpr int kWideWavesLog = 4, kWideWaves = 1 << kWideWavesLog;
+static_assert(64 * kWideWaves == kSegThreads, "one tile per wave");
+constexpr int kWideKeys = 32 * kWideWaves;
+constexpr int kWideParts = 16;        // partials a thread of pass 2 merges at most
+
+// LDS map (bytes):
+//   q     Rpad * ROWB               window queries
+//   rn    Rpad floats               row constants of pass 2: -lse / c2 (kr_sums), else -lse
+//   wrw   Rpad ints                 window index of each row (W for pad rows)
+//   lqw   Rpad floats               1 on last-query rows, else 0
+//   part  max(16 / S * Rpad, 1024)  the waves' row partials (pass 1), the merge of the
+//         float2                    normalisers (pass 2); then in pass 2
+//   red   2 * slots * keys floats   B and Q sums of each row tile (and half, in the
+//                                   key-register order)
+//   hist  kHBins / 2 words          the B histogram, two 16-bit counts a word (pass 2)
+static int wide_slots(int rpad, int split, bool kr_sums) {
+  return split == 1 ? 1 : (rpad / 32) * (kr_sums ? 2 : 1);
+}
+int wide_lds_bytes(bool bf16, int head_dim, int rpad, int split) {
+  const bool kr = kr_supported(bf16, head_dim, rpad);
+  const int part = 8 * std::max(kWideWaves / split * rpad, kSegThreads);
+  const int red = 8 * wide_slots(rpad, split, kr) * (kWideKeys / split);
+  return rpad * head_dim * (bf16 ? 2 : 4) + 12 * rpad + std::max(part, std::max(8 * kSegThreads, red) + 2 * kHBins);
+}
+bool wide_supported(bool bf16, int head_dim, int rpad, int split) {
+  return rpad <= kMaxRows && wide_lds_bytes(bf16, head_dim, rpad, split) <= kLdsBytes;
+}
+int wide_keys(int split) { return kWideKeys / split; }
+// log2 of the power of two that holds rpad rows.
+int wide_row_log(int rpad) {
+  int l = 5;
+  while ((1 << l) < rpad) ++l;
+  return l;
+}
+// Chunks per sequence whose partials pass 2 can merge.
+int wide_max_chunks(int rpad) { return kWideParts * (kSegThreads >> wide_row_log(rpad)); }
+
+extern __shared__ __align__(16) unsigned char wide_smem[];
+
+// Job x of a wide pass: the chunks [c, c + cnt) of sequence b.
+__device__ __forceinline__ void wide_job(const PassArgs &a, const SeqTable &st, int x, int &b, int &c, int &cnt) {
+  b = 0;
+  int j = x;
+  while (true) {
+    const int nch = st.chunk_base[b + 1] - st.chunk_base[b];
+    const int cpw = 1 << a.wide_cpw_log, jobs = (nch + cpw - 1) >> a.wide_cpw_log;
+    if (j < jobs || b + 1 >= st.batch) {
+      c = j << a.wide_cpw_log;
+      cnt = max(0, min(cpw, nch - c));
+      return;
+    }
+    j -= jobs;
+    ++b;
+  }
+}
+
+// (max, sum) of n of them, `stride` apart in LDS, in order; sixteen reads in
+// flight at a time.
+__device__ __forceinline__ void merge_lds(const float2 *p, int stride, int n, float &mx, float &sx) {
+  mx = -INFINITY;
+  sx = 0.f;
+  for (int q0 = 0; q0 < n; q0 += 16) {
+    float2 v[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) v[q] = p[min(q0 + q, n - 1) * stride];
+    float m = mx;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m = fmaxf(m, v[q].x);
+    if (m == -INFINITY) continue;
+    float l = mx == -INFINITY ? 0.f : sx * __builtin_amdgcn_exp2f(mx - m);
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      l += q0 + q < n && v[q].x != -INFINITY ? v[q].y * __builtin_amdgcn_exp2f(v[q].x - m) : 0.f;
+    mx = m;
+    sx = l;
+  }
+}
+
+template <int MODE, bool BF16, int D>
+__device__ __forceinline__ void wide_body(const PassArgs &a, const SeqTable &st, int x, int h) {
+  using C = PassCfg<BF16, D>;
+  constexpr int NU = C::NU, NT = kSegThreads;
+  constexpr bool FUSED = MODE == PASS_FUSED;
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, half = lane >> 5, l32 = lane & 31;
+  int b, c0, cnt;
+  wide_job(a, st, x, b, c0, cnt);
+  const int n = st.cu[b + 1] - st.cu[b];
+  // (every divisor here is a power of two or W: an integer division by a
+  // runtime value is a chain of some 40 instructions, and these sit ahead of
+  // the first loads)
+  const int S = 1 << a.wide_split_log, kt_log = kWideWavesLog - a.wide_split_log;
+  const int KT = 1 << kt_log, CK = 32 * KT;                          // key tiles and keys of a chunk
+  const int kt = wave & (KT - 1), rg = wave >> kt_log;               // the wave's key tile and row group
+  auto div_w = [&](int r) { return (int)(((unsigned)r * a.w_magic) >> 16); };   // r / W, r < 256
+  const int W = a.W, R = a.R, NR = a.Rpad, wfirst = n - W, nrt = NR / 32;
+  unsigned char *qbuf = wide_smem;
+  float *rn = reinterpret_cast<float *>(qbuf + NR * C::ROWB);
+  int *wrw = reinterpret_cast<int *>(rn + NR);
+  float *lqw = reinterpret_cast<float *>(wrw + NR);
+  float2 *part = reinterpret_cast<float2 *>(lqw + NR);
+  const int slots = S == 1 ? 1 : nrt * (a.kr_sums ? 2 : 1);
+  float *red = reinterpret_cast<float *>(part);                      // [B, Q][slots][CK]
+  unsigned *hist = reinterpret_cast<unsigned *>(red + max(2 * NT, 2 * slots * CK));
+
+  // ---- loads: queries (up to four pieces per thread at a time), then the
+  // wave's keys; keys past the chunk repeat its last one (masked below)
+  constexpr int QB = 4;
+  const int npc = NR * C::PIECES;
+  // (uniform bases and 32-bit offsets: a window's queries span W Hq rows, a
+  // chunk's keys 512 Hkv rows; rows past the last real one repeat it)
+  const unsigned char *qbase = static_cast<const unsigned char *>(a.q) +
+                               ((int64_t)b * W * a.Hq + (int64_t)h * a.G) * C::ROWB;
+  auto qaddr = [&](int i) {
+    const int row = i / C::PIECES, pc = i % C::PIECES;
+    const int rr = min(row, R - 1), g = div_w(rr), w = rr - g * W;
+    return qbase + (unsigned)((w * a.Hq + g) * C::ROWB + 16 * pc);
+  };
+  auto qslot = [&](int i) {
+    const int row = i / C::PIECES, pc = i % C::PIECES;
+    return qbuf + row * C::ROWB + 16 * (pc ^ (row & C::SWM));
+  };
+  u32x4 qv[QB];
+#pragma unroll
+  for (int j = 0; j < QB; ++j)
+    if (j * NT < npc) qv[j] = *reinterpret_cast<const u32x4 *>(qaddr(min(t + j * NT, npc - 1)));
+  float lsev = 0.f;
+  float2 pv[FUSED ? kWideParts : 1];
+  const int nch = st.chunk_base[b + 1] - st.chunk_base[b];
+  // (thread t takes row t mod the power of two that holds the rows)
+  const int parts = NT >> a.row_log, prow = t & ((1 << a.row_log) - 1), pp = t >> a.row_log;
+  if constexpr (FUSED) {
+    // the row normalisers: the caller's, or thread t's part of row t % NR of
+    // the chunks' partials
+    if (a.lse_in) {
+      const int r = min(t, R - 1), g = div_w(r), w = r - g * W;
+      lsev = a.lse_in[((int64_t)b * a.Hq + (int64_t)h * a.G + g) * W + w];
+    } else if (prow < NR) {
+      const float2 *src = a.partials + ((int64_t)h * st.total_chunks + st.chunk_base[b]) * NR + prow;
+#pragma unroll
+      for (int j = 0; j < kWideParts; ++j)
+        if (j * parts < nch) pv[j] = src[(int64_t)min(pp + j * parts, nch - 1) * NR];
+    }
+  }
+  const unsigned char *kb = static_cast<const unsigned char *>(a.k) + ((int64_t)st.cu[b] * a.Hkv + h) * C::ROWB;
+  u32x4 kr[NU];
+  auto load_keys = [&](int c) {
+    const int k0 = c * CK;
+    const unsigned char *kp = kb + (int64_t)k0 * a.Hkv * C::ROWB +
+        (unsigned)(min(kt * 32 + l32, min(n - k0, CK) - 1) * a.Hkv * C::ROWB + 16 * half);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) kr[u] = *reinterpret_cast<const u32x4 *>(kp + 32 * u);
+  };
+  // (512-byte rows: the keys' 64 registers do not fit beside the partials')
+  constexpr bool LATE = FUSED && C::ROWB == 512;
+  asm volatile("" ::: "memory");
+  if (!LATE && rg < nrt) load_keys(c0);
+  asm volatile("" ::: "memory");
+  if constexpr (FUSED)
+    for (int q = 4 * t; q < kHBins / 2; q += 4 * NT) *reinterpret_cast<uint4 *>(hist + q) = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+  for (int j = 0; j < QB; ++j)
+    if (j * NT < npc) pin(qv[j]);
+#pragma unroll
+  for (int j = 0; j < QB; ++j)
+    if (t + j * NT < npc) *reinterpret_cast<u32x4 *>(qslot(t + j * NT)) = qv[j];
+  for (int i0 = QB * NT; i0 < npc; i0 += QB * NT) {
+#pragma unroll
+    for (int j = 0; j < QB; ++j) qv[j] = *reinterpret_cast<const u32x4 *>(qaddr(min(i0 + t + j * NT, npc - 1)));
+#pragma unroll
+    for (int j = 0; j < QB; ++j)
+      if (i0 + t + j * NT < npc) *reinterpret_cast<u32x4 *>(qslot(i0 + t + j * NT)) = qv[j];
+  }
+  if (t < NR) {
+    const int w = t < R ? t - div_w(t) * W : W;
+    wrw[t] = w;
+    lqw[t] = w == W - 1 ? 1.f : 0.f;
+  }
+  if constexpr (FUSED) {
+    // pad rows: probability 0
+    auto set_row = [&](float l2) { rn[t] = t < R ? (a.kr_sums ? -l2 / a.c2 : -l2) : -INFINITY; };
+    if (a.lse_in) {
+      if (t < NR) set_row(lsev * kLog2e);
+    } else {
+      float mx = -INFINITY, sx = 0.f;
+      if (prow < NR && pp < nch) {
+#pragma unroll
+        for (int j = 0; j < kWideParts; ++j)
+          if (j * parts < nch && pp + j * parts < nch) mx = fmaxf(mx, pv[j].x);
+        if (mx != -INFINITY) {
+#pragma unroll
+          for (int j = 0; j < kWideParts; ++j)
+            if (j * parts < nch && pp + j * parts < nch && pv[j].x != -INFINITY) sx += pv[j].y * __builtin_amdgcn_exp2f(pv[j].x - mx);
+        }
+        part[t] = make_float2(mx, sx);               // [parts][1 << row_log]
+      }
+      lds_barrier();
+      if (t < NR) {
+        const int used = min(parts, nch);
+        merge_lds(part + t, 1 << a.row_log, used, mx, sx);
+        set_row(mx + log2f(sx));
+      }
+    }
+  }
+  if constexpr (LATE) {
+    asm volatile("" ::: "memory");
+    if (rg < nrt) load_keys(c0);
+  }
+  // (a bare barrier: the keys stay in flight)
+  lds_barrier();
+
+  // row tile j against the wave's keys; query fragments are read QA units
+  // ahead of their MFMA.  The lane's piece 2u + half of a row sits in slot
+  // (2u + half) ^ m, m the row's low bits: u's low three bits and m's upper
+  // ones are taken through an opaque copy, so that the eight addresses are
+  // formed again (one instruction each) rather than held across the tiles.
+  constexpr int QA = NU < 4 ? NU : (BF16 ? 4 : 2);
+  auto mma = [&](int j, f32x16 acc) {
+    const int m = l32 & C::SWM;
+    const unsigned char *qt = qbuf + j * 32 * C::ROWB + l32 * C::ROWB + 16 * (half ^ (m & 1));
+    const int mh = opaque(16 * (m & ~1));
+    auto frag = [&](int u) {
+      return *reinterpret_cast<const u32x4 *>(qt + ((32 * (u & 7)) ^ mh) + 256 * (u >> 3));
+    };
+    u32x4 qf[QA];
+#pragma unroll
+    for (int u = 0; u < QA; ++u) qf[u] = frag(u);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      acc = FUSED ? mfma_unit<BF16>(qf[u % QA], kr[u], acc) : mfma_unit<BF16>(kr[u], qf[u % QA], acc);
+      if (u + QA < NU) qf[u % QA] = frag(u + QA);
+    }
+    return acc;
+  };
+
+  for (int cc = 0; cc < cnt; ++cc) {
+    const int c = c0 + cc, gchunk = st.chunk_base[b] + c;
+    const int k0 = c * CK, k1 = min(n, k0 + CK);
+    const int kbase = k0 + kt * 32;
+    const bool edge = (kbase + 31 >= k1) || (kbase + 31 > wfirst);
+    if constexpr (!FUSED) {
+      for (int j = rg; j < nrt; j += S) {
+        const f32x16 acc = mma(j, f32x16{});
+        // acc[reg]: key kbase + acc_row(reg, half), row j*32 + l32
+        float av[16];
+#pragma unroll
+        for (int reg = 0; reg < 16; ++reg) av[reg] = acc[reg];
+        if (edge) {
+          const int tpos = wfirst + min(wrw[j * 32 + l32], W - 1);
+#pragma unroll
+          for (int reg = 0; reg < 16; ++reg) {
+            const int key = kbase + acc_row(reg, half);
+            if (!(key < k1 && key <= tpos)) av[reg] = -INFINITY;
+          }
+        }
+        float m = tree_max16(av);
+        m = fmaxf(m, xor32(m, half));
+        const float off = m == -INFINITY ? 0.f : -m * a.c2;
+        float ev[16];
+#pragma unroll
+        for (int reg = 0; reg < 16; ++reg) ev[reg] = __builtin_amdgcn_exp2f(fmaf(av[reg], a.c2, off));
+        float l = tree_sum16(ev);
+        l += xor32(l, half);
+        if (half == 0) part[kt * NR + j * 32 + l32] = make_float2(m == -INFINITY ? -INFINITY : m * a.c2, l);
+      }
+      if (cc + 1 < cnt && rg < nrt) load_keys(c + 1);
+      lds_barrier();
+      if (t < NR) {
+        float mx, sx;
+        merge_lds(part + t, NR, KT, mx, sx);
+        a.partials[((int64_t)h * st.total_chunks + gchunk) * NR + t] = make_float2(mx, sx);
+      }
+      if (cc + 1 < cnt) lds_barrier();                // the partials are read
+    } else {
+      const int key = kbase + l32;
+      float bsum = 0.f, qsum = 0.f;
+      for (int j = rg; j < nrt; j += S) {
+        const int row0 = j * 32 + 4 * half;          // the lane's rows: runs of four, 8 apart
+        f32x16 acc = {};
+        float p[16];
+        // the accumulators start at -lse / c2 of their rows (key-register
+        // order), or -lse is added before the exp (streaming order)
+        if (a.kr_sums) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 v = *reinterpret_cast<const float4 *>(rn + row0 + 8 * i);
+            acc[4 * i + 0] = v.x; acc[4 * i + 1] = v.y; acc[4 * i + 2] = v.z; acc[4 * i + 3] = v.w;
+          }
+          acc = mma(j, acc);
+#pragma unroll
+          for (int reg = 0; reg < 16; ++reg) p[reg] = __builtin_amdgcn_exp2f(acc[reg] * a.c2);
+        } else {
+          acc = mma(j, acc);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 o = *reinterpret_cast<const float4 *>(rn + row0 + 8 * i);
+            p[4 * i + 0] = __builtin_amdgcn_exp2f(fmaf(acc[4 * i + 0], a.c2, o.x));
+            p[4 * i + 1] = __builtin_amdgcn_exp2f(fmaf(acc[4 * i + 1], a.c2, o.y));
+            p[4 * i + 2] = __builtin_amdgcn_exp2f(fmaf(acc[4 * i + 2], a.c2, o.z));
+            p[4 * i + 3] = __builtin_amdgcn_exp2f(fmaf(acc[4 * i + 3], a.c2, o.w));
+          }
+        }
+        if (edge) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int4 wr = *reinterpret_cast<const int4 *>(wrw + row0 + 8 * i);
+            if (!(key < k1 && key - wfirst <= wr.x)) p[4 * i + 0] = 0.f;
+            if (!(key < k1 && key - wfirst <= wr.y)) p[4 * i + 1] = 0.f;
+            if (!(key < k1 && key - wfirst <= wr.z)) p[4 * i + 2] = 0.f;
+            if (!(key < k1 && key - wfirst <= wr.w)) p[4 * i + 3] = 0.f;
+          }
+        }
+        // with the rows split over waves each tile's sums start anew
+        const bool fresh = S > 1 || !a.kr_sums;
+        float bt = tree_sum16(p), qt = fresh ? 0.f : qsum;
+        if (W == 32) {
+          qt += half ? p[15] : 0.f;                  // row 31 of the tile
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 lw = *reinterpret_cast<const float4 *>(lqw + row0 + 8 * i);
+            qt = fmaf(p[4 * i + 0], lw.x, qt);
+            qt = fmaf(p[4 * i + 1], lw.y, qt);
+            qt = fmaf(p[4 * i + 2], lw.z, qt);
+            qt = fmaf(p[4 * i + 3], lw.w, qt);
+          }
+        }
+        if (!a.kr_sums) {
+          bt += xor32(bt, half);
+          qt += xor32(qt, half);
+        }
+        if (S == 1) {
+          bsum += bt;
+          qsum = a.kr_sums ? qt : qsum + qt;
+        } else if (a.kr_sums || half == 0) {
+          const int sl = a.kr_sums ? 2 * j + half : j;
+          red[sl * CK + kt * 32 + l32] = bt;
+          red[(slots + sl) * CK + kt * 32 + l32] = qt;
+        }
+      }
+      if (cc + 1 < cnt && rg < nrt) load_keys(c + 1);
+      if (S == 1) {
+        if (a.kr_sums) {
+          bsum += xor32(bsum, half);
+          qsum += xor32(qsum, half);
+        }
+        if (half == 0) {
+          red[kt * 32 + l32] = bsum;
+          red[CK + kt * 32 + l32] = qsum;
+        }
+      }
+      lds_barrier();
+      // a thread per key
+      const int ke = k0 + t;
+      const bool mine = t < CK && ke < k1, cand = mine && ke < wfirst;
+      if (mine) {
+        float sb = red[t], sq = red[slots * CK + t];
+        if (slots > 1) {
+          if (a.kr_sums) {
+            // each half over the tiles, then the two halves
+            float sb1 = red[CK + t], sq1 = red[(slots + 1) * CK + t];
+            for (int j = 2; j < slots; j += 2) {
+              sb += red[j * CK + t];
+              sb1 += red[(j + 1) * CK + t];
+              sq += red[(slots + j) * CK + t];
+              sq1 += red[(slots + j + 1) * CK + t];
+            }
+            sb += sb1;
+            sq += sq1;
+          } else {
+            for (int j = 1; j < slots; ++j) {
+              sb += red[j * CK + t];
+              sq += red[(slots + j) * CK + t];
+            }
+          }
+        }
+        const float gw = (float)(a.G * W), gf = (float)a.G;
+        const float Bv = a.kr_sums ? sb * (1.f / gw) : sb / gw, Qv = a.kr_sums ? sq * (1.f / gf) : sq / gf;
+        const int64_t pos = (int64_t)h * a.T + st.cu[b] + ke;
+        // E (Eq. boundary_residual) to this layer's history slot
+        a.ring[a.ring_write * a.ring_stride + pos] = (Qv > Bv) ? (Qv - Bv) : 0.f;
+        a.vec_B[pos] = Bv;
+        const int bin = hbin(float_key(Bv));
+        if (cand) atomicAdd(&hist[bin >> 1], (bin & 1) ? 0x10000u : 1u);
+      }
+      if (cc + 1 < cnt) lds_barrier();                // the sums are read
+    }
+  }
+  if constexpr (FUSED) {
+    // the chunks' histogram to memory; consecutive lanes take consecutive
+    // bins, so that a wave's additions fall on few lines
+    lds_barrier();
+    unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+    const unsigned short *h16 = reinterpret_cast<const unsigned short *>(hist);
+    unsigned num[kHBins / NT];
+#pragma unroll
+    for (int i = 0; i < kHBins / NT; ++i) num[i] = h16[t + i * NT];
+#pragma unroll
+    for (int i = 0; i < kHBins / NT; ++i)
+      if (num[i]) atomicAdd(&gh[t + i * NT], num[i]);
+  }
+}
+
 // ---------------------------------------------------------------- single-read pass
 // One read of K per layer (bf16 keys, up to 128 window rows).  A workgroup of
 // kKrWaves waves holds kr_keys() keys of one KV head, loaded straight into
@@ -1715,17 +2152,6 @@ int single_resident_blocks(int head_dim, int rpad) {
 }
 
 // ---------------------------------------------------------------- block helpers
-// Workgroup barrier for LDS traffic: waits for this wave's LDS operations
-// only.  The fence of __syncthreads also waits for every global load and
-// store the wave has in flight, which the select kernels never need: none
-// of them reads global memory another of its threads wrote in the same
-// launch; their threads exchange data through LDS only.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 // Shared scratch of the block-wide primitives for NT threads.
 template <int NT>
 struct SelSharedT {
@@ -3634,6 +4060,23 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
 // two workgroups per CU.  A launch of one job has a kernel of its own
 // (k_sel_one), without the register bound, which costs the scores and the
 // final job spills: 7.8 against 9.1 us (four short sequences, 14/2 heads).
+
+// Row normalisers by a select workgroup: each takes kSegThreads /
+// kMergeThreads row groups of a sequence.
+__device__ __forceinline__ void merge_job(const PassArgs &m, const SeqTable &st, int x, int h) {
+  constexpr int groups = kSegThreads / kMergeThreads;
+  MergeLds &lds = *reinterpret_cast<MergeLds *>(sel_smem);
+  const int per_seq = (m.Rpad / kMergeRows + groups - 1) / groups;
+  const int b = x / per_seq;
+  const int grp = threadIdx.x / kMergeThreads;
+  const int rg = (x - b * per_seq) * groups + grp;
+  merge_rows(m, st, rg, b, h, threadIdx.x % kMergeThreads, lds.mrg[grp], rg * kMergeRows < m.Rpad);
+}
+static int merge_jobs(const PassArgs *m, int batch) {
+  constexpr int groups = kSegThreads / kMergeThreads;
+  return m ? batch * ((m->Rpad / kMergeRows + groups - 1) / groups) : 0;
+}
+
 enum SelJob { JOB_SCORE, JOB_FINAL, JOB_CAL, JOB_CAND };
 template <int JOB>
 __global__ __launch_bounds__(kSegThreads) void k_sel_one(SegArgs a, SeqTable st) {
@@ -3665,13 +4108,7 @@ __global__ __launch_bounds__(kSegThreads, 2 * kSegThreads / 256) void k_sel(
   }
   x -= ncal;
   if (x < nmerge) {
-    constexpr int groups = kSegThreads / kMergeThreads;
-    MergeLds &lds = *reinterpret_cast<MergeLds *>(sel_smem);
-    const int per_seq = (m.Rpad / kMergeRows + groups - 1) / groups;
-    const int b = x / per_seq;
-    const int grp = threadIdx.x / kMergeThreads;
-    const int rg = (x - b * per_seq) * groups + grp;
-    merge_rows(m, st, rg, b, h, threadIdx.x % kMergeThreads, lds.mrg[grp], rg * kMergeRows < m.Rpad);
+    merge_job(m, st, x, h);
     return;
   }
   x -= nmerge;
@@ -3690,16 +4127,15 @@ static hipError_t launch_sel_one(const SegArgs &a, const SeqTable &st, int jobs,
 }
 
 hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s) {
-  constexpr int groups = kSegThreads / kMergeThreads;
   const SegArgs *any = j.score ? j.score : j.fin ? j.fin : j.cal ? j.cal : j.cand;
   if (!any) return hipErrorInvalidValue;
-  int nmerge = 0, nfinal = 0;
+  int nfinal = 0;
+  const int nmerge = merge_jobs(j.merge, st.batch);
   size_t lds = sizeof(CandLds);
   if (j.score) lds = std::max(lds, sizeof(ScoreLds));
   if (j.cal) lds = std::max(lds, sizeof(CalLds));
   if (j.merge) {
     if (j.merge->Rpad % kMergeRows || j.merge->Hkv != any->Hkv) return hipErrorInvalidValue;
-    nmerge = st.batch * ((j.merge->Rpad / kMergeRows + groups - 1) / groups);
     lds = std::max(lds, sizeof(MergeLds));
   }
   if (j.fin) {
@@ -3722,6 +4158,118 @@ hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s) {
                      j.cand ? *j.cand : *any, j.merge ? *j.merge : PassArgs{}, st, nscore, nfinal, ncal,
                      nmerge, ncand);
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- one launch per layer
+// The K passes of small grids alone (per-layer calls).
+template <int MODE, bool BF16, int D>
+__global__ __launch_bounds__(kSegThreads) void k_wide(PassArgs a, SeqTable st) {
+  wide_body<MODE, BF16, D>(a, st, blockIdx.y, blockIdx.x);
+}
+
+// Every stage of a prompt's layers in one launch, each of its own layer: pass 1
+// of layer l, pass 2 of l - 1, and the four select jobs of l - 2 to l - 5.
+// For grids whose workgroups all fit at once (one 1024-thread workgroup of up
+// to 128 registers per CU) a launch takes as long as its longest job, about 8
+// us, where the K passes and the select launch ran one after the other.
+template <bool BF16, int D>
+__global__ __launch_bounds__(kSegThreads) void k_mega(SegArgs score, SegArgs fin, SegArgs cal, SegArgs cand,
+                                                      PassArgs p2, PassArgs p1, SeqTable st, int npass2,
+                                                      int npass1, int nscore, int nfinal, int ncal, int ncand) {
+  const int h = blockIdx.x;
+  int x = blockIdx.y;
+  if (x < npass2) {
+    wide_body<PASS_FUSED, BF16, D>(p2, st, x, h);
+    return;
+  }
+  x -= npass2;
+  if (x < npass1) {
+    wide_body<PASS_LSE, BF16, D>(p1, st, x, h);
+    return;
+  }
+  x -= npass1;
+  if (x < nscore) {
+    segscore_body<true>(score, st, x, h, find_seg(st, x));
+    return;
+  }
+  x -= nscore;
+  if (x < nfinal) {
+    final_body<true>(fin, st, x % fin.parts, x / fin.parts, h);
+    return;
+  }
+  x -= nfinal;
+  if (x < ncal) {
+    segcal_body(cal, st, x, h, find_seg(st, x));
+    return;
+  }
+  x -= ncal;
+  if (x < ncand) segcand_body(cand, st, x, h, find_seg(st, x));
+}
+
+template <bool BF16, int D>
+static hipError_t launch_wide_t(int mode, const PassArgs &a, const SeqTable &st, hipStream_t s) {
+  const int lds = wide_lds_bytes(BF16, D, a.Rpad, 1 << a.wide_split_log);
+  const dim3 grid(a.Hkv, a.wide_jobs), block(kSegThreads);
+  if (mode == PASS_LSE) {
+    allow_lds<k_wide<PASS_LSE, BF16, D>>(lds);
+    hipLaunchKernelGGL((k_wide<PASS_LSE, BF16, D>), grid, block, lds, s, a, st);
+  } else {
+    allow_lds<k_wide<PASS_FUSED, BF16, D>>(lds);
+    hipLaunchKernelGGL((k_wide<PASS_FUSED, BF16, D>), grid, block, lds, s, a, st);
+  }
+  return hipGetLastError();
+}
+// What the kernels assume of the plan in the arguments.
+static bool wide_ok(bool bf16, int head_dim, const PassArgs &a) {
+  return a.wide_split_log >= 0 && a.wide_split_log <= 2 && a.wide_cpw_log >= 0 && a.wide_cpw_log < 8 &&
+         a.wide_jobs >= 1 && a.chunk == wide_keys(1 << a.wide_split_log) &&
+         wide_supported(bf16, head_dim, a.Rpad, 1 << a.wide_split_log) && a.row_log == wide_row_log(a.Rpad) &&
+         a.w_magic == 65536u / (unsigned)a.W + 1u && (a.kr_sums != 0) == kr_supported(bf16, head_dim, a.Rpad);
+}
+hipError_t launch_wide(int mode, bool bf16, int head_dim, const PassArgs &a, const SeqTable &st, hipStream_t s) {
+  if (!wide_ok(bf16, head_dim, a) || (mode != PASS_LSE && mode != PASS_FUSED)) return hipErrorInvalidValue;
+  if (bf16) return head_dim == 128 ? launch_wide_t<true, 128>(mode, a, st, s) : launch_wide_t<true, 64>(mode, a, st, s);
+  return head_dim == 128 ? launch_wide_t<false, 128>(mode, a, st, s) : launch_wide_t<false, 64>(mode, a, st, s);
+}
+
+template <bool BF16, int D>
+static hipError_t launch_mega_t(const SelJobs &j, const PassArgs *p2, const PassArgs *p1, const SeqTable &st,
+                                hipStream_t s) {
+  const SegArgs *any = j.score ? j.score : j.fin ? j.fin : j.cal ? j.cal : j.cand;
+  const SegArgs none{};
+  if (!any) any = &none;
+  size_t lds = sizeof(CandLds);
+  int hkv = any->Hkv;
+  for (const PassArgs *p : {p2, p1})
+    if (p) {
+      lds = std::max(lds, (size_t)wide_lds_bytes(BF16, D, p->Rpad, 1 << p->wide_split_log));
+      hkv = p->Hkv;
+    }
+  if (j.score) lds = std::max(lds, sizeof(ScoreLds));
+  if (j.cal) lds = std::max(lds, sizeof(CalLds));
+  int nfinal = 0;
+  if (j.fin) {
+    if (j.fin->parts < 1) return hipErrorInvalidValue;
+    nfinal = j.fin->parts * st.batch;
+    lds = std::max(lds, final_lds_bytes(j.fin_budget, j.fin->W));
+  }
+  if (lds > (size_t)kLdsBytes || hkv < 1) return hipErrorInvalidValue;
+  const int npass2 = p2 ? p2->wide_jobs : 0, npass1 = p1 ? p1->wide_jobs : 0;
+  const int nscore = j.score ? st.total_segs : 0, ncal = j.cal ? st.total_segs : 0,
+            ncand = j.cand ? st.total_segs : 0;
+  allow_lds<k_mega<BF16, D>>(lds);
+  hipLaunchKernelGGL((k_mega<BF16, D>), dim3(hkv, npass2 + npass1 + nscore + nfinal + ncal + ncand),
+                     dim3(kSegThreads), lds, s, j.score ? *j.score : *any, j.fin ? *j.fin : *any,
+                     j.cal ? *j.cal : *any, j.cand ? *j.cand : *any, p2 ? *p2 : PassArgs{},
+                     p1 ? *p1 : PassArgs{}, st, npass2, npass1, nscore, nfinal, ncal, ncand);
+  return hipGetLastError();
+}
+hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs *p2, const PassArgs *p1,
+                       const SeqTable &st, hipStream_t s) {
+  for (const PassArgs *p : {p2, p1})
+    if (p && !wide_ok(bf16, head_dim, *p)) return hipErrorInvalidValue;
+  if (bf16) return head_dim == 128 ? launch_mega_t<true, 128>(j, p2, p1, st, s) : launch_mega_t<true, 64>(j, p2, p1, st, s);
+  return head_dim == 128 ? launch_mega_t<false, 128>(j, p2, p1, st, s) : launch_mega_t<false, 64>(j, p2, p1, st, s);
 }
 
 // ---------------------------------------------------------------- head-wise allocation
