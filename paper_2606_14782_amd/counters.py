@@ -38,7 +38,7 @@ _NAMES = [
     (r"bacon::k_krdual<", "window_score_calib_lse_kr"),
     (r"bacon::k_pass_dual<", "window_score_calib_lse"),
     (r"bacon::k_single<", "window_score_single"),
-    (r"bacon::k_sel\b", "segment_select"),
+    (r"bacon::k_sel<", "segment_select"),
     (r"bacon::k_mega<", "layer_stages"),
     (r"bacon::k_wide<0,", "window_lse_wide"),
     (r"bacon::k_wide<2,", "window_score_calib_wide"),

@@ -41,7 +41,9 @@ struct Layout {
   size_t sync_bytes;
   // distances between the copies that layers in flight take in turn
   size_t vec_stride, hist_b_stride, hist_s_stride, list_stride, cnt_stride, rec_stride, hb_stride, sb_stride,
-      part_stride, lse_stride;
+      part_stride, lse_stride, hist_a_stride;
+  size_t vec_a, hist_a, list_a, cnt_a, rec_a;   // head-wise allocation
+  int copies_b, copies_hist_b;
   int rpad, slots;
   int64_t chunks_cap;
 };
@@ -61,8 +63,12 @@ struct Layout {
 //  * the budget tables, written before the layer's first launch and read until
 //    its last: eight.
 // The E history has a slot more than the layers a persistence term reads and
-// the one in flight.
+// the one in flight.  The head-wise allocation puts three stages between pass 2
+// and the calibration, and B, its histogram and the E history three more
+// copies; its own pooled scores are read two stages on (three copies), its
+// histogram cleared three on (four).
 constexpr int kCopies2 = 2, kCopiesB = 3, kCopiesHistB = 4, kCopiesS = 4, kCopiesTab = 8;
+constexpr int kAllocLag = 3, kCopiesA = 3, kCopiesHistA = 4;
 
 bacon_status check_shape(const bacon_shape *s) {
   if (!s) return fail(BACON_ERR_INVALID, "shape is NULL");
@@ -117,14 +123,18 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.rpad = ((G * s->window + 31) / 32) * 32;
   // E history: m + 2 slot vectors, so the slots that a layer and the next one
   // write are never one of the m its persistence term reads
-  L.slots = p->persist_m + 2;
+  const bool adaptive = p->head_alloc == BACON_ALLOC_ADAPTIVE;
+  const int lag = adaptive ? kAllocLag : 0;
+  L.copies_b = kCopiesB + lag;
+  L.copies_hist_b = kCopiesHistB + lag;
+  L.slots = p->persist_m + 2 + lag;
   const int tk = 32 * std::min(L.rpad / 32, 4);
   L.chunks_cap = (s->max_total_tokens + tk - 1) / tk + s->max_batch;
   const size_t vec = (size_t)s->num_kv_heads * (size_t)s->max_total_tokens * sizeof(float);
   size_t off = 0;
   L.vec_stride = align256(vec);
   L.ring = off;     off += align256((size_t)L.slots * vec);
-  L.vec_b = off;    off += kCopiesB * L.vec_stride;
+  L.vec_b = off;    off += L.copies_b * L.vec_stride;
   L.vec_vp = off;   off += L.vec_stride;
   L.vec_v = off;    off += kCopies2 * L.vec_stride;
   L.vec_pb = off;   off += kCopies2 * L.vec_stride;
@@ -133,7 +143,13 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   const size_t hist = (size_t)s->max_batch * s->num_kv_heads * kHBins * sizeof(unsigned);
   L.hist_b_stride = align256(hist * kHCopies);
   L.hist_s_stride = align256(hist);
-  L.hist_b = off;   off += kCopiesHistB * L.hist_b_stride;
+  L.hist_b = off;   off += L.copies_hist_b * L.hist_b_stride;
+  // the allocation's histograms: cleared with them where a prompt uses them
+  // (bacon_allocate_heads clears its own copy)
+  L.hist_a_stride = align256((size_t)s->max_batch * s->num_kv_heads * alloc_hist_words() * sizeof(unsigned));
+  if (adaptive) {
+    L.hist_a = off; off += kCopiesHistA * L.hist_a_stride;
+  }
   // meeting words of the single-read pass (arrival and done counters per
   // (sequence, KV head) on lines of their own, the error word, the published
   // row normalisers), right after the B histograms so that one clearing
@@ -141,6 +157,9 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.sync_bytes = align256((size_t)(kSyncStride * s->max_batch * s->num_kv_heads + 1) * sizeof(unsigned)) +
                  align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(unsigned));
   L.sync = off;     off += L.sync_bytes;
+  if (!adaptive) {
+    L.hist_a = off; off += L.hist_a_stride;
+  }
   L.hist_s = off;   off += kCopiesS * L.hist_s_stride;
   // the lists of one copy lie one after the other: keys, positions, V for B
   // (3 vectors) and keys, positions for S (2 vectors)
@@ -158,6 +177,10 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.rec_stride = align256((size_t)s->max_batch * s->num_kv_heads * sizeof(int4));
   L.rec_b = off;    off += kCopies2 * L.rec_stride;
   L.rec_s = off;    off += kCopies2 * L.rec_stride;
+  L.vec_a = off;    off += (adaptive ? kCopiesA : 1) * L.vec_stride;
+  L.list_a = off;   off += (adaptive ? kCopies2 : 1) * L.vec_stride;
+  L.cnt_a = off;    off += (adaptive ? kCopies2 : 1) * L.cnt_stride;
+  L.rec_a = off;    off += (adaptive ? kCopies2 : 1) * L.rec_stride;
   L.part_stride = align256((size_t)s->num_kv_heads * L.chunks_cap * L.rpad * sizeof(float2));
   L.partials = off; off += kCopies2 * L.part_stride;
   L.lse_stride = align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(float));
@@ -196,9 +219,10 @@ struct bacon_ctx {
   int chunk_stages_override = 0;
   bool kr_off = false;   // key-register passes switched off (streaming passes only)
   int single_mode = -1;      // single-read pass: -1 where it pays, 0 never, 1 wherever it can run
-  // largest grid of the wide passes, in 512-key workgroups: on 246 (224 rows, 14/2
-  // heads) they take 176 against 178 us a prompt of three layers, on 440 to 512
-  // the key-register and streaming passes are a third faster (ragged batch)
+  // largest grid of the wide passes, in 512-key workgroups: on 224 (32 heads of
+  // d 64, three sequences) a prompt of seven layers takes 195 us with them and
+  // 207 with the key-register passes, on 246 (224 rows, 14/2 heads) 180 either
+  // way; the ragged batch's 856 take 4139 with them and 2739 without
   int wide_limit = 256;
   int single_cap = -1;       // single-read workgroups the device holds at once (-1: not yet asked)
   int cus = -1;              // compute units of the device (-1: not yet asked)
@@ -472,6 +496,28 @@ SelArgs sel_args(const bacon_ctx *c) {
   return a;
 }
 
+// The head-wise allocation's arguments of a layer, but for B and the sequences'
+// budgets.
+AllocArgs alloc_args(const bacon_ctx *c, int64_t T, int layer) {
+  const Layout &L = c->L;
+  const bool ad = c->params.head_alloc == BACON_ALLOC_ADAPTIVE;
+  const size_t c2 = ad ? layer % kCopies2 : 0;
+  AllocArgs a{};
+  a.Hkv = c->shape.num_kv_heads;
+  a.W = c->shape.window;
+  a.pool_half = c->params.pool_kernel / 2;
+  a.T = T;
+  a.alpha = c->params.alloc_floor;
+  a.vec_A = reinterpret_cast<float *>(c->ws + L.vec_a + (ad ? layer % kCopiesA : 0) * L.vec_stride);
+  a.hist_A = reinterpret_cast<unsigned *>(c->ws + L.hist_a + (ad ? layer % kCopiesHistA : 0) * L.hist_a_stride);
+  a.list_A = reinterpret_cast<unsigned *>(c->ws + L.list_a + c2 * L.vec_stride);
+  a.cnt_A = reinterpret_cast<int *>(c->ws + L.cnt_a + c2 * L.cnt_stride);
+  a.rec_A = reinterpret_cast<uint2 *>(c->ws + L.rec_a + c2 * L.rec_stride);
+  a.hb = reinterpret_cast<int2 *>(c->ws + L.hb + (size_t)(layer % kCopiesTab) * L.hb_stride);
+  a.err = error_word(const_cast<bacon_ctx *>(c));
+  return a;
+}
+
 int max_len(const bacon_batch *bt);
 
 // Every workgroup of the pass must fit the LDS of one CU; checked before
@@ -570,7 +616,7 @@ bacon_status bacon_begin_prompt(bacon_ctx *c, const bacon_batch *bt, void *strea
   // (each layer's candidate job clears its copy for the layer that takes it
   // next), and so do the meeting counters of the single-read pass
   const hipError_t e = launch_zero(reinterpret_cast<unsigned *>(c->ws + c->L.hist_b),
-                                   (int64_t)((kCopiesHistB * c->L.hist_b_stride + c->L.sync_bytes) / sizeof(unsigned)),
+                                   (int64_t)((c->L.sync + c->L.sync_bytes - c->L.hist_b) / sizeof(unsigned)),
                                    static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "clear");
   c->prompt = true;
@@ -689,18 +735,19 @@ bacon_status bacon_allocate_heads(bacon_ctx *c, const bacon_batch *bt, const flo
   hipStream_t s = static_cast<hipStream_t>(stream);
   int chunk = 0;
   const SeqTable st = make_table(c, bt, &chunk);
-  AllocArgs a{};
-  a.Hkv = c->shape.num_kv_heads;
-  a.W = c->shape.window;
-  a.pool_half = c->params.pool_kernel / 2;
-  a.T = bt->cu_seqlens[bt->batch];
-  a.alpha = c->params.alloc_floor;
+  AllocArgs a = alloc_args(c, bt->cu_seqlens[bt->batch], 0);
   a.vec_B = d_B;
-  a.vec_A = reinterpret_cast<float *>(c->ws + c->L.vec_pb);
-  a.hb = reinterpret_cast<int2 *>(c->ws + c->L.hb);
   a.out = d_budgets;
-  a.err = error_word(c);
-  return timed(c, KI_ALLOC, s, [&] { return launch_alloc(a, st, s); });
+  // the histogram is zero before the pool job, here and for a prompt's layers
+  auto clear = [&] {
+    return launch_zero(a.hist_A, (int64_t)(c->L.hist_a_stride / sizeof(unsigned)), s);
+  };
+  hipError_t e = clear();
+  if (e != hipSuccess) return hip_fail(e, "clear");
+  for (int stage = 0; stage < 3; ++stage)
+    TRY(timed(c, KI_ALLOC, s, [&] { return launch_alloc(stage, a, st, s); }));
+  e = clear();
+  return e == hipSuccess ? BACON_OK : hip_fail(e, "clear");
 }
 
 bacon_status bacon_alloc_output(bacon_ctx *c, int32_t *d_budgets) {
@@ -751,6 +798,7 @@ struct LayerRun {
   SeqTable st{};
   PassArgs a{};
   SegArgs g{};
+  AllocArgs al{};
   const float *lse = nullptr;   // caller normalisers (pass 1 skipped)
 };
 
@@ -880,8 +928,8 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   a = pass_args(c, r.st, r.chunk, d_q_win, d_k);
   a.T = T;
   a.lse_in = d_lse;
-  a.hist_B += layer % kCopiesHistB * c->L.hist_b_stride / sizeof(unsigned);
-  a.vec_B += layer % kCopiesB * c->L.vec_stride / sizeof(float);
+  a.hist_B += layer % c->L.copies_hist_b * c->L.hist_b_stride / sizeof(unsigned);
+  a.vec_B += layer % c->L.copies_b * c->L.vec_stride / sizeof(float);
   a.partials += c2 * c->L.part_stride / sizeof(float2);
   a.lse2 += c2 * c->L.lse_stride / sizeof(float);
   a.kr_sums = kr_shape;
@@ -941,6 +989,13 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.v_out = d_v_out;
   g.row_bytes = c->shape.head_dim * (r.bf16 ? 2 : 4);
   g.flat_heads = r.adaptive;
+  if (r.adaptive) {
+    r.al = alloc_args(c, T, layer);
+    r.al.vec_B = a.vec_B;
+    r.al.out = c->alloc_out ? c->alloc_out + (size_t)layer * c->shape.max_batch * c->shape.num_kv_heads : nullptr;
+    g.hist_A = r.al.hist_A;
+    g.hb = r.al.hb;
+  }
   // final workgroups per (sequence, KV head): up to eight.  Beside the other
   // jobs of a prompt call's select launch, no more than keep the launch to
   // the rounds over the GPU that one part per head needs (two 1024-thread
@@ -948,7 +1003,8 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   // rounds with every part.
   {
     const int hkv = c->shape.num_kv_heads, heads = std::max(1, bt->batch * hkv);
-    const int others = 3 * r.st.total_segs * hkv;   // calibration, scores and candidate lists
+    // calibration, scores and candidate lists (and the allocation's jobs)
+    const int others = (r.adaptive ? 5 : 3) * r.st.total_segs * hkv;
     auto rounds = [&](int p) { return (others + p * heads + 2 * c->cus - 1) / (2 * c->cus); };
     int p = std::max(1, std::min(8, c->cus / heads));
     r.parts_alone = p;
@@ -1002,78 +1058,74 @@ bacon_status stage_pass(bacon_ctx *c, const LayerRun &r, bool lse_merged, const 
   return BACON_OK;
 }
 
-// The adaptive allocation's budget table of a layer (where given head
-// budgets go otherwise).
-int2 *alloc_table(bacon_ctx *c, int layer) {
-  return reinterpret_cast<int2 *>(c->ws + c->L.hb + (size_t)(layer % kCopiesTab) * c->L.hb_stride);
-}
-
 // Head-wise budgets of r's layer from its window score (adaptive allocation
 // only), before its calibration reads them.
 bacon_status stage_alloc(bacon_ctx *c, const LayerRun &r, hipStream_t s) {
   if (!r.adaptive) return BACON_OK;
-  AllocArgs a{};
-  a.Hkv = c->shape.num_kv_heads;
-  a.W = c->shape.window;
-  a.pool_half = c->params.pool_kernel / 2;
-  a.T = r.g.T;
-  a.alpha = c->params.alloc_floor;
-  a.vec_B = r.g.vec_B;
-  a.vec_A = r.g.vec_pB;   // free until this layer's calibration writes the pooled B there
-  a.hb = alloc_table(c, r.layer);
-  a.out = c->alloc_out ? c->alloc_out + (size_t)r.layer * c->shape.max_batch * c->shape.num_kv_heads
-                       : nullptr;
-  a.sb = r.g.sb;
-  a.err = error_word(c);
-  return timed(c, KI_ALLOC, s, [&] { return launch_alloc(a, r.st, s); });
+  for (int stage = 0; stage < 3; ++stage)
+    TRY(timed(c, KI_ALLOC, s, [&] { return launch_alloc(stage, r.al, r.st, s); }));
+  return BACON_OK;
 }
 
-// One select launch: the jobs of up to four layers (NULL: none) and the next
-// layer's row normalisers (the layers share the sequences, so any of their
-// tables serves; the budgets come with each layer's own arguments).
-bacon_status stage_select(bacon_ctx *c, const LayerRun *cal, const LayerRun *score, const LayerRun *cand,
-                          const LayerRun *fin, const PassArgs *merge, hipStream_t s) {
-  SelJobs j;
-  SegArgs f;
-  j.cal = cal ? &cal->g : nullptr;
-  j.score = score ? &score->g : nullptr;
-  j.cand = cand ? &cand->g : nullptr;
-  j.merge = merge;
-  const bool alone = fin && !cal && !score && !cand;
-  if (fin) {
-    f = fin->g;
-    if (alone) f.parts = fin->parts_alone;
-    j.fin = &f;
-    j.fin_budget = fin->kmax;
+// The layers of the stages that one launch holds (NULL: none): passes 1 and 2,
+// the allocation's three jobs, the four select jobs.
+struct Stages {
+  const LayerRun *p1 = nullptr, *p2 = nullptr, *pool = nullptr, *list = nullptr, *pick = nullptr,
+                 *cal = nullptr, *score = nullptr, *cand = nullptr, *fin = nullptr;
+  const PassArgs *merge = nullptr;    // the next layer's row normalisers
+  int count() const {
+    int n = merge != nullptr;
+    for (const LayerRun *r : {p1, p2, pool, list, pick, cal, score, cand, fin}) n += r != nullptr;
+    return n;
   }
-  const LayerRun *any = cal ? cal : score ? score : cand ? cand : fin;
+  const LayerRun *any() const {
+    for (const LayerRun *r : {p1, p2, pool, list, pick, cal, score, cand, fin})
+      if (r) return r;
+    return nullptr;
+  }
+  // f: storage for the final job's arguments with `parts` workgroups per head
+  SelJobs jobs(SegArgs &f, int parts) const {
+    SelJobs j;
+    j.cal = cal ? &cal->g : nullptr;
+    j.score = score ? &score->g : nullptr;
+    j.cand = cand ? &cand->g : nullptr;
+    j.merge = merge;
+    j.pool = pool ? &pool->al : nullptr;
+    j.list = list ? &list->al : nullptr;
+    j.pick = pick ? &pick->al : nullptr;
+    if (fin) {
+      f = fin->g;
+      f.parts = parts;
+      j.fin = &f;
+      j.fin_budget = fin->kmax;
+    }
+    return j;
+  }
+};
+
+// One select launch: the jobs of the given layers and the next layer's row
+// normalisers (the layers share the sequences, so any of their tables serves;
+// the budgets come with each layer's own arguments).
+bacon_status stage_select(bacon_ctx *c, const Stages &g, hipStream_t s) {
+  const int njobs = g.count();
+  const LayerRun *any = g.any();
   if (!any) return BACON_OK;
-  const int njobs = (cal != nullptr) + (score != nullptr) + (cand != nullptr) + (fin != nullptr) + (merge != nullptr);
-  // (the table of the launch is the one its jobs without a budget table read)
-  const int kid = njobs > 1 ? KI_SEL : cal ? KI_SEGCAL : score ? KI_SEGSCORE : cand ? KI_SEGCAND : KI_FINAL;
+  SegArgs f;
+  const SelJobs j = g.jobs(f, g.fin ? (njobs == 1 ? g.fin->parts_alone : g.fin->g.parts) : 0);
+  const int kid = njobs > 1 || !(g.cal || g.score || g.cand || g.fin) ? KI_SEL
+                  : g.cal ? KI_SEGCAL : g.score ? KI_SEGSCORE : g.cand ? KI_SEGCAND : KI_FINAL;
   return timed(c, kid, s, [&] { return launch_sel(j, any->st, s); });
 }
 
-// One launch with any of the stages, each of its own layer (NULL: none).
-bacon_status stage_mega(bacon_ctx *c, const LayerRun *p1, const LayerRun *p2, const LayerRun *cal,
-                        const LayerRun *score, const LayerRun *cand, const LayerRun *fin, hipStream_t s) {
-  const LayerRun *any = nullptr;
-  for (const LayerRun *r : {p1, p2, cal, score, cand, fin})
-    if (r) any = r;
+// One launch with any of the stages, each of its own layer.
+bacon_status stage_mega(bacon_ctx *c, const Stages &g, hipStream_t s) {
+  const LayerRun *any = g.any();
   if (!any) return BACON_OK;
-  SelJobs j;
   SegArgs f;
-  j.cal = cal ? &cal->g : nullptr;
-  j.score = score ? &score->g : nullptr;
-  j.cand = cand ? &cand->g : nullptr;
-  if (fin) {
-    f = fin->g;
-    f.parts = fin->parts_mega;
-    j.fin = &f;
-    j.fin_budget = fin->kmax;
-  }
+  const SelJobs j = g.jobs(f, g.fin ? g.fin->parts_mega : 0);
   return timed(c, KI_MEGA, s, [&] {
-    return launch_mega(any->bf16, c->shape.head_dim, j, p2 ? &p2->a : nullptr, p1 ? &p1->a : nullptr, any->st, s);
+    return launch_mega(any->bf16, c->shape.head_dim, j, g.p2 ? &g.p2->a : nullptr, g.p1 ? &g.p1->a : nullptr,
+                       any->st, s);
   });
 }
 
@@ -1105,15 +1157,16 @@ bacon_status compress(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const 
   LayerRun r;
   TRY(plan_layer(c, layer, bt, d_q_win, d_k, d_v, d_lse, d_idx, d_k_out, d_v_out, r));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  TRY(head_table(c, bt, s, &r.g.hb, layer % kCopiesTab));
-  if (r.adaptive) r.g.hb = alloc_table(c, layer);
+  if (!r.adaptive) TRY(head_table(c, bt, s, &r.g.hb, layer % kCopiesTab));
   TRY(stage_pass(c, r, false, nullptr, s));
   TRY(stage_alloc(c, r, s));
-  TRY(stage_select(c, &r, nullptr, nullptr, nullptr, nullptr, s));
-  TRY(stage_select(c, nullptr, &r, nullptr, nullptr, nullptr, s));
+  Stages cal, score, cand, fin;
+  cal.cal = score.score = cand.cand = fin.fin = &r;
+  TRY(stage_select(c, cal, s));
+  TRY(stage_select(c, score, s));
   TRY(stage_capture(c, r, bt, s));
-  TRY(stage_select(c, nullptr, nullptr, &r, nullptr, nullptr, s));
-  TRY(stage_select(c, nullptr, nullptr, nullptr, &r, nullptr, s));
+  TRY(stage_select(c, cand, s));
+  TRY(stage_select(c, fin, s));
   c->next_layer = layer + 1;
   return BACON_OK;
 }
@@ -1173,52 +1226,50 @@ bacon_status bacon_compress_prompt(bacon_ctx *c, const bacon_batch *bt, int32_t 
     TRY(plan_layer(c, first_layer + i, lbt(i), d_q_win[i], d_k[i], d_v[i],
                    d_lse ? d_lse[i] : nullptr, d_idx[i], d_k_out[i], d_v_out[i], runs[i]));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // Layers in flight at once: the select launch that follows layer l's K
-  // passes holds its calibration, the scores of layer l - 1, the candidate
-  // lists of l - 2 and the final job of l - 3, and layer l + 1's pass 1 runs
-  // in the launch of layer l's pass 2.  The last three select launches have
-  // no K pass before them.
+  // Layers in flight at once.  Small grids: one launch per layer holds pass 1
+  // of layer i, pass 2 of layer i - 1 (which merges the normalisers), and the
+  // stages that follow, each of the layer before.  Others: the select launch
+  // that follows layer i's K passes holds its calibration, the scores of layer
+  // i - 1, the candidate lists of i - 2 and the final job of i - 3, and layer
+  // i + 1's pass 1 runs in the launch of layer i's pass 2.  The adaptive
+  // allocation's three jobs come between pass 2 and the calibration.  The last
+  // launches have no K pass.
   auto at = [&](int i) -> const LayerRun * { return i >= 0 && i < num_layers ? &runs[i] : nullptr; };
-  auto tables = [&](int i) -> bacon_status {
-    LayerRun &r = runs[i];
-    TRY(head_table(c, lbt(i), s, &r.g.hb, r.layer % kCopiesTab));
-    if (r.adaptive) r.g.hb = alloc_table(c, r.layer);
-    if (layer_batch) TRY(seq_table(c, r.st, s, &r.g.sb, r.layer % kCopiesTab));
-    return BACON_OK;
-  };
-  if (runs[0].wide) {   // (the layers share the sequences, so all of them are)
-    // Small grids: one launch per layer holds pass 1 of layer i, pass 2 of
-    // layer i - 1 (which merges the normalisers), and the four select jobs,
-    // each of the layer before.
-    const int lag2 = runs[0].lse ? 0 : 1;
-    for (int i = 0; i < num_layers + lag2 + 4; ++i) {
-      if (i < num_layers) {
-        TRY(tables(i));
-        c->next_layer = runs[i].layer + 1;
-      }
-      const int l2 = i - lag2;
-      TRY(stage_mega(c, lag2 > 0 ? at(i) : nullptr, at(l2), at(l2 - 1), at(l2 - 2), at(l2 - 3), at(l2 - 4), s));
-      if (at(l2)) TRY(stage_alloc(c, runs[l2], s));
-      if (at(l2 - 2)) TRY(stage_capture(c, runs[l2 - 2], lbt(l2 - 2), s));
-    }
-    return BACON_OK;
-  }
+  const bool wide = runs[0].wide, adaptive = runs[0].adaptive;   // (the layers share the sequences)
+  const int lag2 = wide && !runs[0].lse ? 1 : 0;                 // pass 2
+  const int lagc = lag2 + (wide ? 1 : 0) + (adaptive ? kAllocLag : 0);   // calibration
   bool merged = false;
-  for (int i = 0; i < num_layers + 3; ++i) {
-    const PassArgs *next = nullptr;
+  for (int i = 0; i < num_layers + lagc + 3; ++i) {
+    Stages g;
     if (i < num_layers) {
       LayerRun &r = runs[i];
-      TRY(tables(i));
-      // the next layer's pass 1 rides in this layer's pass-2 launch, unless the
-      // next layer reads K once (single-read pass) or has its normalisers given
-      if (!r.lse && !r.single && i + 1 < num_layers && !runs[i + 1].single) next = &runs[i + 1].a;
-      TRY(stage_pass(c, r, merged, next, s));
-      TRY(stage_alloc(c, r, s));
-      merged = next != nullptr;
+      if (layer_batch) TRY(seq_table(c, r.st, s, &r.g.sb, r.layer % kCopiesTab));
+      if (adaptive) r.al.sb = r.g.sb;
+      else TRY(head_table(c, lbt(i), s, &r.g.hb, r.layer % kCopiesTab));
       c->next_layer = r.layer + 1;
+      if (!wide) {
+        // the next layer's pass 1 rides in this layer's pass-2 launch, unless the
+        // next layer reads K once (single-read pass) or has its normalisers given
+        if (!r.lse && !r.single && i + 1 < num_layers && !runs[i + 1].single) g.merge = &runs[i + 1].a;
+        TRY(stage_pass(c, r, merged, g.merge, s));
+        merged = g.merge != nullptr;
+      }
     }
-    TRY(stage_select(c, at(i), at(i - 1), at(i - 2), at(i - 3), next, s));
-    if (i >= 1 && i <= num_layers) TRY(stage_capture(c, runs[i - 1], lbt(i - 1), s));
+    if (wide) {
+      if (lag2) g.p1 = at(i);
+      g.p2 = at(i - lag2);
+    }
+    if (adaptive) {
+      g.pool = at(i - lagc + 3);
+      g.list = at(i - lagc + 2);
+      g.pick = at(i - lagc + 1);
+    }
+    g.cal = at(i - lagc);
+    g.score = at(i - lagc - 1);
+    g.cand = at(i - lagc - 2);
+    g.fin = at(i - lagc - 3);
+    TRY(wide ? stage_mega(c, g, s) : stage_select(c, g, s));
+    if (g.score) TRY(stage_capture(c, *g.score, lbt(i - lagc - 1), s));
   }
   return BACON_OK;
 }

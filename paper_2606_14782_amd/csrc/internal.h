@@ -128,6 +128,7 @@ struct SegArgs {
   float *vec_V;                  // [Hkv, T] V = E + L + T over I
   float *vec_pB, *vec_pV;        // [Hkv, T] pooled B and V over I
   unsigned *vec_S;               // [Hkv, T] keys of the pooled score over I
+  unsigned *hist_A;              // the allocation's histogram, cleared by the calibration (may be NULL)
   unsigned *hist_B, *hist_S;     // key histograms of B [B, Hkv, kHCopies, kHBins] (the bin count is
                                  // the sum of the copies) and of the pooled score [B, Hkv, kHBins];
                                  // the final kernel clears hist_B for the next layer, the
@@ -163,7 +164,11 @@ struct AllocArgs {
   int64_t T;
   double alpha;                  // floor fraction: every head keeps floor(alpha K) at least
   const float *vec_B;            // [Hkv, T]
-  float *vec_A;                  // [Hkv, T] scratch: the pooled B
+  float *vec_A;                  // [Hkv, T] the pooled B
+  unsigned *hist_A;              // [B, Hkv, alloc_hist_words()] histogram of its keys (zero before the pool job)
+  unsigned *list_A;              // [Hkv, T] keys of the boundary bin, segment s from slot s*kSegLen
+  int *cnt_A;                    // [Hkv, total_segs] their number
+  uint2 *rec_A;                  // [B, Hkv] boundary bin, the head's count above it
   int2 *hb;                      // out [B, Hkv] (K_{b,h}, idx offset in the sequence)
   int32_t *out;                  // optional out [B, Hkv] K_{b,h}
   const int4 *sb;                // optional per-layer sequence table (budget K_b in .x)
@@ -266,6 +271,7 @@ hipError_t launch_lse_merge(const PassArgs &a, const SeqTable &st, hipStream_t s
 struct SelJobs {
   const SegArgs *cal = nullptr, *score = nullptr, *cand = nullptr, *fin = nullptr;
   const PassArgs *merge = nullptr;   // row normalisers to merge
+  const AllocArgs *pool = nullptr, *list = nullptr, *pick = nullptr;   // head-wise allocation
   int fin_budget = 0;                // largest budget of fin's layer
 };
 hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s);
@@ -283,7 +289,9 @@ hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs
 // LDS of the final workgroup for budgets up to max_budget.
 size_t final_lds_bytes(int max_budget, int window);
 size_t alloc_lds_bytes(int hkv);
-hipError_t launch_alloc(const AllocArgs &a, const SeqTable &st, hipStream_t s);
+int alloc_hist_words();
+// One job of the allocation in a launch of its own: 0 pool, 1 list, 2 pick.
+hipError_t launch_alloc(int stage, const AllocArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_zero(unsigned *p, int64_t n, hipStream_t s);
 // Device address of the static scratch on the current device (looked up

@@ -3270,7 +3270,9 @@ struct ListView {
   bool fits;
 };
 
-// Calibration kernel (segment_calib).
+// Calibration kernel (segment_calib).  ADAPT: it may have an allocation's
+// histogram to clear.
+template <bool ADAPT>
 __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st, int gs, int h, int b) {
   constexpr int NT = kSegThreads, PER = kSegPer, NW = NT / 64;
   constexpr int TAPS = kSegTaps;
@@ -3311,6 +3313,14 @@ __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st
     unsigned *hs = a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins;
     for (int q = sg * sl + 4 * t; q < min(kHBins, (sg + 1) * sl); q += 4 * NT)
       *reinterpret_cast<u32x4 *>(hs + q) = u32x4{0u, 0u, 0u, 0u};
+    // ... and of the allocation's histogram, which this layer is done with
+    if (ADAPT && a.hist_A) {
+      constexpr int HA = kHBins + 64;
+      const int sa = 4 * ((HA / 4 + nseg - 1) / nseg);
+      unsigned *ha = a.hist_A + ((int64_t)b * a.Hkv + h) * HA;
+      for (int q = sg * sa + 4 * t; q < min(HA, (sg + 1) * sa); q += 4 * NT)
+        *reinterpret_cast<u32x4 *>(ha + q) = u32x4{0u, 0u, 0u, 0u};
+    }
   }
 
   // one round of loads: B and T (the earlier layers' E, oldest first) over
@@ -4042,6 +4052,383 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
   }
 }
 
+// ---------------------------------------------------------------- head-wise allocation
+// AdaKV's budget allocation of one (layer, sequence) (App. B: the backbone's
+// head-wise budgets, kept under BACON).  Every KV head keeps its top
+// f = floor(alpha K) positions by the backbone score A, the mean pool of B
+// over the candidates; the other H (K - f) slots go to the highest A over the
+// union of every head's remaining positions (ties: score desc, head asc,
+// position asc).  Counted without sorting: with g_h(x) the head's entries
+// at or above key x, the union's slots at or above x number
+// F(x) = sum_h max(0, g_h(x) - f), so the boundary key tau is the largest with
+// F(tau) >= H (K - f); the tie at tau goes to the lower heads, and K_h = f + the
+// head's share.
+//
+// Three jobs over segments, as the select's (one workgroup per sequence read
+// every position four times: 63 us at 8K tokens and four heads, 256 us at 19K
+// and eight; the three jobs take 3 to 6 us each and, in a prompt call, share
+// the launches of other layers' stages):
+//  * alloc_pool: A, each head's histogram of its keys (the bins of the select
+//    histograms) and its sums over 64 groups of 128 bins;
+//  * alloc_list: every workgroup finds the bin of tau from the heads'
+//    histograms (groups first, then the bins of one group) and lists its
+//    segment's keys in that bin;
+//  * alloc_pick (one workgroup per sequence): tau from the lists, nine key
+//    bits at a time, and the budgets.  Bin 0 also holds the keys of negative
+//    values (B of a caller's own): there it searches all 32 key bits over A.
+constexpr int kMaxAllocHeads = 32;
+constexpr int kAllocGroups = 64, kAllocGroupBins = kHBins / kAllocGroups;
+constexpr int kAllocRow = kHBins + kAllocGroups;        // words of a head's histogram
+constexpr int kAllocDigits = 512;                       // bins of a level of alloc_pick
+static_assert(kAllocGroupBins == 128 && kHPer == 8, "groups of 16 threads");
+int alloc_hist_words() { return kAllocRow; }
+
+struct AllocPoolLds {
+  unsigned hist[kHBins];
+  float tile[kSegWin];
+};
+struct AllocListLds {
+  SelSharedT<kSegThreads> ss;
+  unsigned coarse[kMaxAllocHeads][kAllocGroups];
+  unsigned fine[kMaxAllocHeads][kAllocGroupBins];
+  unsigned cnt;
+};
+struct AllocPickLds {
+  SelSharedT<kSegThreads> ss;
+  unsigned pre[kMaxAllocHeads * kMaxSegs];
+  unsigned above[kMaxAllocHeads], eq[kMaxAllocHeads];
+  int kh[kMaxAllocHeads];
+  // then the heads' digit histograms, [Hkv][kAllocDigits]
+};
+static size_t alloc_pick_lds(int hkv) { return sizeof(AllocPickLds) + (size_t)hkv * kAllocDigits * sizeof(unsigned); }
+
+// The floor f and the union's slots R of a sequence with budget K.
+__device__ __forceinline__ int alloc_floor(const AllocArgs &a, int K) {
+  return (int)min((double)K, floor(a.alpha * (double)K));
+}
+
+__device__ __forceinline__ void alloc_pool_body(const AllocArgs &a, const SeqTable &st, int gs, int h) {
+  constexpr int NT = kSegThreads;
+  AllocPoolLds &lds = *reinterpret_cast<AllocPoolLds *>(sel_smem);
+  const int t = threadIdx.x, lane = t & 63;
+  const int b = find_seg(st, gs), sg = gs - st.seg_base[b];
+  const int n = st.cu[b + 1] - st.cu[b], nc = n - a.W;
+  if (nc <= sel_seq_budget(st, a.sb, b)) return;        // every head keeps all its candidates
+  const int64_t base = (int64_t)h * a.T + st.cu[b];
+  const int i0 = sg * kSegLen, w0 = i0 - kPoolHalo, ph = a.pool_half;
+  float x[kSegWinJ];
+#pragma unroll
+  for (int j = 0; j < kSegWinJ; ++j) x[j] = a.vec_B[base + min(max(w0 + t + j * NT, 0), n - 1)];
+  for (int q = 4 * t; q < kHBins; q += 4 * NT) *reinterpret_cast<uint4 *>(lds.hist + q) = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+  for (int j = 0; j < kSegWinJ; ++j)
+    if (t + j * NT < kSegWin) lds.tile[t + j * NT] = x[j];
+  lds_barrier();
+#pragma unroll
+  for (int j = 0; j < kSegPer; ++j) {
+    const int i = i0 + t + j * NT;
+    if (i < min(nc, i0 + kSegLen)) {
+      const int lo = max(0, i - ph), hi = min(nc - 1, i + ph);
+      float acc = 0.f;
+      for (int u = lo; u <= hi; ++u) acc += lds.tile[u - w0];
+      const float v = acc / (float)(hi - lo + 1);
+      a.vec_A[base + i] = v;
+      atomicAdd(&lds.hist[hbin(float_key(v))], 1u);
+    }
+  }
+  lds_barrier();
+  unsigned *gh = a.hist_A + ((int64_t)b * a.Hkv + h) * kAllocRow;
+#pragma unroll
+  for (int q = 0; q < kHBins / NT; ++q) {
+    const unsigned c = lds.hist[t + q * NT];
+    if (c) atomicAdd(&gh[t + q * NT], c);
+  }
+  // the groups' sums: 16 threads of eight bins each
+  unsigned c = 0;
+#pragma unroll
+  for (int q = 0; q < kHPer; q += 4) {
+    const uint4 v = *reinterpret_cast<const uint4 *>(lds.hist + kHPer * t + q);
+    c += (v.x + v.y) + (v.z + v.w);
+  }
+  c += dpp_u<0x111, 0xf>(0u, c);                        // row_shr: lane 15 of a row ends with its sum
+  c += dpp_u<0x112, 0xf>(0u, c);
+  c += dpp_u<0x114, 0xf>(0u, c);
+  c += dpp_u<0x118, 0xf>(0u, c);
+  if ((lane & 15) == 15 && c) atomicAdd(&gh[kHBins + (t >> 4)], c);
+}
+
+// Suffix sums, in place, of the heads' rows of NB values a lane (the sum over
+// the values at or after each one, plus `above` of the head).  A wave takes
+// the heads congruent to it.
+template <int NB, typename AboveF>
+__device__ __forceinline__ void alloc_suffix(unsigned *rows, int H, AboveF above) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int h = wave; h < H; h += kSegThreads / 64) {
+    unsigned *r = rows + h * 64 * NB + NB * lane;
+    unsigned v[NB], s = 0;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      v[q] = r[q];
+      s += v[q];
+    }
+    const unsigned incl = wave_incl_sum_u(s);
+    unsigned acc = lane63_u(incl) - incl + above(h);    // after this lane's values
+#pragma unroll
+    for (int q = NB - 1; q >= 0; --q) {
+      acc += v[q];
+      r[q] = acc;
+    }
+  }
+}
+
+__device__ __forceinline__ void alloc_list_body(const AllocArgs &a, const SeqTable &st, int gs, int h) {
+  constexpr int NT = kSegThreads;
+  AllocListLds &lds = *reinterpret_cast<AllocListLds *>(sel_smem);
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63, H = a.Hkv;
+  const int b = find_seg(st, gs), sg = gs - st.seg_base[b];
+  const int n = st.cu[b + 1] - st.cu[b], nc = n - a.W;
+  const int K = sel_seq_budget(st, a.sb, b);
+  if (nc <= K) return;
+  const int f = alloc_floor(a, K);
+  const unsigned R = (unsigned)H * (unsigned)(K - f);
+  const int64_t base = (int64_t)h * a.T + st.cu[b];
+  const int i0 = sg * kSegLen, i1 = min(nc, i0 + kSegLen);
+  const unsigned *gh = a.hist_A + (int64_t)b * H * kAllocRow;
+  float x[kSegPer];
+#pragma unroll
+  for (int j = 0; j < kSegPer; ++j) x[j] = a.vec_A[base + min(i0 + t + j * NT, nc - 1)];
+  for (int e = t; e < H * kAllocGroups; e += NT)
+    (&lds.coarse[0][0])[e] = gh[(int64_t)(e >> 6) * kAllocRow + kHBins + (e & 63)];
+  if (t == 0) lds.cnt = 0u;
+  lds_barrier();
+  alloc_suffix<1>(&lds.coarse[0][0], H, [](int) { return 0u; });
+  lds_barrier();
+  // the largest group with F >= R at its lowest bin (F of group 0 counts
+  // every candidate, more than the slots)
+  if (wave == 0) {
+    unsigned F = 0;
+    for (int q = 0; q < H; ++q) F += max(lds.coarse[q][lane], (unsigned)f) - (unsigned)f;
+    const uint64_t m = __ballot(F >= R) | 1ull;
+    if (lane == 0) lds.ss.bc_i[0] = 63 - __clzll((long long)m);
+  }
+  lds_barrier();
+  const int g = lds.ss.bc_i[0];
+  for (int e = t; e < H * kAllocGroupBins; e += NT)
+    (&lds.fine[0][0])[e] = gh[(int64_t)(e >> 7) * kAllocRow + g * kAllocGroupBins + (e & 127)];
+  lds_barrier();
+  alloc_suffix<2>(&lds.fine[0][0], H,
+                  [&](int q) { return g + 1 < kAllocGroups ? lds.coarse[q][g + 1] : 0u; });
+  lds_barrier();
+  if (wave < 2) {
+    unsigned F = 0;
+    for (int q = 0; q < H; ++q) F += max(lds.fine[q][t], (unsigned)f) - (unsigned)f;
+    const uint64_t m = __ballot(F >= R);
+    if (lane == 0) lds.ss.bc_i[wave] = m ? 64 * wave + 63 - __clzll((long long)m) : -1;
+  }
+  lds_barrier();
+  const int fb = max(0, max(lds.ss.bc_i[0], lds.ss.bc_i[1]));
+  const int beta = g * kAllocGroupBins + fb;
+  // this segment's keys of the bin, in any order
+#pragma unroll
+  for (int j = 0; j < kSegPer; ++j) {
+    const unsigned key = float_key(x[j]);
+    const bool in = i0 + t + j * NT < i1 && beta > 0 && hbin(key) == beta;
+    const uint64_t m = __ballot(in);
+    if (m) {
+      unsigned o = 0;
+      if (lane == 0) o = atomicAdd(&lds.cnt, (unsigned)__popcll(m));
+      o = (unsigned)__builtin_amdgcn_readfirstlane((int)o);
+      if (in) a.list_A[base + i0 + o + lane_rank(m)] = key;
+    }
+  }
+  lds_barrier();
+  if (t == 0) {
+    a.cnt_A[(int64_t)h * st.total_segs + gs] = (int)lds.cnt;
+    if (sg == 0) {
+      const unsigned up = fb + 1 < kAllocGroupBins ? lds.fine[h][fb + 1]
+                          : (g + 1 < kAllocGroups ? lds.coarse[h][g + 1] : 0u);
+      a.rec_A[b * H + h] = make_uint2((unsigned)beta, up);
+    }
+  }
+}
+
+__device__ __forceinline__ void alloc_pick_body(const AllocArgs &a, const SeqTable &st, int b) {
+  constexpr int NT = kSegThreads;
+  AllocPickLds &lds = *reinterpret_cast<AllocPickLds *>(sel_smem);
+  unsigned *const hist = reinterpret_cast<unsigned *>(sel_smem + sizeof(AllocPickLds));
+  SelSharedT<NT> &ss = lds.ss;
+  const int t = threadIdx.x, H = a.Hkv;
+  const int n = st.cu[b + 1] - st.cu[b], nc = n - a.W;
+  const int K = sel_seq_budget(st, a.sb, b);
+  int2 *tab = a.hb + (int64_t)b * H;
+  if (nc <= K) {
+    // every head keeps all its candidates: the budgets stay uniform
+    for (int h = t; h < H; h += NT) {
+      tab[h] = make_int2(K, h * K);
+      if (a.out) a.out[(int64_t)b * H + h] = K;
+    }
+    return;
+  }
+  const int f = alloc_floor(a, K);
+  const unsigned R = (unsigned)H * (unsigned)(K - f);
+  const int nseg = st.seg_base[b + 1] - st.seg_base[b], np = H * nseg;
+  const int64_t s0 = st.cu[b];
+  const unsigned beta = a.rec_A[b * H].x;
+  const bool all = beta == 0u;                          // every key bit, over all of A
+  if (t < H) lds.above[t] = all ? 0u : a.rec_A[b * H + t].y;
+  // inclusive prefix of the lists' lengths, (head, segment) in order: two
+  // lists a thread
+  static_assert(kMaxAllocHeads * kMaxSegs <= 2 * kSegThreads, "two lists per thread");
+  unsigned c[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int p = min(2 * t + j, np - 1), h = p / nseg;
+    c[j] = 2 * t + j < np ? (unsigned)a.cnt_A[(int64_t)h * st.total_segs + st.seg_base[b] + (p - h * nseg)] : 0u;
+  }
+  const unsigned ex = block_excl_scan_u<NT>(c[0] + c[1], ss);
+  if (2 * t < np) lds.pre[2 * t] = ex + c[0];
+  if (2 * t + 1 < np) lds.pre[2 * t + 1] = ex + c[0] + c[1];
+  lds_barrier();
+  const int total = all ? 0 : (int)lds.pre[np - 1];
+
+  unsigned prefix = all ? 0u : ((1u << 13) | beta);     // known high bits of tau
+  const int levels = all ? 4 : 2;
+  for (int lev = 0; lev < levels; ++lev) {
+    // nine bits a level: key bits 17..9 and 8..0 inside the bin; over all bits
+    // 31..23, 22..14, 13..5 and 4..0
+    const int shift = all ? (lev == 3 ? 0 : 23 - 9 * lev) : 9 - 9 * lev;
+    const int width = all && lev == 3 ? 5 : 9;
+    const unsigned mask = (1u << width) - 1u;
+    for (int e = t; e < H * kAllocDigits; e += NT) hist[e] = 0u;
+    lds_barrier();
+    auto add = [&](int h, unsigned k) {
+      if ((uint64_t)k >> (shift + width) == prefix) atomicAdd(&hist[h * kAllocDigits + ((k >> shift) & mask)], 1u);
+    };
+    if (all) {
+      for (int h = 0; h < H; ++h)
+        for (int i = t; i < nc; i += NT) add(h, float_key(a.vec_A[(int64_t)h * a.T + s0 + i]));
+    } else {
+      for (int e = t; e < total; e += NT) {
+        int lo = 0, hi = np - 1;                        // the first list whose prefix exceeds e
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if ((int)lds.pre[mid] > e) hi = mid; else lo = mid + 1;
+        }
+        const int h = lo / nseg, sg = lo - h * nseg;
+        const int slot = e - (lo > 0 ? (int)lds.pre[lo - 1] : 0);
+        add(h, a.list_A[(int64_t)h * a.T + s0 + min(sg * kSegLen + slot, n - 1)]);
+      }
+    }
+    lds_barrier();
+    alloc_suffix<kAllocDigits / 64>(hist, H, [&](int h) { return lds.above[h]; });
+    lds_barrier();
+    // the largest digit with F >= R (some digit always qualifies: F at digit 0
+    // counts the union at or above the previous boundary)
+    unsigned F = 0u;
+    if (t < kAllocDigits)
+      for (int h = 0; h < H; ++h) F += max(hist[h * kAllocDigits + t], (unsigned)f) - (unsigned)f;
+    const unsigned xb = max(block_reduce_u<1, NT>(t < kAllocDigits && F >= R ? (unsigned)t + 1u : 0u, ss), 1u) - 1u;
+    if (t < H) {
+      const unsigned at = hist[t * kAllocDigits + xb];
+      const unsigned up = xb + 1 < (unsigned)kAllocDigits ? hist[t * kAllocDigits + xb + 1] : lds.above[t];
+      lds.eq[t] = at - up;
+      lds.above[t] = up;
+    }
+    prefix = (prefix << width) | xb;
+    lds_barrier();
+  }
+
+  // the tie at tau: each head's entries equal to tau beyond its floor, taken
+  // in head order until the union's slots are filled
+  if (t == 0) {
+    unsigned got = 0u;
+    for (int h = 0; h < H; ++h) got += lds.above[h] > (unsigned)f ? lds.above[h] - (unsigned)f : 0u;
+    unsigned need = got < R ? R - got : 0u;
+    int off = 0;
+    bool ok = true;
+    for (int h = 0; h < H; ++h) {
+      const unsigned g = lds.above[h], ge = g + lds.eq[h];
+      const unsigned hi2 = ge > (unsigned)f ? ge - (unsigned)f : 0u;
+      const unsigned lo2 = g > (unsigned)f ? g - (unsigned)f : 0u;
+      const unsigned take = min(hi2 - lo2, need);
+      need -= take;
+      lds.kh[h] = f + (int)(lo2 + take);
+      ok = ok && lds.kh[h] <= nc;
+      off += lds.kh[h];
+    }
+    // the budgets fill the sequence's H K slots exactly (its idx region and
+    // compacted rows); anything else would be a fault of the search above,
+    // reported on the error word with the budgets left uniform
+    if (!ok || off != H * K) {
+      for (int h = 0; h < H; ++h) lds.kh[h] = K;
+      if (a.err) __hip_atomic_store(a.err, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    off = 0;
+    for (int h = 0; h < H; ++h) {
+      tab[h] = make_int2(lds.kh[h], off);
+      off += lds.kh[h];
+    }
+  }
+  lds_barrier();
+  if (a.out)
+    for (int h = t; h < H; h += NT) a.out[(int64_t)b * H + h] = lds.kh[h];
+}
+
+// The allocation's jobs in a launch of other stages (ADAPT) or none.
+template <bool ADAPT>
+struct AllocSet {};
+template <>
+struct AllocSet<true> {
+  AllocArgs pool, list, pick;
+  int npool, nlist, npick;
+};
+// Runs job x if it is one of the allocation's, else takes their number off x.
+template <bool ADAPT>
+__device__ __forceinline__ bool alloc_job(const AllocSet<ADAPT> &j, const SeqTable &st, int &x, int h) {
+  if constexpr (ADAPT) {
+    if (x < j.npick) {
+      if (h == 0) alloc_pick_body(j.pick, st, x);
+      return true;
+    }
+    x -= j.npick;
+    if (x < j.nlist) {
+      alloc_list_body(j.list, st, x, h);
+      return true;
+    }
+    x -= j.nlist;
+    if (x < j.npool) {
+      alloc_pool_body(j.pool, st, x, h);
+      return true;
+    }
+    x -= j.npool;
+  }
+  return false;
+}
+static size_t alloc_lds(const AllocArgs *pool, const AllocArgs *list, const AllocArgs *pick) {
+  size_t lds = 0;
+  if (pool) lds = std::max(lds, sizeof(AllocPoolLds));
+  if (list) lds = std::max(lds, sizeof(AllocListLds));
+  if (pick) lds = std::max(lds, alloc_pick_lds(pick->Hkv));
+  return lds;
+}
+size_t alloc_lds_bytes(int hkv) {
+  return std::max(std::max(sizeof(AllocPoolLds), sizeof(AllocListLds)), alloc_pick_lds(hkv));
+}
+static AllocSet<true> alloc_set(const SelJobs &j, const SeqTable &st) {
+  AllocSet<true> r{};
+  if (j.pool) r.pool = *j.pool;
+  if (j.list) r.list = *j.list;
+  if (j.pick) r.pick = *j.pick;
+  r.npool = j.pool ? st.total_segs : 0;
+  r.nlist = j.list ? st.total_segs : 0;
+  r.npick = j.pick ? st.batch : 0;
+  return r;
+}
+static bool alloc_ok(const AllocArgs *a) {
+  return !a || (a->Hkv >= 1 && a->Hkv <= kMaxAllocHeads && a->vec_B && a->vec_A && a->hist_A && a->list_A &&
+                a->cnt_A && a->rec_A && a->hb);
+}
+
 // One select launch: any of the four jobs, each of a layer of its own, and the
 // next layer's row normalisers.  In a prompt call a launch holds the
 // calibration of layer l, the scores of layer l - 1, the candidate lists of
@@ -4078,20 +4465,29 @@ static int merge_jobs(const PassArgs *m, int batch) {
 }
 
 enum SelJob { JOB_SCORE, JOB_FINAL, JOB_CAL, JOB_CAND };
+enum AllocJob { JOB_POOL, JOB_LIST, JOB_PICK };
+template <int JOB>
+__global__ __launch_bounds__(kSegThreads) void k_alloc(AllocArgs a, SeqTable st) {
+  if constexpr (JOB == JOB_POOL) alloc_pool_body(a, st, blockIdx.y, blockIdx.x);
+  else if constexpr (JOB == JOB_LIST) alloc_list_body(a, st, blockIdx.y, blockIdx.x);
+  else alloc_pick_body(a, st, blockIdx.x);
+}
 template <int JOB>
 __global__ __launch_bounds__(kSegThreads) void k_sel_one(SegArgs a, SeqTable st) {
   const int h = blockIdx.x, x = blockIdx.y;
   if constexpr (JOB == JOB_SCORE) segscore_body<true>(a, st, x, h, find_seg(st, x));
   else if constexpr (JOB == JOB_FINAL) final_body<true>(a, st, x % a.parts, x / a.parts, h);
-  else if constexpr (JOB == JOB_CAL) segcal_body(a, st, x, h, find_seg(st, x));
+  else if constexpr (JOB == JOB_CAL) segcal_body<true>(a, st, x, h, find_seg(st, x));
   else segcand_body(a, st, x, h, find_seg(st, x));
 }
 
+template <bool ADAPT>
 __global__ __launch_bounds__(kSegThreads, 2 * kSegThreads / 256) void k_sel(
     SegArgs score, SegArgs fin, SegArgs cal, SegArgs cand, PassArgs m, SeqTable st, int nscore,
-    int nfinal, int ncal, int nmerge, int ncand) {
+    int nfinal, int ncal, int nmerge, int ncand, AllocSet<ADAPT> as) {
   const int h = blockIdx.x;
   int x = blockIdx.y;
+  if (alloc_job<ADAPT>(as, st, x, h)) return;
   if (x < nscore) {
     segscore_body<false>(score, st, x, h, find_seg(st, x));
     return;
@@ -4103,7 +4499,7 @@ __global__ __launch_bounds__(kSegThreads, 2 * kSegThreads / 256) void k_sel(
   }
   x -= nfinal;
   if (x < ncal) {
-    segcal_body(cal, st, x, h, find_seg(st, x));
+    segcal_body<ADAPT>(cal, st, x, h, find_seg(st, x));
     return;
   }
   x -= ncal;
@@ -4127,15 +4523,20 @@ static hipError_t launch_sel_one(const SegArgs &a, const SeqTable &st, int jobs,
 }
 
 hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s) {
+  const SegArgs none{};
   const SegArgs *any = j.score ? j.score : j.fin ? j.fin : j.cal ? j.cal : j.cand;
-  if (!any) return hipErrorInvalidValue;
+  if (!any) any = &none;
+  const bool adapt = j.pool || j.list || j.pick;
+  const AllocArgs *aany = j.pool ? j.pool : j.list ? j.list : j.pick;
+  const int hkv = adapt ? aany->Hkv : any->Hkv;
+  if (hkv < 1 || !alloc_ok(j.pool) || !alloc_ok(j.list) || !alloc_ok(j.pick)) return hipErrorInvalidValue;
   int nfinal = 0;
   const int nmerge = merge_jobs(j.merge, st.batch);
-  size_t lds = sizeof(CandLds);
+  size_t lds = std::max(sizeof(CandLds), alloc_lds(j.pool, j.list, j.pick));
   if (j.score) lds = std::max(lds, sizeof(ScoreLds));
   if (j.cal) lds = std::max(lds, sizeof(CalLds));
   if (j.merge) {
-    if (j.merge->Rpad % kMergeRows || j.merge->Hkv != any->Hkv) return hipErrorInvalidValue;
+    if (j.merge->Rpad % kMergeRows || j.merge->Hkv != hkv) return hipErrorInvalidValue;
     lds = std::max(lds, sizeof(MergeLds));
   }
   if (j.fin) {
@@ -4146,17 +4547,41 @@ hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s) {
   if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
   const int nscore = j.score ? st.total_segs : 0, ncal = j.cal ? st.total_segs : 0,
             ncand = j.cand ? st.total_segs : 0;
-  if ((j.score != nullptr) + (j.fin != nullptr) + (j.cal != nullptr) + (j.cand != nullptr) == 1 && !j.merge) {
+  if ((j.score != nullptr) + (j.fin != nullptr) + (j.cal != nullptr) + (j.cand != nullptr) == 1 && !j.merge && !adapt) {
     if (j.score) return launch_sel_one<JOB_SCORE>(*j.score, st, nscore, lds, s);
     if (j.fin) return launch_sel_one<JOB_FINAL>(*j.fin, st, nfinal, lds, s);
     if (j.cal) return launch_sel_one<JOB_CAL>(*j.cal, st, ncal, lds, s);
     return launch_sel_one<JOB_CAND>(*j.cand, st, ncand, lds, s);
   }
-  allow_lds<k_sel>(lds);
-  hipLaunchKernelGGL(k_sel, dim3(any->Hkv, nscore + nfinal + ncal + nmerge + ncand), dim3(kSegThreads), lds, s,
-                     j.score ? *j.score : *any, j.fin ? *j.fin : *any, j.cal ? *j.cal : *any,
-                     j.cand ? *j.cand : *any, j.merge ? *j.merge : PassArgs{}, st, nscore, nfinal, ncal,
-                     nmerge, ncand);
+  auto go = [&](auto kern, int extra, auto set) {
+    hipLaunchKernelGGL(kern, dim3(hkv, extra + nscore + nfinal + ncal + nmerge + ncand), dim3(kSegThreads), lds, s,
+                       j.score ? *j.score : *any, j.fin ? *j.fin : *any, j.cal ? *j.cal : *any,
+                       j.cand ? *j.cand : *any, j.merge ? *j.merge : PassArgs{}, st, nscore, nfinal, ncal,
+                       nmerge, ncand, set);
+    return hipGetLastError();
+  };
+  if (adapt) {
+    allow_lds<k_sel<true>>(lds);
+    const AllocSet<true> as = alloc_set(j, st);
+    return go(k_sel<true>, as.npool + as.nlist + as.npick, as);
+  }
+  allow_lds<k_sel<false>>(lds);
+  return go(k_sel<false>, 0, AllocSet<false>{});
+}
+
+hipError_t launch_alloc(int stage, const AllocArgs &a, const SeqTable &st, hipStream_t s) {
+  if (!alloc_ok(&a)) return hipErrorInvalidValue;
+  const size_t lds = stage == 0 ? sizeof(AllocPoolLds) : stage == 1 ? sizeof(AllocListLds) : alloc_pick_lds(a.Hkv);
+  if (stage == 0) {
+    allow_lds<k_alloc<JOB_POOL>>(lds);
+    hipLaunchKernelGGL(k_alloc<JOB_POOL>, dim3(a.Hkv, st.total_segs), dim3(kSegThreads), lds, s, a, st);
+  } else if (stage == 1) {
+    allow_lds<k_alloc<JOB_LIST>>(lds);
+    hipLaunchKernelGGL(k_alloc<JOB_LIST>, dim3(a.Hkv, st.total_segs), dim3(kSegThreads), lds, s, a, st);
+  } else {
+    allow_lds<k_alloc<JOB_PICK>>(lds);
+    hipLaunchKernelGGL(k_alloc<JOB_PICK>, dim3(st.batch), dim3(kSegThreads), lds, s, a, st);
+  }
   return hipGetLastError();
 }
 
@@ -4172,12 +4597,14 @@ __global__ __launch_bounds__(kSegThreads) void k_wide(PassArgs a, SeqTable st) {
 // For grids whose workgroups all fit at once (one 1024-thread workgroup of up
 // to 128 registers per CU) a launch takes as long as its longest job, about 8
 // us, where the K passes and the select launch ran one after the other.
-template <bool BF16, int D>
+template <bool BF16, int D, bool ADAPT>
 __global__ __launch_bounds__(kSegThreads) void k_mega(SegArgs score, SegArgs fin, SegArgs cal, SegArgs cand,
                                                       PassArgs p2, PassArgs p1, SeqTable st, int npass2,
-                                                      int npass1, int nscore, int nfinal, int ncal, int ncand) {
+                                                      int npass1, int nscore, int nfinal, int ncal, int ncand,
+                                                      AllocSet<ADAPT> as) {
   const int h = blockIdx.x;
   int x = blockIdx.y;
+  if (alloc_job<ADAPT>(as, st, x, h)) return;
   if (x < npass2) {
     wide_body<PASS_FUSED, BF16, D>(p2, st, x, h);
     return;
@@ -4199,7 +4626,7 @@ __global__ __launch_bounds__(kSegThreads) void k_mega(SegArgs score, SegArgs fin
   }
   x -= nfinal;
   if (x < ncal) {
-    segcal_body(cal, st, x, h, find_seg(st, x));
+    segcal_body<ADAPT>(cal, st, x, h, find_seg(st, x));
     return;
   }
   x -= ncal;
@@ -4238,8 +4665,14 @@ static hipError_t launch_mega_t(const SelJobs &j, const PassArgs *p2, const Pass
   const SegArgs *any = j.score ? j.score : j.fin ? j.fin : j.cal ? j.cal : j.cand;
   const SegArgs none{};
   if (!any) any = &none;
-  size_t lds = sizeof(CandLds);
+  size_t lds = std::max(sizeof(CandLds), alloc_lds(j.pool, j.list, j.pick));
   int hkv = any->Hkv;
+  const bool adapt = j.pool || j.list || j.pick;
+  for (const AllocArgs *p : {j.pool, j.list, j.pick})
+    if (p) {
+      if (!alloc_ok(p)) return hipErrorInvalidValue;
+      hkv = p->Hkv;
+    }
   for (const PassArgs *p : {p2, p1})
     if (p) {
       lds = std::max(lds, (size_t)wide_lds_bytes(BF16, D, p->Rpad, 1 << p->wide_split_log));
@@ -4257,12 +4690,20 @@ static hipError_t launch_mega_t(const SelJobs &j, const PassArgs *p2, const Pass
   const int npass2 = p2 ? p2->wide_jobs : 0, npass1 = p1 ? p1->wide_jobs : 0;
   const int nscore = j.score ? st.total_segs : 0, ncal = j.cal ? st.total_segs : 0,
             ncand = j.cand ? st.total_segs : 0;
-  allow_lds<k_mega<BF16, D>>(lds);
-  hipLaunchKernelGGL((k_mega<BF16, D>), dim3(hkv, npass2 + npass1 + nscore + nfinal + ncal + ncand),
-                     dim3(kSegThreads), lds, s, j.score ? *j.score : *any, j.fin ? *j.fin : *any,
-                     j.cal ? *j.cal : *any, j.cand ? *j.cand : *any, p2 ? *p2 : PassArgs{},
-                     p1 ? *p1 : PassArgs{}, st, npass2, npass1, nscore, nfinal, ncal, ncand);
-  return hipGetLastError();
+  auto go = [&](auto kern, int extra, auto set) {
+    hipLaunchKernelGGL(kern, dim3(hkv, extra + npass2 + npass1 + nscore + nfinal + ncal + ncand), dim3(kSegThreads),
+                       lds, s, j.score ? *j.score : *any, j.fin ? *j.fin : *any, j.cal ? *j.cal : *any,
+                       j.cand ? *j.cand : *any, p2 ? *p2 : PassArgs{}, p1 ? *p1 : PassArgs{}, st, npass2,
+                       npass1, nscore, nfinal, ncal, ncand, set);
+    return hipGetLastError();
+  };
+  if (adapt) {
+    allow_lds<k_mega<BF16, D, true>>(lds);
+    const AllocSet<true> as = alloc_set(j, st);
+    return go(k_mega<BF16, D, true>, as.npool + as.nlist + as.npick, as);
+  }
+  allow_lds<k_mega<BF16, D, false>>(lds);
+  return go(k_mega<BF16, D, false>, 0, AllocSet<false>{});
 }
 hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs *p2, const PassArgs *p1,
                        const SeqTable &st, hipStream_t s) {
@@ -4270,166 +4711,6 @@ hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs
     if (p && !wide_ok(bf16, head_dim, *p)) return hipErrorInvalidValue;
   if (bf16) return head_dim == 128 ? launch_mega_t<true, 128>(j, p2, p1, st, s) : launch_mega_t<true, 64>(j, p2, p1, st, s);
   return head_dim == 128 ? launch_mega_t<false, 128>(j, p2, p1, st, s) : launch_mega_t<false, 64>(j, p2, p1, st, s);
-}
-
-// ---------------------------------------------------------------- head-wise allocation
-// AdaKV's budget allocation of one (layer, sequence) (App. B: the backbone's
-// head-wise budgets, kept under BACON).  Every KV head keeps its top
-// f = floor(alpha K) positions by the backbone score A, the mean pool of B
-// over the candidates; the other H (K - f) slots go to the highest A over the
-// union of every head's remaining positions (ties: score desc, head asc,
-// position asc).  Counted without sorting: with g_h(x) the head's entries
-// above key x, the union's slots above x number F(x) = sum_h max(0, g_h(x) - f),
-// so a radix search over the key digits (per-head histograms in LDS) finds
-// the boundary key tau with F(above tau) < H (K - f) <= F(tau); the tie at tau
-// goes to the lower heads, and K_h = f + the head's share.  One workgroup per
-// sequence; A is written to a [Hkv, T] buffer between the passes.
-constexpr int kAllocThreads = 1024;
-constexpr int kAllocDigits = 1024;       // bins of a radix level (10 bits)
-constexpr int kAllocTile = 4096;         // positions of B staged per round of the pool
-constexpr int kMaxAllocHeads = 32;
-
-size_t alloc_lds_bytes(int hkv) { return (size_t)hkv * kAllocDigits * sizeof(unsigned); }
-
-__global__ __launch_bounds__(kAllocThreads) void k_alloc(AllocArgs a, SeqTable st) {
-  constexpr int NT = kAllocThreads;
-  extern __shared__ __align__(16) unsigned hist[];      // [Hkv][kAllocDigits]
-  __shared__ float tile[kAllocTile + 2 * kPoolHalo];
-  __shared__ SelSharedT<NT> ss;
-  __shared__ unsigned above[kMaxAllocHeads], eq[kMaxAllocHeads];
-  __shared__ int kh_s[kMaxAllocHeads];
-  const int t = threadIdx.x, b = blockIdx.x, H = a.Hkv;
-  const int n = st.cu[b + 1] - st.cu[b];
-  const int nc = n - a.W;
-  const int K = seq_budget(st, a.sb, b);
-  int2 *tab = a.hb + (int64_t)b * H;
-  if (nc <= K) {
-    // every head keeps all its candidates: the budgets stay uniform
-    for (int h = t; h < H; h += NT) {
-      tab[h] = make_int2(K, h * K);
-      if (a.out) a.out[(int64_t)b * H + h] = K;
-    }
-    return;
-  }
-  const int f = (int)min((double)K, floor(a.alpha * (double)K));
-  const unsigned R = (unsigned)H * (unsigned)(K - f);
-  const int ph = a.pool_half;
-  const int64_t T = a.T, s0 = st.cu[b];
-
-  // pass 0: A = the mean pool of B over the candidates (truncated at the
-  // ends), written out, and the histograms of its top key digit
-  for (int e = t; e < H * kAllocDigits; e += NT) hist[e] = 0u;
-  for (int h = 0; h < H; ++h) {
-    const float *B = a.vec_B + (int64_t)h * T + s0;
-    float *A = a.vec_A + (int64_t)h * T + s0;
-    for (int i0 = 0; i0 < nc; i0 += kAllocTile) {
-      __syncthreads();
-      const int lo = max(0, i0 - ph), hi = min(nc, i0 + kAllocTile + ph);
-      for (int j = lo + t; j < hi; j += NT) tile[j - lo] = B[j];
-      __syncthreads();
-      for (int i = i0 + t; i < min(nc, i0 + kAllocTile); i += NT) {
-        const int w0 = max(0, i - ph), w1 = min(nc - 1, i + ph);
-        float acc = 0.f;
-        for (int j = w0; j <= w1; ++j) acc += tile[j - lo];
-        const float v = acc / (float)(w1 - w0 + 1);
-        A[i] = v;
-        atomicAdd(&hist[h * kAllocDigits + (float_key(v) >> 22)], 1u);
-      }
-    }
-  }
-  for (int h = t; h < H; h += NT) above[h] = 0u;
-  __syncthreads();
-
-  // radix levels over key bits 31..22, 21..12, 11..2, 1..0
-  unsigned prefix = 0u;
-  for (int lev = 0; lev < 4; ++lev) {
-    const int shift = lev == 3 ? 0 : 22 - 10 * lev;
-    const int width = lev == 3 ? 2 : 10;
-    if (lev > 0) {
-      for (int e = t; e < H * kAllocDigits; e += NT) hist[e] = 0u;
-      __syncthreads();
-      const int pshift = shift + width;
-      for (int h = 0; h < H; ++h) {
-        const float *A = a.vec_A + (int64_t)h * T + s0;
-        for (int i = t; i < nc; i += NT) {
-          const unsigned k = float_key(A[i]);
-          if ((k >> pshift) == prefix)
-            atomicAdd(&hist[h * kAllocDigits + ((k >> shift) & ((1u << width) - 1u))], 1u);
-        }
-      }
-      __syncthreads();
-    }
-    // suffix sums per head in place: hist[h][x] = entries of head h with
-    // this level's digit >= x (under the prefix)
-    for (int h = 0; h < H; ++h) {
-      const unsigned v = hist[h * kAllocDigits + (kAllocDigits - 1 - t)];
-      const unsigned inc = block_excl_scan_u<NT>(v, ss) + v;
-      hist[h * kAllocDigits + (kAllocDigits - 1 - t)] = inc;
-      __syncthreads();
-    }
-    // F(x) at this thread's digit; the boundary is the largest x with F >= R
-    unsigned F = 0u;
-    for (int h = 0; h < H; ++h) {
-      const unsigned g = above[h] + hist[h * kAllocDigits + t];
-      F += g > (unsigned)f ? g - (unsigned)f : 0u;
-    }
-    // (some digit always qualifies: F at digit 0 counts the union at or
-    // below the previous boundary; the clamp only keeps indexes in range)
-    const unsigned xb = max(block_reduce_u<1, NT>(F >= R ? (unsigned)t + 1u : 0u, ss), 1u) - 1u;
-    // the entries above the boundary digit join `above`; the boundary digit's
-    // own count is kept for the last level
-    if (t < H) {
-      const unsigned at = hist[t * kAllocDigits + xb];
-      const unsigned up = xb + 1 < (unsigned)kAllocDigits ? hist[t * kAllocDigits + xb + 1] : 0u;
-      eq[t] = at - up;
-      above[t] += up;
-    }
-    prefix = (prefix << width) | xb;
-    __syncthreads();
-  }
-
-  // the tie at tau: each head's entries equal to tau beyond its floor, taken
-  // in head order until the union's slots are filled
-  if (t == 0) {
-    unsigned got = 0u;
-    for (int h = 0; h < H; ++h) got += above[h] > (unsigned)f ? above[h] - (unsigned)f : 0u;
-    unsigned need = got < R ? R - got : 0u;
-    int off = 0;
-    bool ok = true;
-    for (int h = 0; h < H; ++h) {
-      const unsigned g = above[h], ge = g + eq[h];
-      const unsigned hi2 = ge > (unsigned)f ? ge - (unsigned)f : 0u;
-      const unsigned lo2 = g > (unsigned)f ? g - (unsigned)f : 0u;
-      const unsigned take = min(hi2 - lo2, need);
-      need -= take;
-      kh_s[h] = f + (int)(lo2 + take);
-      ok = ok && kh_s[h] <= nc;
-      off += kh_s[h];
-    }
-    // the budgets fill the sequence's H K slots exactly (its idx region and
-    // compacted rows); anything else would be a fault of the search above,
-    // reported on the error word with the budgets left uniform
-    if (!ok || off != H * K) {
-      for (int h = 0; h < H; ++h) kh_s[h] = K;
-      if (a.err) __hip_atomic_store(a.err, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    off = 0;
-    for (int h = 0; h < H; ++h) {
-      tab[h] = make_int2(kh_s[h], off);
-      off += kh_s[h];
-    }
-  }
-  __syncthreads();
-  if (a.out)
-    for (int h = t; h < H; h += NT) a.out[(int64_t)b * H + h] = kh_s[h];
-}
-
-hipError_t launch_alloc(const AllocArgs &a, const SeqTable &st, hipStream_t s) {
-  if (a.Hkv < 1 || a.Hkv > kMaxAllocHeads || !a.vec_B || !a.vec_A || !a.hb) return hipErrorInvalidValue;
-  const size_t lds = alloc_lds_bytes(a.Hkv);
-  allow_lds<k_alloc>(lds);
-  hipLaunchKernelGGL(k_alloc, dim3(st.batch), dim3(kAllocThreads), lds, s, a, st);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- split calibrate

@@ -69,3 +69,69 @@ def test_small_grids(hq, hkv, d, window, dtype, lens, wide, monkeypatch):
     for l in range(wl.num_layers):
         for x, y in zip(got[l], want[l]):
             assert torch.equal(x, y), f"layer {l}"
+
+
+def _budgets_by_counting(B, cu, W, budgets, half, alpha):
+    """The adaptive allocation's budgets by sorting the pooled scores, pooled
+    in float32 in position order as the GPU does."""
+    import numpy as np
+    H = B.shape[0]
+    out = []
+    for b, K in enumerate(budgets):
+        x = B[:, cu[b]:cu[b + 1] - W]
+        nc = x.shape[1]
+        if nc <= K:
+            out.append([K] * H)
+            continue
+        A = np.zeros_like(x)
+        cnt = np.zeros(nc, np.float32)
+        for o in range(-half, half + 1):
+            lo, hi = max(0, -o), min(nc, nc - o)
+            A[:, lo:hi] += x[:, lo + o:hi + o]
+            cnt[lo:hi] += 1
+        A = A / cnt
+        f = int(min(float(K), np.floor(float(np.float32(alpha)) * K)))
+        rest = []
+        for h in range(H):
+            order = np.lexsort((np.arange(nc), -A[h]))[f:]
+            rest += [(-A[h, i], h, i) for i in order]
+        rest.sort()
+        kh = [f] * H
+        for _, h, _i in rest[:H * (K - f)]:
+            kh[h] += 1
+        out.append(kh)
+    return np.array(out, np.int32)
+
+
+@pytest.mark.parametrize("hkv,lens,budgets", [
+    (1, (64, 2080, 33), (10, 100, 40)),          # one head; a sequence that keeps everything
+    (5, (2047, 4130), (17, 400)),
+    (32, (1000, 6200), (50, 300)),
+])
+@pytest.mark.parametrize("values", ["spread", "ties", "negative", "constant"])
+@pytest.mark.parametrize("alpha", [0.0, 0.2, 1.0])
+def test_allocation(hkv, lens, budgets, values, alpha):
+    """bacon_allocate_heads against sorting, exactly: keys spread over many
+    bins, thousands of ties in the boundary bin, negative values (which share
+    the histogram's lowest bin), and one constant."""
+    import numpy as np
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    wl = _wl(1, hkv, hkv, 64, 16, 5, "bf16", lens, budgets)
+    rng = np.random.default_rng(hkv * 100 + len(values))
+    T = wl.total_tokens
+    B = rng.random((hkv, T), dtype=np.float32) ** 3
+    if values == "ties":
+        B = np.round(B * 4).astype(np.float32) / 4
+    elif values == "negative":
+        B -= 0.9
+    elif values == "constant":
+        B = np.full_like(B, 0.25)
+    ctx = P.make_ctx(wl, P.params_for(wl, alloc_floor=alpha))
+    batch = bacon.BatchLayout(wl.cu_seqlens, wl.budgets_arr)
+    got = ctx.bacon_allocate_heads(batch, torch.from_numpy(B).cuda()).cpu().numpy()
+    again = ctx.bacon_allocate_heads(batch, torch.from_numpy(B).cuda()).cpu().numpy()
+    want = _budgets_by_counting(B, wl.cu_seqlens, wl.window, wl.budgets, wl.pool_kernel // 2, alpha)
+    assert np.array_equal(got, again)
+    assert np.array_equal(got, want)
