@@ -53,9 +53,8 @@ _NAMES = [
     (r"bacon::k_segcand\b", "segment_cand"),
     (r"bacon::k_segfinal\b", "final_topk"),
     (r"bacon::k_compact\b", "compact"),
-    (r"bacon::k_select<1>", "select_calib"),
-    (r"bacon::k_select<2>", "select_topk"),
-    (r"bacon::k_elem\b", "calib_elem"),
+    (r"bacon::k_split_", "split_calib"),
+    (r"bacon::k_select\b", "select_topk"),
     (r"bacon::k_alloc\b", "head_alloc"),
 ]
 

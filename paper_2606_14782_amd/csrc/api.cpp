@@ -36,7 +36,7 @@ bacon_status hip_fail(hipError_t e, const char *what) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t ring, vec_b, vec_vp, vec_v, vec_pb, vec_pv, vec_s, hist_b, hist_s, list_bk, list_bp, list_bv,
+  size_t ring, vec_b, vec_v, vec_pb, vec_pv, vec_s, hist_b, hist_s, list_bk, list_bp, list_bv,
       list_sk, list_sp, cnt_b, cnt_s, rec_b, rec_s, partials, lse2, lambda, hb, sb, sync, total;
   size_t sync_bytes;
   // distances between the copies that layers in flight take in turn
@@ -135,7 +135,6 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.vec_stride = align256(vec);
   L.ring = off;     off += align256((size_t)L.slots * vec);
   L.vec_b = off;    off += L.copies_b * L.vec_stride;
-  L.vec_vp = off;   off += L.vec_stride;
   L.vec_v = off;    off += kCopies2 * L.vec_stride;
   L.vec_pb = off;   off += kCopies2 * L.vec_stride;
   L.vec_pv = off;   off += kCopies2 * L.vec_stride;
@@ -196,13 +195,13 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
 
 const char *kKernelNames[] = {"window_lse",    "lse_merge",     "window_score", "window_score_calib",
                               "segment_calib", "segment_score", "segment_cand",
-                              "final_topk",    "select_calib",  "select_topk",
-                              "calib_elem",    "compact",       "window_lse_kr",
+                              "final_topk",    "split_calib",   "select_topk",
+                              "compact",       "window_lse_kr",
                               "window_score_calib_kr", "window_score_calib_lse_kr",
                               "segment_select", "layer_stages", "window_lse_wide", "window_score_calib_wide",
                               "window_score_calib_lse", "window_score_single", "head_alloc"};
 enum KernelId { KI_LSE, KI_MERGE, KI_SCORE, KI_FUSED, KI_SEGCAL, KI_SEGSCORE, KI_SEGCAND, KI_FINAL,
-                KI_SEL_CALIB, KI_SEL_TOPK, KI_ELEM, KI_COMPACT, KI_LSE_KR, KI_FUSED_KR, KI_DUAL_KR,
+                KI_SPLIT_CALIB, KI_SEL_TOPK, KI_COMPACT, KI_LSE_KR, KI_FUSED_KR, KI_DUAL_KR,
                 KI_SEL, KI_MEGA, KI_LSE_WIDE, KI_FUSED_WIDE, KI_DUAL, KI_SINGLE, KI_ALLOC, KI_COUNT };
 
 }  // namespace
@@ -334,10 +333,7 @@ int batch_seq_rows(const bacon_batch *bt, int hkv, int b) {
   return m;
 }
 
-// edge_tables: the split calibrate path completes L next to chunk boundaries
-// from an LDS table of kEdgeEntries positions, which bounds the chunk count.
-SeqTable make_table(const bacon_ctx *c, const bacon_batch *bt, int *chunk_out,
-                    bool edge_tables = true, int force_chunk = 0) {
+SeqTable make_table(const bacon_ctx *c, const bacon_batch *bt, int *chunk_out, int force_chunk = 0) {
   SeqTable st{};
   st.batch = bt->batch;
   const bool bf16 = c->shape.dtype == BACON_BF16;
@@ -355,13 +351,6 @@ SeqTable make_table(const bacon_ctx *c, const bacon_batch *bt, int *chunk_out,
   const int64_t slots = 256LL * std::min(by_lds, by_waves);
   int per_wg = (int)std::max<int64_t>(1, (stages + slots - 1) / slots);
   if (c->chunk_stages_override > 0) per_wg = c->chunk_stages_override;
-  // the select kernel stages 2r positions around every chunk boundary
-  int nmax = 0;
-  for (int b = 0; b < bt->batch; ++b) nmax = std::max(nmax, bt->cu_seqlens[b + 1] - bt->cu_seqlens[b]);
-  if (edge_tables && c->params.radius > 0) {
-    const int min_chunk = (int)(((int64_t)nmax * 2 * c->params.radius + kEdgeEntries - 1) / kEdgeEntries);
-    per_wg = std::max(per_wg, (min_chunk + tk - 1) / tk);
-  }
   per_wg = std::min(per_wg, kMaxChunk / tk);
   const int chunk = force_chunk > 0 ? force_chunk : tk * per_wg;
   int cb = 0, ib = 0, kb = 0, sb = 0;
@@ -408,7 +397,6 @@ PassArgs pass_args(const bacon_ctx *c, const SeqTable &st, int chunk, const void
     a.hist_B = reinterpret_cast<unsigned *>(c->ws + c->L.hist_b);
     a.ring = reinterpret_cast<float *>(c->ws + c->L.ring);
     a.vec_B = reinterpret_cast<float *>(c->ws + c->L.vec_b);
-    a.vec_VP = reinterpret_cast<float *>(c->ws + c->L.vec_vp);
   }
   a.radius = c->params.radius;
   a.terms = c->params.terms;
@@ -474,26 +462,56 @@ void ring_slots(const bacon_ctx *c, int layer, int *wr, int *cnt) {
   *wr = layer % c->L.slots;
 }
 
-SelArgs sel_args(const bacon_ctx *c) {
-  SelArgs a{};
-  const bacon_shape &s = c->shape;
-  const bacon_params &p = c->params;
-  a.Hkv = s.num_kv_heads;
-  a.W = s.window;
-  a.T = s.max_total_tokens;
-  a.radius = p.radius;
-  a.pool_half = p.pool_kernel / 2;
-  a.pool_mode = p.pool_mode;
-  a.rho = p.rho;
-  a.gamma = p.gamma;
-  a.eps = p.eps;
-  a.use_last_query = p.use_last_query;
-  a.terms = p.terms;
-  a.vec_B = reinterpret_cast<const float *>(c->ws + c->L.vec_b);
-  a.vec_VP = reinterpret_cast<const float *>(c->ws + c->L.vec_vp);
-  a.vp_chunk = 1 << 30;
-  a.lambda_ws = reinterpret_cast<float *>(c->ws + c->L.lambda);
-  return a;
+// Whether a batch takes the wide passes, with how many row groups per
+// workgroup and chunks per workgroup.  The estimate of a launch that holds
+// both passes and the select jobs (us, from traces of 16 to 512 workgroups):
+// a workgroup takes 6 us plus 2.2 per further chunk and, per row tile of four
+// waves on a SIMD, 0.9 (bf16) or what its fp32 matrix instructions take; a select workgroup 8;
+// beyond one round of the CUs a launch takes the sum over the CUs and half a
+// workgroup more.
+bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) {
+  const bool bf16 = c->shape.dtype == BACON_BF16;
+  const int nrt = c->L.rpad / 32, hkv = c->shape.num_kv_heads;
+  const double tile = bf16 ? 0.9 : 0.053 * c->shape.head_dim;
+  int64_t segs = 0;
+  for (int b = 0; b < bt->batch; ++b) segs += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + kSegLen - 1) / kSegLen;
+  const double sel = (double)(3 * segs + bt->batch) * hkv;
+  double best = 1e30;
+  for (int s = 1; s <= 4; s *= 2) {
+    if (!wide_supported(bf16, c->shape.head_dim, c->L.rpad, s)) continue;
+    int64_t blocks = 0;
+    int nch = 0;
+    for (int b = 0; b < bt->batch; ++b) {
+      const int k = (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s);
+      blocks += k;
+      nch = std::max(nch, k);
+    }
+    if (nch > wide_max_chunks(c->L.rpad) || blocks * hkv > (int64_t)c->wide_limit * s) continue;
+    for (int p = 1; p <= 2; ++p) {
+      int64_t jobs = 0;
+      for (int b = 0; b < bt->batch; ++b)
+        jobs += ((bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s) + p - 1) / p;
+      const double t = 6.0 + 2.2 * (p - 1) + p * tile * std::max((double)nrt / s, 0.25 * ((nrt + s - 1) / s));
+      const double n = 2.0 * jobs * hkv + sel, cus = c->cus > 0 ? c->cus : 256;
+      const double est = n <= cus ? std::max(t, 8.0) : (2.0 * jobs * hkv * t + sel * 8.0) / cus + 0.5 * t;
+      if (est < best) {
+        best = est;
+        *split = s;
+        *cpw = p;
+      }
+    }
+  }
+  return best < 1e30;
+}
+
+// The wide passes' fields of a's arguments over the chunks of st.
+void wide_args(const bacon_ctx *c, PassArgs &a, int split, int cpw, const SeqTable &st) {
+  a.wide_split_log = split >> 1;   // 1, 2, 4
+  a.wide_cpw_log = cpw >> 1;       // 1, 2
+  a.row_log = wide_row_log(c->L.rpad);
+  a.w_magic = 65536u / (unsigned)a.W + 1u;
+  a.wide_jobs = 0;
+  for (int b = 0; b < st.batch; ++b) a.wide_jobs += (st.chunk_base[b + 1] - st.chunk_base[b] + cpw - 1) / cpw;
 }
 
 // The head-wise allocation's arguments of a layer, but for B and the sequences'
@@ -522,21 +540,16 @@ int max_len(const bacon_batch *bt);
 
 // Every workgroup of the pass must fit the LDS of one CU; checked before
 // anything is enqueued.
-bacon_status check_lds(const bacon_ctx *c, const bacon_batch *bt, int chunk, bool passes,
-                       int sel_mode) {
-  const bool bf16 = c->shape.dtype == BACON_BF16;
-  if (passes && pass_lds_bytes(PASS_FUSED, bf16, c->shape.head_dim, c->L.rpad, chunk) > kLdsBytes)
+bacon_status check_lds(const bacon_ctx *c, int chunk) {
+  if (pass_lds_bytes(PASS_FUSED, c->shape.dtype == BACON_BF16, c->shape.head_dim, c->L.rpad, chunk) > kLdsBytes)
     return fail(BACON_ERR_UNSUPPORTED, "pass workgroup needs more LDS than a CU has");
-  if (sel_mode >= 0 && max_len(bt) > kMaxSelLen)
+  return BACON_OK;
+}
+// The split calls' selections hold sequences of up to kMaxSelLen tokens.
+bacon_status check_split(const bacon_batch *bt) {
+  if (max_len(bt) > kMaxSelLen)
     return fail(BACON_ERR_UNSUPPORTED, "the split calls select sequences of up to %d tokens (%d given); "
                 "the fused calls take up to %d", kMaxSelLen, max_len(bt), kMaxSeqLen);
-  if (sel_mode >= 0 && select_lds_bytes(sel_mode, max_len(bt)) > (size_t)kLdsBytes)
-    return fail(BACON_ERR_UNSUPPORTED, "select workgroup needs more LDS than a CU has");
-  if (sel_mode == SEL_CALIB) {
-    const int n = max_len(bt);
-    if (chunk < n && (int64_t)((n - 1) / chunk) * 2 * c->params.radius > kEdgeEntries)
-      return fail(BACON_ERR_UNSUPPORTED, "too many chunk boundaries for radius %d", c->params.radius);
-  }
   return BACON_OK;
 }
 
@@ -637,8 +650,12 @@ bacon_status bacon_score(bacon_ctx *c, int32_t layer, const bacon_batch *bt, con
   if (d_lse) TRY(check_ptr(d_lse, "lse", 4));
   hipStream_t s = static_cast<hipStream_t>(stream);
   int chunk = 0;
-  const SeqTable st = make_table(c, bt, &chunk);
-  TRY(check_lds(c, bt, chunk, true, -1));
+  SeqTable st = make_table(c, bt, &chunk);
+  TRY(check_lds(c, chunk));
+  // small grids take the wide passes (with the streaming passes' sums)
+  int split = 1, cpw = 1;
+  const bool wide = !c->kr_off && wide_plan(c, bt, &split, &cpw);
+  if (wide) st = make_table(c, bt, &chunk, wide_keys(split));
   PassArgs a = pass_args(c, st, chunk, d_q_win, d_k);
   a.T = bt->cu_seqlens[bt->batch];
   a.lse_user = d_lse;
@@ -646,6 +663,12 @@ bacon_status bacon_score(bacon_ctx *c, int32_t layer, const bacon_batch *bt, con
   a.out_Q = d_Q;
   const bool bf16 = c->shape.dtype == BACON_BF16;
   const bool w32 = c->shape.window == 32;
+  if (wide) {
+    wide_args(c, a, split, 1, st);
+    TRY(timed(c, KI_LSE_WIDE, s, [&] { return launch_wide(PASS_LSE, bf16, c->shape.head_dim, a, st, s); }));
+    if (d_lse) TRY(timed(c, KI_MERGE, s, [&] { return launch_lse_merge(a, st, s); }));
+    return timed(c, KI_FUSED_WIDE, s, [&] { return launch_wide(PASS_FUSED, bf16, c->shape.head_dim, a, st, s); });
+  }
   TRY(timed(c, KI_LSE, s, [&] { return launch_pass(PASS_LSE, bf16, c->shape.head_dim, false, a, st, s); }));
   TRY(timed(c, KI_MERGE, s, [&] { return launch_lse_merge(a, st, s); }));
   return timed(c, KI_SCORE, s, [&] { return launch_pass(PASS_SCORE, bf16, c->shape.head_dim, w32, a, st, s); });
@@ -668,38 +691,49 @@ bacon_status bacon_calibrate(bacon_ctx *c, int32_t layer, const bacon_batch *bt,
   if (d_E) TRY(check_ptr(d_E, "E", 4));
   if (d_V) TRY(check_ptr(d_V, "V", 4));
   hipStream_t s = static_cast<hipStream_t>(stream);
+  TRY(check_split(bt));
   int chunk = 0;
   const SeqTable st = make_table(c, bt, &chunk);
-  TRY(check_lds(c, bt, chunk, false, SEL_CALIB));
-  const int64_t T = bt->cu_seqlens[bt->batch];
-  ElemArgs e{};
-  e.in_B = d_B;
-  e.in_Q = d_Q;
-  e.ring = reinterpret_cast<float *>(c->ws + c->L.ring);
-  ring_slots(c, layer, &e.ring_write, &e.ring_cnt);
-  e.ring_slots = c->L.slots;
-  e.ring_stride = (int64_t)c->shape.num_kv_heads * T;
-  e.vec_VP = reinterpret_cast<float *>(c->ws + c->L.vec_vp);
-  e.Hkv = c->shape.num_kv_heads;
-  e.radius = c->params.radius;
-  e.chunk = chunk;
-  e.T = T;
-  e.terms = c->params.terms;
-  // the [Hkv, T] vectors of the split path use the batch's T as row length
-  TRY(timed(c, KI_ELEM, s, [&] { return launch_elem(e, st, s); }));
-  SelArgs a = sel_args(c);
-  a.T = T;
+  // the [Hkv, T] vectors of the split path use the batch's T as row length;
+  // its lists and V take the first copies of the fused pass's, and the B
+  // histogram an S histogram (each user clears it first)
+  const Layout &L = c->L;
+  SplitArgs p{};
+  SegArgs &a = p.s;
+  a.Hkv = c->shape.num_kv_heads;
+  a.W = c->shape.window;
+  a.T = bt->cu_seqlens[bt->batch];
+  a.radius = c->params.radius;
+  a.pool_half = c->params.pool_kernel / 2;
+  a.pool_mode = c->params.pool_mode;
+  a.rho = c->params.rho;
+  a.gamma = c->params.gamma;
+  a.eps = c->params.eps;
+  a.use_last_query = c->params.use_last_query;
+  a.terms = c->params.terms;
   a.vec_B = d_B;
-  a.vp_chunk = chunk;   // same chunking as the fused pass
-  a.ring = e.ring;
-  a.ring_stride = e.ring_stride;
-  a.ring_slot = e.ring_write;
-  a.out_S = d_S;
-  a.out_V = d_V;
-  a.out_E = d_E;
+  a.ring = reinterpret_cast<float *>(c->ws + L.ring);
+  a.ring_stride = (int64_t)a.Hkv * a.T;
+  a.ring_slots = L.slots;
+  ring_slots(c, layer, &a.ring_slot, &a.ring_cnt);
+  a.vec_V = reinterpret_cast<float *>(c->ws + L.vec_v);
+  a.hist_B = reinterpret_cast<unsigned *>(c->ws + L.hist_s);
+  a.listB_key = reinterpret_cast<unsigned *>(c->ws + L.list_bk);
+  a.listB_pos = reinterpret_cast<int *>(c->ws + L.list_bp);
+  a.listB_v = reinterpret_cast<float *>(c->ws + L.list_bv);
+  a.cntB = reinterpret_cast<int *>(c->ws + L.cnt_b);
+  a.recB = reinterpret_cast<int4 *>(c->ws + L.rec_b);
+  a.lambda_ws = reinterpret_cast<float *>(c->ws + L.lambda);
   a.out_lambda = d_lambda;
+  p.in_Q = d_Q;
+  p.out_S = d_S;
+  p.out_V = d_V;
+  p.out_E = d_E;
   TRY(head_table(c, bt, s, &a.hb));
-  TRY(timed(c, KI_SEL_CALIB, s, [&] { return launch_select(SEL_CALIB, max_len(bt), a, st, s); }));
+  const hipError_t e = launch_zero(a.hist_B, (int64_t)bt->batch * a.Hkv * kHBins, s);
+  if (e != hipSuccess) return hip_fail(e, "clear");
+  for (int stage = 0; stage < 3; ++stage)
+    TRY(timed(c, KI_SPLIT_CALIB, s, [&] { return launch_split(stage, p, st, s); }));
   c->next_layer = layer + 1;
   return BACON_OK;
 }
@@ -713,13 +747,17 @@ bacon_status bacon_select_topk(bacon_ctx *c, const bacon_batch *bt, const float 
   hipStream_t s = static_cast<hipStream_t>(stream);
   int chunk = 0;
   const SeqTable st = make_table(c, bt, &chunk);
-  TRY(check_lds(c, bt, chunk, false, SEL_TOPK));
-  SelArgs a = sel_args(c);
+  TRY(check_split(bt));
+  SelArgs a{};
+  a.Hkv = c->shape.num_kv_heads;
+  a.W = c->shape.window;
   a.T = bt->cu_seqlens[bt->batch];
+  a.pool_half = c->params.pool_kernel / 2;
+  a.pool_mode = c->params.pool_mode;
   a.in_S = d_S;
   a.idx = d_idx;
   TRY(head_table(c, bt, s, &a.hb));
-  return timed(c, KI_SEL_TOPK, s, [&] { return launch_select(SEL_TOPK, max_len(bt), a, st, s); });
+  return timed(c, KI_SEL_TOPK, s, [&] { return launch_select(a, st, s); });
 }
 
 bacon_status bacon_allocate_heads(bacon_ctx *c, const bacon_batch *bt, const float *d_B,
@@ -802,48 +840,6 @@ struct LayerRun {
   const float *lse = nullptr;   // caller normalisers (pass 1 skipped)
 };
 
-// Whether a batch takes the wide passes, with how many row groups per
-// workgroup and chunks per workgroup.  The estimate of a launch that holds
-// both passes and the select jobs (us, from traces of 16 to 512 workgroups):
-// a workgroup takes 6 us plus 2.2 per further chunk and, per row tile of four
-// waves on a SIMD, 0.9 (bf16) or what its fp32 matrix instructions take; a select workgroup 8;
-// beyond one round of the CUs a launch takes the sum over the CUs and half a
-// workgroup more.
-bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) {
-  const bool bf16 = c->shape.dtype == BACON_BF16;
-  const int nrt = c->L.rpad / 32, hkv = c->shape.num_kv_heads;
-  const double tile = bf16 ? 0.9 : 0.053 * c->shape.head_dim;
-  int64_t segs = 0;
-  for (int b = 0; b < bt->batch; ++b) segs += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + kSegLen - 1) / kSegLen;
-  const double sel = (double)(3 * segs + bt->batch) * hkv;
-  double best = 1e30;
-  for (int s = 1; s <= 4; s *= 2) {
-    if (!wide_supported(bf16, c->shape.head_dim, c->L.rpad, s)) continue;
-    int64_t blocks = 0;
-    int nch = 0;
-    for (int b = 0; b < bt->batch; ++b) {
-      const int k = (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s);
-      blocks += k;
-      nch = std::max(nch, k);
-    }
-    if (nch > wide_max_chunks(c->L.rpad) || blocks * hkv > (int64_t)c->wide_limit * s) continue;
-    for (int p = 1; p <= 2; ++p) {
-      int64_t jobs = 0;
-      for (int b = 0; b < bt->batch; ++b)
-        jobs += ((bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s) + p - 1) / p;
-      const double t = 6.0 + 2.2 * (p - 1) + p * tile * std::max((double)nrt / s, 0.25 * ((nrt + s - 1) / s));
-      const double n = 2.0 * jobs * hkv + sel, cus = c->cus > 0 ? c->cus : 256;
-      const double est = n <= cus ? std::max(t, 8.0) : (2.0 * jobs * hkv * t + sel * 8.0) / cus + 0.5 * t;
-      if (est < best) {
-        best = est;
-        *split = s;
-        *cpw = p;
-      }
-    }
-  }
-  return best < 1e30;
-}
-
 // Checks one layer's arguments and builds its launch arguments; enqueues
 // nothing.  The layer order is the caller's to check.  Buffers that later
 // layers may write while this layer's select is still in flight come in
@@ -868,10 +864,10 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   // key-register passes where they cover the shape, else the streaming passes
   r.kr = !c->kr_off && kr_supported(r.bf16, c->shape.head_dim, c->L.rpad);
   if (r.kr) {
-    r.st = make_table(c, bt, &r.chunk, false, kr_keys(r.bf16, c->shape.head_dim));
+    r.st = make_table(c, bt, &r.chunk, kr_keys(r.bf16, c->shape.head_dim));
   } else {
-    r.st = make_table(c, bt, &r.chunk, false);
-    TRY(check_lds(c, bt, r.chunk, true, -1));
+    r.st = make_table(c, bt, &r.chunk);
+    TRY(check_lds(c, r.chunk));
   }
   // One read of K (the single-read pass) when its meeting can complete:
   // workgroups run in grid order, chunk-major with the KV heads innermost,
@@ -904,7 +900,7 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   if (!c->kr_off && !r.single) r.wide = wide_plan(c, bt, &split, &cpw);
   if (r.wide) {
     r.kr = false;
-    r.st = make_table(c, bt, &r.chunk, false, wide_keys(split));
+    r.st = make_table(c, bt, &r.chunk, wide_keys(split));
   }
   r.kmax = 0;
   for (int b = 0; b < bt->batch; ++b) r.kmax = std::max(r.kmax, batch_seq_rows(bt, c->shape.num_kv_heads, b));
@@ -933,11 +929,7 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   a.partials += c2 * c->L.part_stride / sizeof(float2);
   a.lse2 += c2 * c->L.lse_stride / sizeof(float);
   a.kr_sums = kr_shape;
-  a.wide_split_log = split >> 1;   // 1, 2, 4
-  a.wide_cpw_log = cpw >> 1;       // 1, 2
-  a.row_log = wide_row_log(c->L.rpad);
-  a.w_magic = 65536u / (unsigned)a.W + 1u;
-  for (int b = 0; b < bt->batch; ++b) a.wide_jobs += (r.st.chunk_base[b + 1] - r.st.chunk_base[b] + cpw - 1) / cpw;
+  wide_args(c, a, split, cpw, r.st);
   int ring_cnt = 0;
   ring_slots(c, layer, &a.ring_write, &ring_cnt);
   a.ring_stride = (int64_t)c->shape.num_kv_heads * T;
@@ -949,7 +941,6 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.radius = c->params.radius;
   g.pool_half = c->params.pool_kernel / 2;
   g.pool_mode = c->params.pool_mode;
-  g.vp_chunk = r.chunk;
   g.rho = c->params.rho;
   g.gamma = c->params.gamma;
   g.eps = c->params.eps;
@@ -959,7 +950,6 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.use_last_query = c->params.use_last_query;
   g.terms = c->params.terms;
   g.vec_B = a.vec_B;
-  g.vec_VP = a.vec_VP;
   g.ring = a.ring;
   g.ring_stride = a.ring_stride;
   g.ring_slots = c->L.slots;
@@ -1295,10 +1285,10 @@ bacon_status window_lse(bacon_ctx *c, const bacon_batch *bt, const void *d_q_win
   SeqTable st{};
   const bool kr = !c->kr_off && kr_supported(bf16, c->shape.head_dim, c->L.rpad);
   if (kr) {
-    st = make_table(c, bt, &chunk, false, kr_keys(bf16, c->shape.head_dim));
+    st = make_table(c, bt, &chunk, kr_keys(bf16, c->shape.head_dim));
   } else {
-    st = make_table(c, bt, &chunk, false);
-    TRY(check_lds(c, bt, chunk, true, -1));
+    st = make_table(c, bt, &chunk);
+    TRY(check_lds(c, chunk));
   }
   PassArgs a = pass_args(c, st, chunk, d_q_win, d_k);
   a.T = bt->cu_seqlens[bt->batch];

@@ -21,7 +21,6 @@ constexpr int kPoolHalo = 16;       // largest pool half-width
 constexpr int kHBins = 8192;        // bins of the select histograms (32 per octave of a float)
 constexpr int kHCopies = 1;         // copies of the B histogram the fused pass spreads its atomics over
 constexpr int kLdsBytes = 160 * 1024;   // LDS per CU (and per workgroup) on gfx950
-constexpr int kEdgeEntries = 1024;      // positions next to chunk boundaries the select stages
 constexpr int kKrWaves = 4;             // waves of a key-register pass workgroup
 constexpr int kSyncStride = 64;          // words between groups' meeting counters (own 256-byte lines)
 // Static device scratch of the allocation-free entry point (per GPU).
@@ -63,7 +62,6 @@ struct PassArgs {
   int64_t ring_stride;  // Hkv * T, floats between slots
   int ring_write;       // slot receiving this layer's E
   float *vec_B;         // [Hkv, T] window score
-  float *vec_VP;        // [Hkv, T] unused by the fused pass (the calibration kernel forms V)
   int radius;
   uint32_t terms;
   // single-read pass: per group (sequence, KV head) an arrival and a done
@@ -82,28 +80,15 @@ struct PassArgs {
   unsigned w_magic;       // 65536 / W + 1: r / W is (r * w_magic) >> 16 for r < 256, W <= 256
 };
 
-enum SelMode { SEL_CALIB = 1, SEL_TOPK = 2 };
 enum PoolMode { POOL_MEAN_S = 0, POOL_MAX_S = 1, POOL_MEAN_B = 2 };
 
+// The split top-K.
 struct SelArgs {
   int Hkv, W;
   int64_t T;
-  int radius, pool_half, pool_mode;
-  int vp_chunk;            // chunk size of the in-chunk L partial in vec_VP
-  double rho;              // scale-matching expansion (double: M = floor(rho K) as the oracle forms it)
-  float gamma, eps;
-  int use_last_query;
-  uint32_t terms;
-  const float *vec_B;      // [Hkv, T]
-  const float *vec_VP;     // [Hkv, T]
-  const float *ring;       // [slots, Hkv, T] E history
-  int64_t ring_stride;     // Hkv * T
-  int ring_slot;           // slot of this layer's E
-  const float *in_S;       // SEL_TOPK: user S [Hkv, T]
-  float *out_S, *out_V, *out_E;  // SEL_CALIB optional outputs [Hkv, T]
-  float *out_lambda;       // optional [B, Hkv]
-  float *lambda_ws;        // [B, Hkv]
-  int32_t *idx;            // SEL_TOPK output
+  int pool_half, pool_mode;
+  const float *in_S;       // user S [Hkv, T]
+  int32_t *idx;
   const int2 *hb;          // optional [B, Hkv] (budget, idx offset in the sequence)
 };
 
@@ -111,7 +96,7 @@ struct SelArgs {
 struct SegArgs {
   int Hkv, W;
   int64_t T;
-  int radius, pool_half, pool_mode, vp_chunk;
+  int radius, pool_half, pool_mode;
   double rho;                    // scale-matching expansion
   float gamma, eps;
   // relative rounding bound of B (0 when B is exact to fp32): a set whose
@@ -120,7 +105,7 @@ struct SegArgs {
   float b_floor;
   int use_last_query;
   uint32_t terms;
-  const float *vec_B, *vec_VP;   // [Hkv, T]
+  const float *vec_B;            // [Hkv, T]
   const float *ring;             // [slots, Hkv, T] E history
   int64_t ring_stride;           // Hkv * T
   int ring_slots, ring_slot;     // slot count; slot of this layer's E
@@ -175,15 +160,13 @@ struct AllocArgs {
   unsigned *err;                 // optional error word (set to 2 if the search fails)
 };
 
-struct ElemArgs {           // split calibrate: E, T, L, ring update
-  const float *in_B, *in_Q;
-  float *ring;
-  int64_t ring_stride;
-  int ring_slots, ring_write, ring_cnt;
-  float *vec_VP;
-  int Hkv, radius, chunk;
-  int64_t T;
-  uint32_t terms;
+// The split calibrate: the segment select's arguments (vec_B the caller's B,
+// hist_B zeroed, vec_V over every position), Q and the outputs.
+struct SplitArgs {
+  SegArgs s;
+  const float *in_Q;
+  float *out_S;
+  float *out_V, *out_E;    // optional [Hkv, T]
 };
 
 struct CompactArgs {
@@ -261,11 +244,11 @@ hipError_t launch_single(int head_dim, bool w32, const PassArgs &a, const SeqTab
 // Workgroups of the single-read pass the device holds at once (0 if unknown).
 int single_resident_blocks(int head_dim, int rpad);
 int single_lds_bytes(int head_dim, int rpad);
-// LDS a select workgroup needs (static + dynamic) for sequences up to max_len.
-size_t select_lds_bytes(int mode, int max_len);
-hipError_t launch_select(int mode, int max_len, const SelArgs &a, const SeqTable &st,
-                         hipStream_t s);
-hipError_t launch_elem(const ElemArgs &a, const SeqTable &st, hipStream_t s);
+// LDS a workgroup of the split top-K needs (static + dynamic).
+size_t select_lds_bytes();
+hipError_t launch_select(const SelArgs &a, const SeqTable &st, hipStream_t s);
+// The split calibrate's three launches: 0 evidence, 1 lists, 2 scores.
+hipError_t launch_split(int stage, const SplitArgs &p, const SeqTable &st, hipStream_t s);
 hipError_t launch_lse_merge(const PassArgs &a, const SeqTable &st, hipStream_t s);
 // The jobs of one select launch, each of its own layer (NULL: none).
 struct SelJobs {

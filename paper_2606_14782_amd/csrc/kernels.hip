@@ -1525,11 +1525,17 @@ __device__ __forceinline__ void wide_body(const PassArgs &a, const SeqTable &st,
         const float gw = (float)(a.G * W), gf = (float)a.G;
         const float Bv = a.kr_sums ? sb * (1.f / gw) : sb / gw, Qv = a.kr_sums ? sq * (1.f / gf) : sq / gf;
         const int64_t pos = (int64_t)h * a.T + st.cu[b] + ke;
-        // E (Eq. boundary_residual) to this layer's history slot
-        a.ring[a.ring_write * a.ring_stride + pos] = (Qv > Bv) ? (Qv - Bv) : 0.f;
-        a.vec_B[pos] = Bv;
-        const int bin = hbin(float_key(Bv));
-        if (cand) atomicAdd(&hist[bin >> 1], (bin & 1) ? 0x10000u : 1u);
+        if (a.out_B) {
+          // the split score call: the scores themselves
+          a.out_B[pos] = Bv;
+          a.out_Q[pos] = Qv;
+        } else {
+          // E (Eq. boundary_residual) to this layer's history slot
+          a.ring[a.ring_write * a.ring_stride + pos] = (Qv > Bv) ? (Qv - Bv) : 0.f;
+          a.vec_B[pos] = Bv;
+          const int bin = hbin(float_key(Bv));
+          if (cand) atomicAdd(&hist[bin >> 1], (bin & 1) ? 0x10000u : 1u);
+        }
       }
       if (cc + 1 < cnt) lds_barrier();                // the sums are read
     }
@@ -1537,6 +1543,7 @@ __device__ __forceinline__ void wide_body(const PassArgs &a, const SeqTable &st,
   if constexpr (FUSED) {
     // the chunks' histogram to memory; consecutive lanes take consecutive
     // bins, so that a wave's additions fall on few lines
+    if (a.out_B) return;
     lds_barrier();
     unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
     const unsigned short *h16 = reinterpret_cast<const unsigned short *>(hist);
@@ -2550,8 +2557,6 @@ __device__ __forceinline__ void block_select(KeyF key, int k, unsigned &xk, int 
   xk = lo;
 }
 
-constexpr int kEdgeCap = kEdgeEntries;   // LDS tables of E and L corrections next to chunk boundaries
-
 // Exact top-k threshold with the tie rule (key descending, then position
 // ascending) over the block's non-zero keys, 1 <= k <= count: element j is
 // kept iff key > xk, or key == xk and position <= pthr.
@@ -2688,7 +2693,6 @@ using SelShared = SelSharedT<kSelThreads>;
 __device__ __forceinline__ int pad32(int i) { return i + i / kSelPer; }
 constexpr int kArrWords = kMaxSelLen + kMaxSelLen / kSelPer + 64;
 
-template <int MODE>
 __global__ __launch_bounds__(kSelThreads) void k_select(SelArgs a, SeqTable st) {
   constexpr int PER = kSelPer;
   extern __shared__ __align__(16) float arr[];
@@ -2698,160 +2702,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelArgs a, SeqTable st) 
   const int nc = n - a.W;                           // candidate set [0, nc)
   const int K = head_budget(st, a.hb, a.Hkv, b, h);
   const int64_t base = (int64_t)h * a.T + st.cu[b];
-  // LDS: arr [pad32 extent of kMaxSelLen], candidate list, then per-mode tables
+  // LDS: arr [pad32 extent of kMaxSelLen], candidate list
   unsigned *ckey = reinterpret_cast<unsigned *>(arr + kArrWords);
   int *cpos = reinterpret_cast<int *>(ckey + kCandCap);
-
-  if constexpr (MODE != SEL_TOPK) {
-    // The L neighbours of positions next to a chunk boundary of vec_VP that lie
-    // in the neighbouring chunk.  Boundary c*CH (c >= 1) covers the 2r
-    // positions [c*CH - r, c*CH + r); the host keeps nbnd*2r <= kEdgeCap.
-    const int r = a.radius, CH = a.vp_chunk;
-    const bool use_l = (a.terms & 2u) != 0;
-    const int nbnd = (use_l && CH < n) ? (n - 1) / CH : 0;      // boundaries inside the sequence
-    const int nedge = nbnd * 2 * r;
-    float *edge = reinterpret_cast<float *>(cpos + kCandCap);     // E at those positions
-    float *fixt = edge + kEdgeCap;                                // their L correction
-    const float *re = a.ring + a.ring_slot * a.ring_stride + base;   // E of this layer
-    for (int q = t; q < nedge; q += kSelThreads) {
-      const int c = q / (2 * r) + 1, o = q - (c - 1) * 2 * r;
-      const int u = c * CH - r + o;
-      const float e = re[min(max(u, 0), n - 1)];
-      edge[q] = (u >= 0 && u < n) ? e : 0.f;
-    }
-    lds_barrier();
-    for (int q = t; q < nedge; q += kSelThreads) {
-      const int c = q / (2 * r) + 1, o = q - (c - 1) * 2 * r;
-      const int i = c * CH - r + o;                 // position next to boundary c*CH
-      const int lo = max(0, i - r), hi = min(n - 1, i + r);
-      float sum = 0.f;
-      if (i < c * CH) {                             // left of the boundary: right neighbours
-        for (int u = c * CH; u <= hi; ++u) sum += edge[(c - 1) * 2 * r + (u - (c * CH - r))];
-      } else {                                      // right of it: left neighbours
-        for (int u = lo; u < c * CH; ++u) sum += edge[(c - 1) * 2 * r + (u - (c * CH - r))];
-      }
-      fixt[q] = (i >= 0 && i < n) ? sum / (float)(hi - lo + 1) : 0.f;
-    }
-    // correction of position i (0 when i is not next to a boundary)
-    auto vfix = [&](int i) -> float {
-      if (nbnd == 0) return 0.f;
-      const int c = (i + r) / CH;
-      const int o = i - (c * CH - r);
-      return (c >= 1 && c <= nbnd && o < 2 * r) ? fixt[(c - 1) * 2 * r + o] : 0.f;
-    };
-    // B into LDS (strided: element j of thread t is position t + j*kSelThreads);
-    // all loads of the phase are issued before any is used.
-    {
-      const int tt = opaque(t);   // keeps the phase's address arithmetic local
-      const float *pb = a.vec_B + base;
-      float bv[PER];
-#pragma unroll
-      for (int j = 0; j < PER; ++j) bv[j] = pb[min(tt + j * kSelThreads, n - 1)];
-#pragma unroll
-      for (int j = 0; j < PER; ++j)
-        if (tt + j * kSelThreads < n) arr[pad32(tt + j * kSelThreads)] = bv[j];
-    }
-    lds_barrier();
-    // Scale-matching set: top M = min(rho K, |I|) of B over I (Eq. scale_matching_set).
-    int M = scale_set_size(a.rho, K);
-    if (M > nc) M = nc;
-    if (M < 0) M = 0;
-    const bool calib = M > 0 && a.use_last_query;
-    uint64_t msk = 0;
-    if (calib) {
-      auto keyB = [&](int j) -> unsigned {
-        const int i = t + j * kSelThreads;
-        const unsigned kx = float_key(arr[pad32(i)]);   // i < kMaxSelLen: inside arr
-        return i < nc ? kx : 0u;
-      };
-      auto posf = [&](int j) -> int { return t + j * kSelThreads; };
-      if (M >= nc) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) msk |= (uint64_t)(t + j * kSelThreads < nc ? 1u : 0u) << j;
-      } else {
-        unsigned xm;
-        int pm;
-        block_threshold<PER>(keyB, posf, M, xm, pm, ss, ckey, cpos);
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          const unsigned kj = keyB(j);
-          msk |= (uint64_t)(kj > xm || (kj == xm && posf(j) <= pm) ? 1u : 0u) << j;
-        }
-      }
-    }
-    // V for the thread's positions: vec_VP, completed next to chunk boundaries.
-    const int tt = opaque(t);
-    float vp[PER];
-    {
-      const float *pv = a.vec_VP + base;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) vp[j] = pv[min(tt + j * kSelThreads, n - 1)];
-#pragma unroll
-      for (int j = 0; j < PER; ++j) vp[j] += vfix(tt + j * kSelThreads);
-    }
-    float lam = 0.f;
-    if (calib) {
-      // population moments over the set in double; B shifted by the set minimum
-      float bv[PER];
-#pragma unroll
-      for (int j = 0; j < PER; ++j) bv[j] = arr[pad32(tt + j * kSelThreads)];
-      unsigned kmin = 0xffffffffu;
-#pragma unroll
-      for (int j = 0; j < PER; ++j)
-        kmin = ((msk >> j) & 1ull) ? min(kmin, float_key(bv[j])) : kmin;
-      kmin = block_reduce_u<0>(kmin, ss);
-      const double bref = (double)key_float(kmin);
-      // V is shifted by the smallest V of the set as well: the variance is
-      // the same, and a set of equal V gives exactly 0
-      unsigned vmin = 0xffffffffu;
-#pragma unroll
-      for (int j = 0; j < PER; ++j)
-        vmin = ((msk >> j) & 1ull) ? min(vmin, float_key(vp[j])) : vmin;
-      vmin = block_reduce_u<0>(vmin, ss);
-      const double vref = (double)key_float(vmin);
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const bool in = (msk >> j) & 1ull;
-        const double db = in ? (double)bv[j] - bref : 0.0, dv = in ? (double)vp[j] - vref : 0.0;
-        s0 += db; s1 += db * db; s2 += dv; s3 += dv * dv;
-      }
-      double sums[4];
-      block_sum4_d(s0, s1, s2, s3, ss, sums);
-      const double mb = sums[0] / M, mv = sums[2] / M;
-      double vb = sums[1] / M - mb * mb, vv = sums[3] / M - mv * mv;
-      vb = vb > 0.0 ? vb : 0.0;
-      vv = vv > 0.0 ? vv : 0.0;
-      lam = (float)((double)a.gamma * sqrt(vb) / (sqrt(vv) + (double)a.eps));   // Eq. lambda_solution
-    }
-    if (t == 0) {
-      a.lambda_ws[b * a.Hkv + h] = lam;
-      if (a.out_lambda) a.out_lambda[b * a.Hkv + h] = lam;
-    }
-    // S = B + lambda V (Eq. bacon_score), in place of B; each thread touches
-    // only its own positions.
-    // With pooling before calibration the candidates get pool(B) + lambda V
-    // instead, the score the top-K then ranks unpooled.
-    const bool mean_b = a.pool_mode == POOL_MEAN_B;
-    const int hp = a.pool_half;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int i = tt + j * kSelThreads;
-      if (i < n) {
-        float bi = arr[pad32(i)];
-        if (mean_b && i < nc) {
-          const int lo = max(0, i - hp), hi = min(nc - 1, i + hp);
-          double acc = 0.0;
-          for (int u = lo; u <= hi; ++u) acc += (double)arr[pad32(u)];
-          bi = (float)(acc / (double)(hi - lo + 1));
-        }
-        a.out_S[base + i] = fmaf(lam, vp[j], bi);
-        if (a.out_V) a.out_V[base + i] = vp[j];
-        if (a.out_E) a.out_E[base + i] = re[i];
-      }
-    }
-    return;
-  } else {
+  {
     float sv[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) sv[j] = a.in_S[base + min(t + j * kSelThreads, n - 1)];
@@ -2945,26 +2799,16 @@ __global__ __launch_bounds__(kSelThreads) void k_select(SelArgs a, SeqTable st) 
 
 }
 
-size_t select_lds_bytes(int mode, int max_len) {
-  (void)max_len;   // arr always spans kMaxSelLen so strided reads need no clamping
-  size_t bytes = (size_t)kArrWords * sizeof(float) +                              // arr (padded)
-                 2 * kCandCap * sizeof(unsigned);                                // candidate list
-  if (mode != SEL_TOPK) bytes += 2 * kEdgeCap * sizeof(float);                   // boundary tables
-  return bytes + sizeof(SelShared);
+size_t select_lds_bytes() {
+  // arr (padded) always spans kMaxSelLen, so that strided reads need no clamping
+  return (size_t)kArrWords * sizeof(float) + 2 * kCandCap * sizeof(unsigned) + sizeof(SelShared);
 }
 
-hipError_t launch_select(int mode, int max_len, const SelArgs &a, const SeqTable &st,
-                         hipStream_t s) {
-  dim3 grid(st.batch, a.Hkv), block(kSelThreads);
-  const size_t lds = select_lds_bytes(mode, max_len) - sizeof(SelShared);
+hipError_t launch_select(const SelArgs &a, const SeqTable &st, hipStream_t s) {
+  const size_t lds = select_lds_bytes() - sizeof(SelShared);
   if (lds + sizeof(SelShared) > kLdsBytes) return hipErrorInvalidValue;
-  if (mode == SEL_CALIB) {
-    allow_lds<k_select<SEL_CALIB>>(lds);
-    hipLaunchKernelGGL((k_select<SEL_CALIB>), grid, block, lds, s, a, st);
-  } else {
-    allow_lds<k_select<SEL_TOPK>>(lds);
-    hipLaunchKernelGGL((k_select<SEL_TOPK>), grid, block, lds, s, a, st);
-  }
+  allow_lds<k_select>(lds);
+  hipLaunchKernelGGL(k_select, dim3(st.batch, a.Hkv), dim3(kSelThreads), lds, s, a, st);
   return hipGetLastError();
 }
 
@@ -3270,6 +3114,12 @@ struct ListView {
   bool fits;
 };
 
+__device__ __forceinline__ void list_boundary(const SegArgs &a, const SeqTable &st, int gs, int sg, int h, int b,
+                                              int M, int i0, int ncand, int64_t base,
+                                              const u32x4 (&hv)[kHCopies][kHPer / 4],
+                                              const float (&xb)[kSegPer], const float (&xv)[kSegPer],
+                                              SelSharedT<kSegThreads> &ss, unsigned *pre);
+
 // Calibration kernel (segment_calib).  ADAPT: it may have an allocation's
 // histogram to clear.
 template <bool ADAPT>
@@ -3470,6 +3320,19 @@ __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st
 
   // boundary bin of the top-M of B, and the segment's list of candidates at
   // or above it (key, position, V) in position order
+  list_boundary(a, st, gs, sg, h, b, M, i0, ncand, base, hv, xb, xv, ss, pre);
+}
+
+// The boundary bin of the top-M of B from the histogram bins hv, and the
+// segment's list of candidates at or above it (key, position, V) in position
+// order; xb, xv: B and V of the thread's candidates t + j*NT.
+__device__ __forceinline__ void list_boundary(const SegArgs &a, const SeqTable &st, int gs, int sg, int h, int b,
+                                              int M, int i0, int ncand, int64_t base,
+                                              const u32x4 (&hv)[kHCopies][kHPer / 4],
+                                              const float (&xb)[kSegPer], const float (&xv)[kSegPer],
+                                              SelSharedT<kSegThreads> &ss, unsigned *pre) {
+  constexpr int NT = kSegThreads, PER = kSegPer, NW = NT / 64;
+  const int t = threadIdx.x, wave = t >> 6;
   unsigned cb[kHPer];
 #pragma unroll
   for (int q = 0; q < kHPer / 4; ++q) {
@@ -3692,8 +3555,12 @@ __device__ __attribute__((noinline)) void whole_moments(const SegArgs &a, int64_
 // argument that reaches an out-of-line call costs a stack copy and spills.
 // ONE: for a launch of this job alone; the out-of-line functions take the
 // register bound of every kernel that calls them, so each bound has its own.)
-template <bool ONE>
-__device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int gs, int h, int b) {
+// SPLIT: the split calibrate's scores, S = B + lambda V over every position to
+// out_S (with pooling before calibration the candidates get pool(B) + lambda V),
+// in place of the pooled keys and their histogram.
+template <bool ONE, bool SPLIT = false>
+__device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int gs, int h, int b,
+                                              float *out_S = nullptr) {
   constexpr int NT = kSegThreads, PER = kSegPer;
   ScoreLds &lds = *reinterpret_cast<ScoreLds *>(sel_smem);
   unsigned *const hist = lds.hist, *const ckey = lds.ckey, *const pre = lds.pre;
@@ -3714,8 +3581,20 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
   // lambda pool(V)); mean of B before calibration: pooled B and V itself.
   // (The max of S reads B and V over the widened segment after lambda.)
   const bool max_s = a.pool_mode == POOL_MAX_S;
-  float pb[PER], pv[PER];
-  {
+  float pb[PER], pv[PER], wb0[SPLIT ? kSegWinJ : 1];
+  const bool mean_b = SPLIT && a.pool_mode == POOL_MEAN_B;
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int64_t o = base + min(i0 + t + j * NT, n - 1);
+      pb[j] = a.vec_B[o];
+      pv[j] = a.vec_V[o];
+    }
+    if (mean_b) {
+#pragma unroll
+      for (int j = 0; j < kSegWinJ; ++j) wb0[j] = a.vec_B[base + min(max(i0 - kPoolHalo + t + j * NT, 0), n - 1)];
+    }
+  } else {
     const float *vsrc = a.pool_mode == POOL_MEAN_B ? a.vec_V : a.vec_pV;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
@@ -3773,6 +3652,34 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
     // the moment scratch is free here (its fallback user is done)
     lam = block_lambda<NT>(s0, s1, s2, s3, M, bref_set, a.gamma, a.eps, a.b_floor,
                            lds.sums, ss, &vref_s);
+  }
+  if constexpr (SPLIT) {
+    if (sg == 0 && t == 0) {
+      a.lambda_ws[b * a.Hkv + h] = lam;
+      if (a.out_lambda) a.out_lambda[b * a.Hkv + h] = lam;
+    }
+    if (mean_b) {
+      lds_barrier();
+#pragma unroll
+      for (int j = 0; j < kSegWinJ; ++j)
+        if (t + j * NT < kSegWin) lds.sw[t + j * NT] = wb0[j];
+      lds_barrier();
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int i = i0 + t + j * NT;
+      if (i < n) {
+        float bi = pb[j];
+        if (mean_b && i < nc) {
+          const int lo = max(0, i - a.pool_half), hi = min(nc - 1, i + a.pool_half);
+          double acc = 0.0;
+          for (int u = lo; u <= hi; ++u) acc += (double)lds.sw[u - (i0 - kPoolHalo)];
+          bi = (float)(acc / (double)(hi - lo + 1));
+        }
+        out_S[base + i] = fmaf(lam, pv[j], bi);
+      }
+    }
+    return;
   }
   // the moment scratch is free: the histogram takes its place
   for (int q = 4 * t; q < kHBins; q += 4 * NT) *reinterpret_cast<uint4 *>(hist + q) = make_uint4(0u, 0u, 0u, 0u);
@@ -4651,7 +4558,7 @@ static bool wide_ok(bool bf16, int head_dim, const PassArgs &a) {
   return a.wide_split_log >= 0 && a.wide_split_log <= 2 && a.wide_cpw_log >= 0 && a.wide_cpw_log < 8 &&
          a.wide_jobs >= 1 && a.chunk == wide_keys(1 << a.wide_split_log) &&
          wide_supported(bf16, head_dim, a.Rpad, 1 << a.wide_split_log) && a.row_log == wide_row_log(a.Rpad) &&
-         a.w_magic == 65536u / (unsigned)a.W + 1u && (a.kr_sums != 0) == kr_supported(bf16, head_dim, a.Rpad);
+         a.w_magic == 65536u / (unsigned)a.W + 1u && (!a.kr_sums || kr_supported(bf16, head_dim, a.Rpad));
 }
 hipError_t launch_wide(int mode, bool bf16, int head_dim, const PassArgs &a, const SeqTable &st, hipStream_t s) {
   if (!wide_ok(bf16, head_dim, a) || (mode != PASS_LSE && mode != PASS_FUSED)) return hipErrorInvalidValue;
@@ -4714,45 +4621,125 @@ hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs
 }
 
 // ---------------------------------------------------------------- split calibrate
-// One position per thread: E from B and Q (Eq. boundary_residual), T from the
-// history, the full L over the sequence-truncated neighbourhood, history update.
-__global__ __launch_bounds__(256) void k_elem(ElemArgs a, SeqTable st) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int h = blockIdx.y;
-  if (g >= a.T) return;
-  int b = 0;
-  while (b + 1 < st.batch && st.cu[b + 1] <= g) ++b;
-  const int s0 = st.cu[b], n = st.cu[b + 1] - s0;
-  const int i = (int)(g - s0);
-  const int64_t row = (int64_t)h * a.T;
-  const int64_t pos = row + g;
-  auto resid = [&](int64_t p) {
-    const float Bv = a.in_B[p], Qv = a.in_Q[p];
-    return (Qv > Bv) ? (Qv - Bv) : 0.f;
-  };
-  const float E = resid(pos);
-  // T: the previous ring_cnt layers, oldest first
-  float ts = 0.f;
-  for (int j = a.ring_cnt; j >= 1; --j)
-    ts += a.ring[((a.ring_write - j + a.ring_slots) % a.ring_slots) * a.ring_stride + pos];
-  const float Tv = a.ring_cnt ? ts / (float)a.ring_cnt : 0.f;
-  // part of L with neighbours inside the position's chunk, as the fused pass
-  // forms it (the select kernel adds the neighbours across chunk boundaries)
-  float L = 0.f;
-  if (a.terms & 2u) {
-    const int k0 = (i / a.chunk) * a.chunk, k1 = min(n, k0 + a.chunk);
-    const int lo = max(0, i - a.radius), hi = min(n - 1, i + a.radius);
-    float s = 0.f;
-    for (int u = max(lo, k0); u <= min(hi, k1 - 1); ++u) s += resid(row + s0 + u);
-    L = s / (float)(hi - lo + 1);
+// bacon_calibrate in three launches over segments of kSegLen positions, as the
+// fused pass's selection (one workgroup per (sequence, KV head) held all its
+// positions: 55 us at any length, and an elementwise launch before it; the three
+// take 5 to 7 us each).
+//  * split_evidence: E from B and Q (Eq. boundary_residual) to the history, L over
+//    the sequence-truncated neighbourhood, T from the history, V; the B histogram.
+//  * split_lists: the boundary bin of the top-M and the segments' lists.
+//  * split_scores: lambda and S = B + lambda V (Eq. bacon_score) over every position;
+//    with pooling before calibration the candidates get pool(B) + lambda V
+//    instead, the score the top-K then ranks unpooled.
+struct EvidenceLds {
+  unsigned hist[kHBins];
+  float Es[kSegLen + 2 * kMaxRadius];
+};
+constexpr int kEvJ = (kSegLen + 2 * kMaxRadius + kSegThreads - 1) / kSegThreads;
+
+__global__ __launch_bounds__(kSegThreads) void k_split_evidence(SplitArgs p, SeqTable st) {
+  constexpr int NT = kSegThreads;
+  const SegArgs &a = p.s;
+  EvidenceLds &lds = *reinterpret_cast<EvidenceLds *>(sel_smem);
+  const int t = threadIdx.x, h = blockIdx.x, gs = blockIdx.y;
+  const int b = find_seg(st, gs), sg = gs - st.seg_base[b];
+  const int n = st.cu[b + 1] - st.cu[b], nc = n - a.W, i0 = sg * kSegLen, r = a.radius;
+  const int64_t base = (int64_t)h * a.T + st.cu[b];
+  const int w0 = i0 - kMaxRadius;
+  float bv[kEvJ], qv[kEvJ], tv[kSegPer];
+#pragma unroll
+  for (int j = 0; j < kEvJ; ++j) {
+    const int u = min(max(w0 + t + j * NT, 0), n - 1);
+    bv[j] = a.vec_B[base + u];
+    qv[j] = p.in_Q[base + u];
   }
-  a.ring[a.ring_write * a.ring_stride + pos] = E;
-  a.vec_VP[pos] = ((a.terms & 1u) ? E : 0.f) + ((a.terms & 4u) ? Tv : 0.f) + L;
+  // T: the previous layers' E, oldest first
+#pragma unroll
+  for (int j = 0; j < kSegPer; ++j) tv[j] = 0.f;
+  for (int l = a.ring_cnt; l >= 1; --l) {
+    const float *rt = a.ring + ((a.ring_slot - l + a.ring_slots) % a.ring_slots) * a.ring_stride + base;
+#pragma unroll
+    for (int j = 0; j < kSegPer; ++j) tv[j] += rt[min(i0 + t + j * NT, n - 1)];
+  }
+  for (int q = 4 * t; q < kHBins; q += 4 * NT) *reinterpret_cast<uint4 *>(lds.hist + q) = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+  for (int j = 0; j < kEvJ; ++j) {
+    const int q = t + j * NT, u = w0 + q;
+    if (q < kSegLen + 2 * kMaxRadius)
+      lds.Es[q] = u >= 0 && u < n && qv[j] > bv[j] ? qv[j] - bv[j] : 0.f;
+  }
+  lds_barrier();
+  float *ring = const_cast<float *>(a.ring) + a.ring_slot * a.ring_stride + base;
+#pragma unroll
+  for (int j = 0; j < kSegPer; ++j) {
+    const int q = t + j * NT, i = i0 + q;
+    if (i < n) {
+      const float E = lds.Es[q + kMaxRadius];
+      const float Tv = a.ring_cnt ? tv[j] / (float)a.ring_cnt : 0.f;
+      float L = 0.f;
+      if (a.terms & 2u) {
+        const int lo = max(0, i - r), hi = min(n - 1, i + r);
+        float s = 0.f;
+        for (int u = lo; u <= hi; ++u) s += lds.Es[u - w0];
+        L = s / (float)(hi - lo + 1);
+      }
+      const float V = ((a.terms & 1u) ? E : 0.f) + ((a.terms & 4u) ? Tv : 0.f) + L;
+      ring[i] = E;
+      a.vec_V[base + i] = V;
+      if (p.out_E) p.out_E[base + i] = E;
+      if (p.out_V) p.out_V[base + i] = V;
+      if (i < nc) atomicAdd(&lds.hist[hbin(float_key(a.vec_B[base + i]))], 1u);
+    }
+  }
+  lds_barrier();
+  unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+  for (int q = t; q < kHBins; q += NT) {
+    const unsigned c = lds.hist[q];
+    if (c) atomicAdd(&gh[q], c);
+  }
 }
 
-hipError_t launch_elem(const ElemArgs &a, const SeqTable &st, hipStream_t s) {
-  dim3 grid((unsigned)((a.T + 255) / 256), a.Hkv), block(256);
-  hipLaunchKernelGGL(k_elem, grid, block, 0, s, a, st);
+__global__ __launch_bounds__(kSegThreads) void k_split_lists(SplitArgs p, SeqTable st) {
+  constexpr int NT = kSegThreads;
+  const SegArgs &a = p.s;
+  CandLds &lds = *reinterpret_cast<CandLds *>(sel_smem);
+  const int t = threadIdx.x, h = blockIdx.x, gs = blockIdx.y;
+  const int b = find_seg(st, gs), sg = gs - st.seg_base[b];
+  const int n = st.cu[b + 1] - st.cu[b], nc = n - a.W, i0 = sg * kSegLen;
+  const int ncand = max(0, min(i0 + kSegLen, nc) - i0);
+  const int64_t base = (int64_t)h * a.T + st.cu[b];
+  const int M = max(0, min(scale_set_size(a.rho, sel_head_budget(st, a.hb, a.Hkv, b, h, a.sb)), nc));
+  if (M <= 0 || !a.use_last_query) return;
+  u32x4 hv[kHCopies][kHPer / 4];
+  const unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+#pragma unroll
+  for (int c = 0; c < kHCopies; ++c)
+#pragma unroll
+    for (int q = 0; q < kHPer / 4; ++q)
+      hv[c][q] = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHBins + kHPer * t)[q];
+  float xb[kSegPer], xv[kSegPer];
+#pragma unroll
+  for (int j = 0; j < kSegPer; ++j) {
+    const int64_t o = base + i0 + min(t + j * NT, max(ncand - 1, 0));
+    xb[j] = a.vec_B[o];
+    xv[j] = a.vec_V[o];
+  }
+  list_boundary(a, st, gs, sg, h, b, M, i0, ncand, base, hv, xb, xv, lds.ss, lds.pre);
+}
+
+__global__ __launch_bounds__(kSegThreads) void k_split_scores(SegArgs a, float *out_S, SeqTable st) {
+  segscore_body<true, true>(a, st, blockIdx.y, blockIdx.x, find_seg(st, blockIdx.y), out_S);
+}
+
+hipError_t launch_split(int stage, const SplitArgs &p, const SeqTable &st, hipStream_t s) {
+  const dim3 grid(p.s.Hkv, st.total_segs), block(kSegThreads);
+  if (stage == 0) {
+    hipLaunchKernelGGL(k_split_evidence, grid, block, sizeof(EvidenceLds), s, p, st);
+  } else if (stage == 1) {
+    hipLaunchKernelGGL(k_split_lists, grid, block, sizeof(CandLds), s, p, st);
+  } else {
+    hipLaunchKernelGGL(k_split_scores, grid, block, sizeof(ScoreLds), s, p.s, p.out_S, st);
+  }
   return hipGetLastError();
 }
 

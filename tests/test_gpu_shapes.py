@@ -135,3 +135,15 @@ def test_allocation(hkv, lens, budgets, values, alpha):
     want = _budgets_by_counting(B, wl.cu_seqlens, wl.window, wl.budgets, wl.pool_kernel // 2, alpha)
     assert np.array_equal(got, again)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("lens,budgets,kw", [
+    ((33, 2048, 2081), (4, 300, 90), {}),                       # one candidate; a segment and a window past it
+    ((4097, 700), (1500, 40), {"pool_mode": 2}),                # pooling before calibration over a segment's edge
+    ((6300,), (3100,), {}),                                     # lists beyond one workgroup: every position
+])
+def test_split_segments(lens, budgets, kw):
+    """The split calls over several segments against the oracle (scores, V and
+    lambda of every position, the kept sets)."""
+    wl = _wl(6, 4, 2, 64, 32, 7, "bf16", lens, budgets)
+    TP.run_case("split-segments", wl, gpu_kw=kw, orc_kw=dict(kw), fused=False)
