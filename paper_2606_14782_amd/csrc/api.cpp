@@ -476,6 +476,9 @@ bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) 
   int64_t segs = 0;
   for (int b = 0; b < bt->batch; ++b) segs += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + kSegLen - 1) / kSegLen;
   const double sel = (double)(3 * segs + bt->batch) * hkv;
+  // (more than 128 rows of fp32: a layer call of 13404 and 2013 tokens, 14/2 heads,
+  // takes 111 us a layer here and 89 with the streaming passes)
+  if (!bf16 && nrt > 4) return false;
   double best = 1e30;
   for (int s = 1; s <= 4; s *= 2) {
     if (!wide_supported(bf16, c->shape.head_dim, c->L.rpad, s)) continue;
@@ -493,7 +496,15 @@ bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) 
         jobs += ((bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s) + p - 1) / p;
       const double t = 6.0 + 2.2 * (p - 1) + p * tile * std::max((double)nrt / s, 0.25 * ((nrt + s - 1) / s));
       const double n = 2.0 * jobs * hkv + sel, cus = c->cus > 0 ? c->cus : 256;
-      const double est = n <= cus ? std::max(t, 8.0) : (2.0 * jobs * hkv * t + sel * 8.0) / cus + 0.5 * t;
+      // A pass of a layer call, one chunk per workgroup, counts too: the two kinds
+      // of call share the split, so that they give the same bits.  It weighs more
+      // beyond 128 rows, where one row group leaves a layer call well behind the
+      // streaming passes (28/4 heads, 8K tokens, 12 layers: prompt 280 and layer
+      // calls 742 us with one, 300 and 660 with two; 472 and 629 before).
+      const double layer_weight = nrt > 4 ? 1.3 : 0.5;
+      const double t1 = t - (p - 1) * (t - 3.8) / 2, n1 = (double)blocks * hkv;
+      const double est = (n <= cus ? std::max(t, 8.0) : (2.0 * jobs * hkv * t + sel * 8.0) / cus + 0.5 * t) +
+                         layer_weight * (n1 <= cus ? t1 : n1 * t1 / cus + 0.5 * t1);
       if (est < best) {
         best = est;
         *split = s;
@@ -843,10 +854,13 @@ struct LayerRun {
 // Checks one layer's arguments and builds its launch arguments; enqueues
 // nothing.  The layer order is the caller's to check.  Buffers that later
 // layers may write while this layer's select is still in flight come in
-// copies that the layers take in turn.
+// copies that the layers take in turn: as few as the schedule needs, so that
+// they stay in the caches (histograms four layers old, with the keys of four
+// layers read since, cost an fp32 layer call of 36569 tokens 5 us in pass 2's
+// atomics), and the first alone in a layer call, which leaves none in use.
 bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const void *d_q_win,
                         const void *d_k, const void *d_v, const float *d_lse, int32_t *d_idx,
-                        void *d_k_out, void *d_v_out, LayerRun &r) {
+                        void *d_k_out, void *d_v_out, LayerRun &r, bool alone) {
   TRY(check_batch(c, bt));
   TRY(check_prompt_batch(c, bt));
   if (layer >= c->shape.num_layers)
@@ -918,14 +932,16 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   }
   if (final_lds_bytes(r.kmax, c->shape.window) > (size_t)kLdsBytes)
     return fail(BACON_ERR_UNSUPPORTED, "budget %d needs more LDS than a CU has", r.kmax);
-  const size_t c2 = layer % kCopies2, cS = layer % kCopiesS;
+  const int turn = alone ? 0 : layer;
+  const size_t c2 = turn % kCopies2, cS = turn % kCopiesS;
+  const int fewer = r.wide ? 0 : 1;   // no launch between the K passes and the calibration
   const int64_t T = bt->cu_seqlens[bt->batch];
   PassArgs &a = r.a;
   a = pass_args(c, r.st, r.chunk, d_q_win, d_k);
   a.T = T;
   a.lse_in = d_lse;
-  a.hist_B += layer % c->L.copies_hist_b * c->L.hist_b_stride / sizeof(unsigned);
-  a.vec_B += layer % c->L.copies_b * c->L.vec_stride / sizeof(float);
+  a.hist_B += turn % (c->L.copies_hist_b - fewer) * c->L.hist_b_stride / sizeof(unsigned);
+  a.vec_B += turn % (c->L.copies_b - fewer) * c->L.vec_stride / sizeof(float);
   a.partials += c2 * c->L.part_stride / sizeof(float2);
   a.lse2 += c2 * c->L.lse_stride / sizeof(float);
   a.kr_sums = kr_shape;
@@ -980,7 +996,7 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   g.row_bytes = c->shape.head_dim * (r.bf16 ? 2 : 4);
   g.flat_heads = r.adaptive;
   if (r.adaptive) {
-    r.al = alloc_args(c, T, layer);
+    r.al = alloc_args(c, T, turn);
     r.al.vec_B = a.vec_B;
     r.al.out = c->alloc_out ? c->alloc_out + (size_t)layer * c->shape.max_batch * c->shape.num_kv_heads : nullptr;
     g.hist_A = r.al.hist_A;
@@ -1145,7 +1161,7 @@ bacon_status compress(bacon_ctx *c, int32_t layer, const bacon_batch *bt, const 
   if (layer != c->next_layer)
     return fail(BACON_ERR_ORDER, "layer %d given, layer %d expected next", layer, c->next_layer);
   LayerRun r;
-  TRY(plan_layer(c, layer, bt, d_q_win, d_k, d_v, d_lse, d_idx, d_k_out, d_v_out, r));
+  TRY(plan_layer(c, layer, bt, d_q_win, d_k, d_v, d_lse, d_idx, d_k_out, d_v_out, r, true));
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (!r.adaptive) TRY(head_table(c, bt, s, &r.g.hb, layer % kCopiesTab));
   TRY(stage_pass(c, r, false, nullptr, s));
@@ -1214,7 +1230,7 @@ bacon_status bacon_compress_prompt(bacon_ctx *c, const bacon_batch *bt, int32_t 
   std::vector<LayerRun> runs(num_layers);
   for (int i = 0; i < num_layers; ++i)
     TRY(plan_layer(c, first_layer + i, lbt(i), d_q_win[i], d_k[i], d_v[i],
-                   d_lse ? d_lse[i] : nullptr, d_idx[i], d_k_out[i], d_v_out[i], runs[i]));
+                   d_lse ? d_lse[i] : nullptr, d_idx[i], d_k_out[i], d_v_out[i], runs[i], false));
   hipStream_t s = static_cast<hipStream_t>(stream);
   // Layers in flight at once.  Small grids: one launch per layer holds pass 1
   // of layer i, pass 2 of layer i - 1 (which merges the normalisers), and the

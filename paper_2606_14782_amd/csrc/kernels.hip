@@ -4381,7 +4381,7 @@ __global__ __launch_bounds__(kSegThreads) void k_alloc(AllocArgs a, SeqTable st)
 }
 template <int JOB>
 __global__ __launch_bounds__(kSegThreads) void k_sel_one(SegArgs a, SeqTable st) {
-  const int h = blockIdx.x, x = blockIdx.y;
+  const int h = blockIdx.y, x = blockIdx.x;
   if constexpr (JOB == JOB_SCORE) segscore_body<true>(a, st, x, h, find_seg(st, x));
   else if constexpr (JOB == JOB_FINAL) final_body<true>(a, st, x % a.parts, x / a.parts, h);
   else if constexpr (JOB == JOB_CAL) segcal_body<true>(a, st, x, h, find_seg(st, x));
@@ -4425,7 +4425,7 @@ size_t final_lds_bytes(int max_budget, int window) {
 template <int JOB>
 static hipError_t launch_sel_one(const SegArgs &a, const SeqTable &st, int jobs, size_t lds, hipStream_t s) {
   allow_lds<k_sel_one<JOB>>(lds);
-  hipLaunchKernelGGL(k_sel_one<JOB>, dim3(a.Hkv, jobs), dim3(kSegThreads), lds, s, a, st);
+  hipLaunchKernelGGL(k_sel_one<JOB>, dim3(jobs, a.Hkv), dim3(kSegThreads), lds, s, a, st);
   return hipGetLastError();
 }
 
