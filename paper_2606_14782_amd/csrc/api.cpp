@@ -12,6 +12,7 @@
 
 #include "../../include/bacon.h"
 #include "internal.h"
+#include "schedule.h"
 
 using namespace bacon;
 
@@ -43,32 +44,9 @@ struct Layout {
   size_t vec_stride, hist_b_stride, hist_s_stride, list_stride, cnt_stride, rec_stride, hb_stride, sb_stride,
       part_stride, lse_stride, hist_a_stride;
   size_t vec_a, hist_a, list_a, cnt_a, rec_a;   // head-wise allocation
-  int copies_b, copies_hist_b;
   int rpad, slots;
   int64_t chunks_cap;
 };
-
-// Copies of the buffers that pass between the stages of a layer.  In a prompt
-// call one launch holds stages of up to seven layers (pass 1 of layer l, its
-// normaliser merge a launch later, then pass 2, calibration, scores, candidate
-// lists, final job), so a layer's buffer is free again
-//  * two launches after it was written where only the next stage reads it
-//    (partials, normalisers, V and the pooled vectors, the lists, their counts
-//    and records): two copies;
-//  * after the scores, two stages on (B): three;
-//  * after the candidate job, three stages on, which clears the B histogram
-//    for the layer that counts into its copy next: four;
-//  * after the final job (the S keys and histogram, cleared by the
-//    calibration, which its whole-sequence path reads): four;
-//  * the budget tables, written before the layer's first launch and read until
-//    its last: eight.
-// The E history has a slot more than the layers a persistence term reads and
-// the one in flight.  The head-wise allocation puts three stages between pass 2
-// and the calibration, and B, its histogram and the E history three more
-// copies; its own pooled scores are read two stages on (three copies), its
-// histogram cleared three on (four).
-constexpr int kCopies2 = 2, kCopiesB = 3, kCopiesHistB = 4, kCopiesS = 4, kCopiesTab = 8;
-constexpr int kAllocLag = 3, kCopiesA = 3, kCopiesHistA = 4;
 
 bacon_status check_shape(const bacon_shape *s) {
   if (!s) return fail(BACON_ERR_INVALID, "shape is NULL");
@@ -121,20 +99,15 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   Layout L{};
   const int G = s->num_q_heads / s->num_kv_heads;
   L.rpad = ((G * s->window + 31) / 32) * 32;
-  // E history: m + 2 slot vectors, so the slots that a layer and the next one
-  // write are never one of the m its persistence term reads
   const bool adaptive = p->head_alloc == BACON_ALLOC_ADAPTIVE;
-  const int lag = adaptive ? kAllocLag : 0;
-  L.copies_b = kCopiesB + lag;
-  L.copies_hist_b = kCopiesHistB + lag;
-  L.slots = p->persist_m + 2 + lag;
+  L.slots = history_slots(p->persist_m, adaptive);
   const int tk = 32 * std::min(L.rpad / 32, 4);
   L.chunks_cap = (s->max_total_tokens + tk - 1) / tk + s->max_batch;
   const size_t vec = (size_t)s->num_kv_heads * (size_t)s->max_total_tokens * sizeof(float);
   size_t off = 0;
   L.vec_stride = align256(vec);
   L.ring = off;     off += align256((size_t)L.slots * vec);
-  L.vec_b = off;    off += L.copies_b * L.vec_stride;
+  L.vec_b = off;    off += copies_b(true, adaptive) * L.vec_stride;
   L.vec_v = off;    off += kCopies2 * L.vec_stride;
   L.vec_pb = off;   off += kCopies2 * L.vec_stride;
   L.vec_pv = off;   off += kCopies2 * L.vec_stride;
@@ -142,7 +115,7 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   const size_t hist = (size_t)s->max_batch * s->num_kv_heads * kHBins * sizeof(unsigned);
   L.hist_b_stride = align256(hist * kHCopies);
   L.hist_s_stride = align256(hist);
-  L.hist_b = off;   off += L.copies_hist_b * L.hist_b_stride;
+  L.hist_b = off;   off += copies_hist_b(true, adaptive) * L.hist_b_stride;
   // the allocation's histograms: cleared with them where a prompt uses them
   // (bacon_allocate_heads clears its own copy)
   L.hist_a_stride = align256((size_t)s->max_batch * s->num_kv_heads * alloc_hist_words() * sizeof(unsigned));
@@ -934,14 +907,13 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
     return fail(BACON_ERR_UNSUPPORTED, "budget %d needs more LDS than a CU has", r.kmax);
   const int turn = alone ? 0 : layer;
   const size_t c2 = turn % kCopies2, cS = turn % kCopiesS;
-  const int fewer = r.wide ? 0 : 1;   // no launch between the K passes and the calibration
   const int64_t T = bt->cu_seqlens[bt->batch];
   PassArgs &a = r.a;
   a = pass_args(c, r.st, r.chunk, d_q_win, d_k);
   a.T = T;
   a.lse_in = d_lse;
-  a.hist_B += turn % (c->L.copies_hist_b - fewer) * c->L.hist_b_stride / sizeof(unsigned);
-  a.vec_B += turn % (c->L.copies_b - fewer) * c->L.vec_stride / sizeof(float);
+  a.hist_B += turn % copies_hist_b(r.wide, r.adaptive) * c->L.hist_b_stride / sizeof(unsigned);
+  a.vec_B += turn % copies_b(r.wide, r.adaptive) * c->L.vec_stride / sizeof(float);
   a.partials += c2 * c->L.part_stride / sizeof(float2);
   a.lse2 += c2 * c->L.lse_stride / sizeof(float);
   a.kr_sums = kr_shape;
@@ -1242,10 +1214,9 @@ bacon_status bacon_compress_prompt(bacon_ctx *c, const bacon_batch *bt, int32_t 
   // launches have no K pass.
   auto at = [&](int i) -> const LayerRun * { return i >= 0 && i < num_layers ? &runs[i] : nullptr; };
   const bool wide = runs[0].wide, adaptive = runs[0].adaptive;   // (the layers share the sequences)
-  const int lag2 = wide && !runs[0].lse ? 1 : 0;                 // pass 2
-  const int lagc = lag2 + (wide ? 1 : 0) + (adaptive ? kAllocLag : 0);   // calibration
+  const Lags lag = stage_lags(wide, runs[0].lse != nullptr, adaptive);
   bool merged = false;
-  for (int i = 0; i < num_layers + lagc + 3; ++i) {
+  for (int i = 0; i < num_layers + lag.fin; ++i) {
     Stages g;
     if (i < num_layers) {
       LayerRun &r = runs[i];
@@ -1262,20 +1233,20 @@ bacon_status bacon_compress_prompt(bacon_ctx *c, const bacon_batch *bt, int32_t 
       }
     }
     if (wide) {
-      if (lag2) g.p1 = at(i);
-      g.p2 = at(i - lag2);
+      if (!runs[0].lse) g.p1 = at(i - lag.p1);
+      g.p2 = at(i - lag.p2);
     }
     if (adaptive) {
-      g.pool = at(i - lagc + 3);
-      g.list = at(i - lagc + 2);
-      g.pick = at(i - lagc + 1);
+      g.pool = at(i - lag.pool);
+      g.list = at(i - lag.list);
+      g.pick = at(i - lag.pick);
     }
-    g.cal = at(i - lagc);
-    g.score = at(i - lagc - 1);
-    g.cand = at(i - lagc - 2);
-    g.fin = at(i - lagc - 3);
+    g.cal = at(i - lag.cal);
+    g.score = at(i - lag.score);
+    g.cand = at(i - lag.cand);
+    g.fin = at(i - lag.fin);
     TRY(wide ? stage_mega(c, g, s) : stage_select(c, g, s));
-    if (g.score) TRY(stage_capture(c, *g.score, lbt(i - lagc - 1), s));
+    if (g.score) TRY(stage_capture(c, *g.score, lbt(i - lag.score), s));
   }
   return BACON_OK;
 }

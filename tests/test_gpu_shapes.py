@@ -71,6 +71,43 @@ def test_small_grids(hq, hkv, d, window, dtype, lens, wide, monkeypatch):
             assert torch.equal(x, y), f"layer {l}"
 
 
+@pytest.mark.parametrize("adaptive", [True, False])
+@pytest.mark.parametrize("wide", [True, False])
+@pytest.mark.parametrize("lse", [False, True])
+def test_prompt_longer_than_its_schedule(adaptive, wide, lse, monkeypatch):
+    """More layers than the prompt call keeps in flight, so that every buffer's
+    copies come round, with budgets that change every layer (per sequence
+    under the adaptive allocation, else per head): equal to the per-layer
+    calls bit for bit."""
+    import numpy as np
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    if not wide:
+        monkeypatch.setenv("BACON_WIDE", "0")
+    L = 20
+    wl = _wl(L, 4, 2, 64, 16, 5, "bf16", (700, 2100, 290), (20, 60, 9))
+    rng = np.random.default_rng(9)
+    sched = [(10 + 4 * l, 30 + 7 * l, 5 + 3 * ((l * 7) % L)) for l in range(L)]
+    batches = [bacon.BatchLayout(wl.cu_seqlens, np.asarray(s, np.int32), head_budgets=None if adaptive else
+                                 rng.integers(1, 90, (wl.batch, wl.num_kv_heads)).astype(np.int32)) for s in sched]
+    xs = [inputs.layer_inputs(wl, l) for l in range(L)]
+    qs, ks, vs = ([P.to_dev(x[n], wl) for x in xs] for n in ("q_win", "k", "v"))
+    prm = P.params_for(wl, head_alloc=bacon.ALLOC_ADAPTIVE if adaptive else bacon.ALLOC_GIVEN, alloc_floor=0.2)
+    a, b = P.make_ctx(wl, prm), P.make_ctx(wl, prm)
+    lses = [a.bacon_window_lse(batches[0], q, k) for q, k in zip(qs, ks)] if lse else None
+    a.bacon_begin_prompt(batches[0])
+    want = [a.bacon_compress_layer_lse(l, batches[l], qs[l], ks[l], vs[l], lses[l]) if lse else
+            a.bacon_compress_layer(l, batches[l], qs[l], ks[l], vs[l]) for l in range(L)]
+    b.bacon_begin_prompt(batches[0])
+    got = b.bacon_compress_prompt(0, batches[0], qs, ks, vs, lses=lses, layer_batches=batches)
+    torch.cuda.synchronize()
+    for l in range(L):
+        for x, y in zip(got[l], want[l]):
+            assert torch.equal(x, y), f"layer {l}"
+    assert a.bacon_debug_device_errors() == 0 and b.bacon_debug_device_errors() == 0
+
+
 def _budgets_by_counting(B, cu, W, budgets, half, alpha):
     """The adaptive allocation's budgets by sorting the pooled scores, pooled
     in float32 in position order as the GPU does."""
