@@ -2559,7 +2559,8 @@ __device__ __forceinline__ void block_select(KeyF key, int k, unsigned &xk, int 
 
 // Exact top-k threshold with the tie rule (key descending, then position
 // ascending) over the block's non-zero keys, 1 <= k <= count: element j is
-// kept iff key > xk, or key == xk and position <= pthr.
+// kept iff key > xk, or key == xk and position <= pthr, and pthr is the
+// position of the last element kept at xk (callers read by it).
 // One histogram pass bins every key over [max(min, max - 8 octaves), max];
 // the boundary bin is compacted into an LDS list (ckey, cpos) in a fixed
 // order (ballots, no atomics).  A list of at most NT entries is resolved by
@@ -2615,7 +2616,11 @@ __device__ __forceinline__ void block_threshold(KeyF key, PosF pos, int k, unsig
 #pragma unroll
     for (int j = 0; j < PER; ++j) eq += key(j) == xk;
     if (block_reduce_u<2>(eq, ss) == (unsigned)nd) {
-      pthr = 0x7fffffff;
+      // every key equal to xk is kept: the position of the last
+      unsigned last = 0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) last = key(j) == xk ? max(last, (unsigned)pos(j)) : last;
+      pthr = (int)block_reduce_u<1>(last, ss);
     } else {
       auto pkey = [&](int j) -> unsigned { return key(j) == xk ? 0xffffffffu - (unsigned)pos(j) : 0u; };
       unsigned xp;
@@ -2658,7 +2663,9 @@ __device__ __forceinline__ void block_threshold(KeyF key, PosF pos, int k, unsig
   }
   xk = blo + pre;
   if (E == (unsigned)need) {
-    pthr = 0x7fffffff;
+    unsigned last = 0;
+    for (int q = t; q < (int)C; q += NT) last = ckey[q] == xk ? max(last, (unsigned)cpos[q]) : last;
+    pthr = (int)block_reduce_u<1>(last, ss);
     return;
   }
   // the `need` lowest positions among the E ties (positions < 2^15)

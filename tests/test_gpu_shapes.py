@@ -184,3 +184,47 @@ def test_split_segments(lens, budgets, kw):
     lambda of every position, the kept sets)."""
     wl = _wl(6, 4, 2, 64, 32, 7, "bf16", lens, budgets)
     TP.run_case("split-segments", wl, gpu_kw=kw, orc_kw=dict(kw), fused=False)
+
+
+@pytest.mark.parametrize("wide", [True, False])
+@pytest.mark.parametrize("window,dtype", [(32, "bf16"), (8, "fp32")])
+def test_boundary_far_below_the_maximum(window, dtype, wide, monkeypatch):
+    """A sink that takes nearly all attention and thousands of positions within
+    a few per cent of each other, 17 octaves below it: the boundary bin of B
+    overflows the lists and lies below the octaves that the whole-sequence
+    threshold bins first.  Lambda against the set and the moments (float64) of
+    the call's own B and V."""
+    import numpy as np
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    if not wide:
+        monkeypatch.setenv("BACON_WIDE", "0")
+    wl = _wl(2, 4, 2, 64, window, 5, dtype, (6300, 3100), (1300, 700))
+    batch = bacon.BatchLayout(wl.cu_seqlens, wl.budgets_arr)
+    d, T, H = wl.head_dim, wl.total_tokens, wl.num_kv_heads
+    ctx = P.make_ctx(wl)
+    cap = [torch.zeros(s, device="cuda") for s in ((2, H, T), (2, H, T), (2, 2, H))]
+    ctx.bacon_debug_capture(*cap)
+    ctx.bacon_begin_prompt(batch)
+    for layer in range(2):
+        rng = np.random.default_rng(layer)
+        u = rng.standard_normal(d).astype(np.float32)
+        u /= np.linalg.norm(u)
+        q = 4 * u + 0.05 * rng.standard_normal((wl.batch * window, wl.num_q_heads, d)).astype(np.float32)
+        k = 0.01 * rng.standard_normal((T, H, d)).astype(np.float32)
+        for b in range(wl.batch):
+            k[wl.cu_seqlens[b]] = 3.2 * np.sqrt(d) * u          # logit 12.8 against 0
+        q, k = (P.to_dev(inputs.round_bf16(x), wl) for x in (q, k))
+        ctx.bacon_compress_layer(layer, batch, q, k, k)
+    torch.cuda.synchronize()
+    B, V, lam = (x.cpu().numpy().astype(np.float64) for x in cap)
+    for layer in range(2):
+        for b, (s0, s1) in enumerate(P.seq_slices(wl)):
+            nc = s1 - s0 - window
+            for h in range(H):
+                bb, vv = B[layer, h, s0:s0 + nc], V[layer, h, s0:s0 + nc]
+                m = np.lexsort((np.arange(nc), -bb))[:2 * wl.budgets[b]]
+                want = bb[m].std() / (vv[m].std() + 1e-12)
+                # moments in double of the same float32 values, lambda rounded to float32
+                assert abs(lam[layer, b, h] - want) <= 1e-6 * want, (layer, b, h)
