@@ -2976,8 +2976,10 @@ __device__ __forceinline__ void load_bins(const unsigned *gh, unsigned *cb) {
 // Exact top-k threshold (xk, pthr) of the keys key(j), j < PER, of the block
 // (0 = not a candidate) from the histogram gh of those keys: element j is
 // kept iff key > xk, or key == xk and position <= pthr.  1 <= k <= count.
-// Ends with a barrier.
-template <int PER, int COPIES, typename KeyF, typename PosF>
+// SIGNED: the keys of negative values may be among them; they share bin 0,
+// whose keys then agree in no bits, and a boundary there is searched over the
+// whole keys.  Ends with a barrier.
+template <int PER, int COPIES, bool SIGNED, typename KeyF, typename PosF>
 __device__ __forceinline__ void hist_threshold(const unsigned *gh, KeyF key, PosF pos, int k,
                                                unsigned &xk, int &pthr,
                                                SelSharedT<kSegThreads> &ss, unsigned *ckey,
@@ -2990,7 +2992,7 @@ __device__ __forceinline__ void hist_threshold(const unsigned *gh, KeyF key, Pos
   const int need = k - ss.bc_i[1];
   const unsigned C = ss.bc_u[2];
   lds_barrier();
-  if (C <= (unsigned)kCandCap) {
+  if (C <= (unsigned)kCandCap && !(SIGNED && beta == 0)) {
     compact_ballot<PER, NT>([&](int j) { const unsigned x = key(j); return x != 0u && hbin(x) == beta; },
                             key, pos, ckey, cpos, ss);
     rank_pick_bin<NT>((int)C, need, ckey, cpos, ss, xk, pthr);
@@ -3508,7 +3510,7 @@ __device__ __forceinline__ void whole_topk_stream(const SegArgs &a, int64_t base
 // candidates in registers, the exact threshold over them; V is read for the
 // members only.  Kept out of line so that its registers do not weigh on the
 // list path of the calling kernel.
-template <bool ONE>
+template <bool ONE, bool SIGNED>
 __device__ __attribute__((noinline)) void whole_moments(const SegArgs &a, int64_t base, int nc, int M,
                                                          const unsigned *gh, SelSharedT<kSegThreads> &ss,
                                                          unsigned *ckey, int *cpos, unsigned *pre,
@@ -3526,7 +3528,7 @@ __device__ __attribute__((noinline)) void whole_moments(const SegArgs &a, int64_
   auto posf = [&](int j) -> int { return t + j * NT; };
   unsigned xm;
   int pm;
-  hist_threshold<kAllPer, kHCopies>(gh, keyB, posf, M, xm, pm, ss, ckey, cpos);
+  hist_threshold<kAllPer, kHCopies, SIGNED>(gh, keyB, posf, M, xm, pm, ss, ckey, cpos);
   uint32_t msk = 0;
 #pragma unroll
   for (int j = 0; j < kAllPer; ++j) {
@@ -3564,7 +3566,7 @@ __device__ __attribute__((noinline)) void whole_moments(const SegArgs &a, int64_
 // register bound of every kernel that calls them, so each bound has its own.)
 // SPLIT: the split calibrate's scores, S = B + lambda V over every position to
 // out_S (with pooling before calibration the candidates get pool(B) + lambda V),
-// in place of the pooled keys and their histogram.
+// in place of the pooled keys and their histogram; its B may be negative.
 template <bool ONE, bool SPLIT = false>
 __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int gs, int h, int b,
                                               float *out_S = nullptr) {
@@ -3623,7 +3625,9 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
     load_lists<true>(st, b, base, n, h, a.recB + b * a.Hkv + h, a.listB_key, a.listB_pos, a.listB_v,
                      a.cntB, scnt, L, rec, lk, lp, lv);
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0, bref_set = 0.0;
-    if (L.fits && rec.w <= kSegCandCap) {
+    // (the split call takes any B: the keys of negative values share bin 0, and
+    // rank_pick_bin's narrowing is for keys that agree above bit 17)
+    if (L.fits && rec.w <= kSegCandCap && !(SPLIT && rec.x == 0)) {
       // the boundary bin's entries, ranked under the tie rule
       compact_ballot<kListPer, NT, kSegCandCap>([&](int j) { return lk[j] != 0u && hbin(lk[j]) == rec.x; },
                                    [&](int j) { return lk[j]; }, [&](int j) { return lp[j]; },
@@ -3652,7 +3656,7 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
       if (nc > kAllPer * kSegThreads)
         whole_moments_stream(a, base, nc, M, a.hist_B + hrow * kHCopies, ss, part);
       else
-        whole_moments<ONE>(a, base, nc, M, a.hist_B + hrow * kHCopies, ss, ckey, cpos, pre, lds.mom, part);
+        whole_moments<ONE, SPLIT>(a, base, nc, M, a.hist_B + hrow * kHCopies, ss, ckey, cpos, pre, lds.mom, part);
       s0 = part[0]; s1 = part[1]; s2 = part[2]; s3 = part[3];
       bref_set = part[4];
     }
@@ -3823,7 +3827,7 @@ __device__ __attribute__((noinline)) void whole_topk(const SegArgs &a, int64_t b
   auto posf = [&](int j) -> int { return t + j * NT; };
   unsigned xk;
   int pk;
-  hist_threshold<kAllPer, 1>(gh, keyS, posf, kept, xk, pk,
+  hist_threshold<kAllPer, 1, false>(gh, keyS, posf, kept, xk, pk,
                           ss, ckey, cpos);
   uint32_t msk = 0;
 #pragma unroll

@@ -228,3 +228,63 @@ def test_boundary_far_below_the_maximum(window, dtype, wide, monkeypatch):
                 want = bb[m].std() / (vv[m].std() + 1e-12)
                 # moments in double of the same float32 values, lambda rounded to float32
                 assert abs(lam[layer, b, h] - want) <= 1e-6 * want, (layer, b, h)
+
+
+def _calibrate64(B, Q, cu, W, budgets, radius, rho, pool_half, pool_mode):
+    """First-layer calibration of any B and Q in float64: S, lambda, E, V.  The
+    scale-matching set is taken from the float32 B (score descending, position
+    ascending); V enters lambda as the float32 the GPU keeps."""
+    import numpy as np
+    H, T = B.shape
+    E = np.maximum(Q - B, 0).astype(np.float32).astype(np.float64)
+    S, V, lam = np.zeros((H, T)), np.zeros((H, T)), np.zeros((len(budgets), H))
+
+    def box(x, r):
+        c = np.concatenate([[0.0], np.cumsum(x)])
+        i = np.arange(len(x))
+        lo, hi = np.maximum(0, i - r), np.minimum(len(x), i + r + 1)
+        return (c[hi] - c[lo]) / (hi - lo)
+    for b, K in enumerate(budgets):
+        sl, nc = slice(cu[b], cu[b + 1]), cu[b + 1] - cu[b] - W
+        for h in range(H):
+            bb = B[h, sl].astype(np.float64)
+            v = E[h, sl] + box(E[h, sl], radius)
+            M = min(int(rho * K), nc)
+            m = np.lexsort((np.arange(nc), -bb[:nc]))[:M]
+            lam[b, h] = bb[m].std() / (v[m].std() + 1e-12)
+            if pool_mode == 2:
+                bb[:nc] = box(bb[:nc], pool_half)
+            V[h, sl], S[h, sl] = v, bb + lam[b, h] * v
+    return S, lam, E, V
+
+
+@pytest.mark.parametrize("lens,budgets,keep", [
+    ((1500, 33), (400, 9), 100),           # the boundary among 1368 negative entries, on the lists
+    ((2300,), (150,), 200),                # lists over two segments
+    ((5000,), (2150,), 4200),              # lists beyond one workgroup: 768 negative entries
+    ((6000, 4500), (2500, 1000), 300),     # thousands of them
+])
+def test_calibrate_on_signed_scores(lens, budgets, keep):
+    """bacon_calibrate takes any B: negative values, which share the lowest bin of
+    the histogram, are ranked over their whole keys (ties by position)."""
+    import numpy as np
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    wl = _wl(1, 2, 2, 64, 32, 5, "bf16", lens, budgets)
+    rng = np.random.default_rng(len(lens) + keep)
+    B = -np.exp(rng.uniform(np.log(1e-3), np.log(30.0), (2, wl.total_tokens))).astype(np.float32)
+    B[:, ::7] = np.round(B[:, ::7] * 8) / 8            # ties
+    for b, n in enumerate(lens):
+        pos = rng.permutation(n - wl.window)[:keep]
+        B[:, wl.cu_seqlens[b] + pos] *= -1
+    Q = (B + rng.standard_normal(B.shape) * 0.2).astype(np.float32)
+    batch = bacon.BatchLayout(wl.cu_seqlens, wl.budgets_arr)
+    ctx = P.make_ctx(wl)
+    ctx.bacon_begin_prompt(batch)
+    got = ctx.bacon_calibrate(0, batch, torch.from_numpy(B).cuda(), torch.from_numpy(Q).cuda(), True, True)
+    want = _calibrate64(B, Q, wl.cu_seqlens, wl.window, budgets, 5, 2.0, 2, 0)
+    for name, w in zip(("S", "lambda", "E", "V"), want):
+        # float32 V (a sum of 11 and two more terms): below 1e-6 of its values
+        g = got[name].cpu().numpy()
+        assert np.abs(g - w).max() <= 1e-5 * np.abs(w).max(), name
