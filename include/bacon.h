@@ -197,6 +197,7 @@ bacon_status bacon_score(bacon_ctx *ctx, int32_t layer, const bacon_batch *batch
 
 /* Calibration of one layer (Eqs. boundary_residual .. bacon_score): from B and
  * Q writes S [Hkv, T] and lambda [B, Hkv]; E and V [Hkv, T] when not NULL.
+ * S, E and V may be written over B and Q (of any finite values).
  * Appends E to the prompt's history, so `layer` must be the next layer of the
  * prompt (0, 1, 2, ...) counting calibrate and compress_layer calls. */
 bacon_status bacon_calibrate(bacon_ctx *ctx, int32_t layer, const bacon_batch *batch,

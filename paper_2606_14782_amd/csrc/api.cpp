@@ -679,7 +679,7 @@ bacon_status bacon_calibrate(bacon_ctx *c, int32_t layer, const bacon_batch *bt,
   int chunk = 0;
   const SeqTable st = make_table(c, bt, &chunk);
   // the [Hkv, T] vectors of the split path use the batch's T as row length;
-  // its lists and V take the first copies of the fused pass's, and the B
+  // V, the lists and a copy of B take the first copies of the fused pass's, and the B
   // histogram an S histogram (each user clears it first)
   const Layout &L = c->L;
   SplitArgs p{};
@@ -695,7 +695,16 @@ bacon_status bacon_calibrate(bacon_ctx *c, int32_t layer, const bacon_batch *bt,
   a.eps = c->params.eps;
   a.use_last_query = c->params.use_last_query;
   a.terms = c->params.terms;
+  p.in_B = d_B;
   a.vec_B = d_B;
+  {
+    // outputs over B: the stages after the first read a copy
+    const uintptr_t bytes = (uintptr_t)a.Hkv * a.T * sizeof(float), b0 = reinterpret_cast<uintptr_t>(d_B);
+    for (const float *o : {d_S, d_E, d_V, d_lambda}) {
+      const uintptr_t o0 = reinterpret_cast<uintptr_t>(o);
+      if (o && o0 < b0 + bytes && b0 < o0 + bytes) a.vec_B = p.copy_B = reinterpret_cast<float *>(c->ws + L.vec_b);
+    }
+  }
   a.ring = reinterpret_cast<float *>(c->ws + L.ring);
   a.ring_stride = (int64_t)a.Hkv * a.T;
   a.ring_slots = L.slots;

@@ -160,11 +160,13 @@ struct AllocArgs {
   unsigned *err;                 // optional error word (set to 2 if the search fails)
 };
 
-// The split calibrate: the segment select's arguments (vec_B the caller's B,
-// hist_B zeroed, vec_V over every position), Q and the outputs.
+// The split calibrate: the segment select's arguments (vec_B the caller's B, or
+// its copy; hist_B zeroed, vec_V over every position), the caller's B and Q and
+// the outputs.
 struct SplitArgs {
   SegArgs s;
-  const float *in_Q;
+  const float *in_B, *in_Q;
+  float *copy_B;           // optional copy of B, for outputs that overlap it
   float *out_S;
   float *out_V, *out_E;    // optional [Hkv, T]
 };

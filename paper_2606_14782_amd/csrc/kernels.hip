@@ -4642,6 +4642,8 @@ hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs
 //  * split_scores: lambda and S = B + lambda V (Eq. bacon_score) over every position;
 //    with pooling before calibration the candidates get pool(B) + lambda V
 //    instead, the score the top-K then ranks unpooled.
+// The caller's S, E and V may be its B or Q: the last launch alone writes the
+// outputs, and reads B's copy that the first one made where they overlap.
 struct EvidenceLds {
   unsigned hist[kHBins];
   float Es[kSegLen + 2 * kMaxRadius];
@@ -4661,7 +4663,7 @@ __global__ __launch_bounds__(kSegThreads) void k_split_evidence(SplitArgs p, Seq
 #pragma unroll
   for (int j = 0; j < kEvJ; ++j) {
     const int u = min(max(w0 + t + j * NT, 0), n - 1);
-    bv[j] = a.vec_B[base + u];
+    bv[j] = p.in_B[base + u];
     qv[j] = p.in_Q[base + u];
   }
   // T: the previous layers' E, oldest first
@@ -4697,9 +4699,9 @@ __global__ __launch_bounds__(kSegThreads) void k_split_evidence(SplitArgs p, Seq
       const float V = ((a.terms & 1u) ? E : 0.f) + ((a.terms & 4u) ? Tv : 0.f) + L;
       ring[i] = E;
       a.vec_V[base + i] = V;
-      if (p.out_E) p.out_E[base + i] = E;
-      if (p.out_V) p.out_V[base + i] = V;
-      if (i < nc) atomicAdd(&lds.hist[hbin(float_key(a.vec_B[base + i]))], 1u);
+      const float Bi = p.in_B[base + i];
+      if (p.copy_B) p.copy_B[base + i] = Bi;
+      if (i < nc) atomicAdd(&lds.hist[hbin(float_key(Bi))], 1u);
     }
   }
   lds_barrier();
@@ -4738,8 +4740,19 @@ __global__ __launch_bounds__(kSegThreads) void k_split_lists(SplitArgs p, SeqTab
   list_boundary(a, st, gs, sg, h, b, M, i0, ncand, base, hv, xb, xv, lds.ss, lds.pre);
 }
 
-__global__ __launch_bounds__(kSegThreads) void k_split_scores(SegArgs a, float *out_S, SeqTable st) {
-  segscore_body<true, true>(a, st, blockIdx.y, blockIdx.x, find_seg(st, blockIdx.y), out_S);
+__global__ __launch_bounds__(kSegThreads) void k_split_scores(SplitArgs p, SeqTable st) {
+  const int h = blockIdx.x, gs = blockIdx.y, b = find_seg(st, gs);
+  if (p.out_E || p.out_V) {
+    const SegArgs &a = p.s;
+    const int n = st.cu[b + 1] - st.cu[b], i0 = (gs - st.seg_base[b]) * kSegLen;
+    const int64_t base = (int64_t)h * a.T + st.cu[b];
+    const float *re = a.ring + a.ring_slot * a.ring_stride + base;
+    for (int i = i0 + threadIdx.x; i < min(n, i0 + kSegLen); i += kSegThreads) {
+      if (p.out_E) p.out_E[base + i] = re[i];
+      if (p.out_V) p.out_V[base + i] = a.vec_V[base + i];
+    }
+  }
+  segscore_body<true, true>(p.s, st, gs, h, b, p.out_S);
 }
 
 hipError_t launch_split(int stage, const SplitArgs &p, const SeqTable &st, hipStream_t s) {
@@ -4749,7 +4762,7 @@ hipError_t launch_split(int stage, const SplitArgs &p, const SeqTable &st, hipSt
   } else if (stage == 1) {
     hipLaunchKernelGGL(k_split_lists, grid, block, sizeof(CandLds), s, p, st);
   } else {
-    hipLaunchKernelGGL(k_split_scores, grid, block, sizeof(ScoreLds), s, p.s, p.out_S, st);
+    hipLaunchKernelGGL(k_split_scores, grid, block, sizeof(ScoreLds), s, p, st);
   }
   return hipGetLastError();
 }

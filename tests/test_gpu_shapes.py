@@ -288,3 +288,38 @@ def test_calibrate_on_signed_scores(lens, budgets, keep):
         # float32 V (a sum of 11 and two more terms): below 1e-6 of its values
         g = got[name].cpu().numpy()
         assert np.abs(g - w).max() <= 1e-5 * np.abs(w).max(), name
+
+
+@pytest.mark.parametrize("pool_mode", [0, 2])
+@pytest.mark.parametrize("over", [("S", "E", None), ("E", "S", None), ("V", "E", "S"), (None, "V", "S")])
+def test_calibrate_in_place(pool_mode, over):
+    """bacon_calibrate with outputs over its inputs (over: what B's buffer, Q's
+    buffer and a third one receive): the same as into buffers of their own, over
+    several segments and with lists beyond one workgroup, whose scale-matching set
+    is taken from every position's B."""
+    import ctypes
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    wl = _wl(2, 4, 2, 64, 32, 7, "bf16", (6300, 2100, 40), (3100, 200, 4))
+    batch = bacon.BatchLayout(wl.cu_seqlens, wl.budgets_arr)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    B = torch.rand(2, wl.total_tokens, device="cuda", generator=g) ** 3
+    Q = torch.rand(2, wl.total_tokens, device="cuda", generator=g) ** 3
+    a, c = (P.make_ctx(wl, P.params_for(wl, pool_mode=pool_mode)) for _ in range(2))
+    a.bacon_begin_prompt(batch)
+    c.bacon_begin_prompt(batch)
+    ptr = lambda t: None if t is None else ctypes.c_void_p(t.data_ptr())
+    for layer in range(2):
+        want = a.bacon_calibrate(layer, batch, B, Q, want_E=True, want_V=True)
+        bufs = [B.clone(), Q.clone(), torch.empty_like(B)]
+        out = {n: bufs[i] for i, n in enumerate(over) if n}
+        lam = torch.empty_like(want["lambda"])
+        S = out.get("S", torch.empty_like(B))
+        bacon._check(bacon.lib().bacon_calibrate(
+            c._h, layer, ctypes.byref(batch.c), ptr(bufs[0]), ptr(bufs[1]), ptr(S), ptr(lam),
+            ptr(out.get("E")), ptr(out.get("V")), bacon._stream()))
+        torch.cuda.synchronize()
+        assert torch.equal(lam, want["lambda"])
+        for n, t in dict(out, S=S).items():
+            assert torch.equal(t, want[n]), (layer, n)
