@@ -112,13 +112,13 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.vec_pb = off;   off += kCopies2 * L.vec_stride;
   L.vec_pv = off;   off += kCopies2 * L.vec_stride;
   L.vec_s = off;    off += kCopiesS * L.vec_stride;
-  const size_t hist = (size_t)s->max_batch * s->num_kv_heads * kHBins * sizeof(unsigned);
+  const size_t hist = (size_t)s->max_batch * s->num_kv_heads * kHRow * sizeof(unsigned);
   L.hist_b_stride = align256(hist * kHCopies);
   L.hist_s_stride = align256(hist);
   L.hist_b = off;   off += copies_hist_b(true, adaptive) * L.hist_b_stride;
   // the allocation's histograms: cleared with them where a prompt uses them
   // (bacon_allocate_heads clears its own copy)
-  L.hist_a_stride = align256((size_t)s->max_batch * s->num_kv_heads * alloc_hist_words() * sizeof(unsigned));
+  L.hist_a_stride = align256(hist);
   if (adaptive) {
     L.hist_a = off; off += kCopiesHistA * L.hist_a_stride;
   }
@@ -723,7 +723,7 @@ bacon_status bacon_calibrate(bacon_ctx *c, int32_t layer, const bacon_batch *bt,
   p.out_V = d_V;
   p.out_E = d_E;
   TRY(head_table(c, bt, s, &a.hb));
-  const hipError_t e = launch_zero(a.hist_B, (int64_t)bt->batch * a.Hkv * kHBins, s);
+  const hipError_t e = launch_zero(a.hist_B, (int64_t)bt->batch * a.Hkv * kHRow, s);
   if (e != hipSuccess) return hip_fail(e, "clear");
   for (int stage = 0; stage < 3; ++stage)
     TRY(timed(c, KI_SPLIT_CALIB, s, [&] { return launch_split(stage, p, st, s); }));

@@ -19,6 +19,14 @@ constexpr int kSegLen = 2048;       // positions per segment of the histogram se
 constexpr int kSegThreads = 1024;
 constexpr int kPoolHalo = 16;       // largest pool half-width
 constexpr int kHBins = 8192;        // bins of the select histograms (32 per octave of a float)
+// Words between the histograms of consecutive (sequence, KV head) pairs.  The
+// counts of all of them fall on the same few lines (scores of a prompt span
+// a few octaves), and at 32 KiB apart those lines share few memory channels, how
+// few depending on where the workspace lies: a 46079-token layer call (16/8
+// heads, d 64) took 557 to 611 us over the workspace's offsets from 2 MiB and takes
+// 530 to 540 at this distance, a 59464-token one (28/4) 696 to 749 and 672 (other
+// distances: 256 bytes more than 32 KiB 733 to 768, 1280 696 to 728, 16640 680 to 720).
+constexpr int kHRow = kHBins + 1088;
 constexpr int kHCopies = 1;         // copies of the B histogram the fused pass spreads its atomics over
 constexpr int kLdsBytes = 160 * 1024;   // LDS per CU (and per workgroup) on gfx950
 constexpr int kKrWaves = 4;             // waves of a key-register pass workgroup
@@ -54,7 +62,7 @@ struct PassArgs {
   float *lse2;          // [B, Hkv, Rpad] row normalisers, log2 units (merge kernel writes)
   float *lse_user;      // optional [B, Hq, W] natural-log normaliser (merge kernel writes)
   const float *lse_in;  // optional [B, Hq, W] natural-log normalisers given by the caller (pass 2 reads)
-  unsigned *hist_B;     // [B, Hkv, kHCopies, kHBins] B histogram of the select (fused pass adds)
+  unsigned *hist_B;     // [B, Hkv, kHCopies, kHRow] B histogram of the select (fused pass adds)
   // PASS_SCORE
   float *out_B, *out_Q; // [Hkv, T]
   // PASS_FUSED
@@ -114,8 +122,8 @@ struct SegArgs {
   float *vec_pB, *vec_pV;        // [Hkv, T] pooled B and V over I
   unsigned *vec_S;               // [Hkv, T] keys of the pooled score over I
   unsigned *hist_A;              // the allocation's histogram, cleared by the calibration (may be NULL)
-  unsigned *hist_B, *hist_S;     // key histograms of B [B, Hkv, kHCopies, kHBins] (the bin count is
-                                 // the sum of the copies) and of the pooled score [B, Hkv, kHBins];
+  unsigned *hist_B, *hist_S;     // key histograms of B [B, Hkv, kHCopies, kHRow] (the bin count is
+                                 // the sum of the copies) and of the pooled score [B, Hkv, kHRow];
                                  // the final kernel clears hist_B for the next layer, the
                                  // calibration kernel clears hist_S
   // per-segment lists at or above a boundary bin: segment s of a sequence
@@ -150,7 +158,7 @@ struct AllocArgs {
   double alpha;                  // floor fraction: every head keeps floor(alpha K) at least
   const float *vec_B;            // [Hkv, T]
   float *vec_A;                  // [Hkv, T] the pooled B
-  unsigned *hist_A;              // [B, Hkv, alloc_hist_words()] histogram of its keys (zero before the pool job)
+  unsigned *hist_A;              // [B, Hkv, kHRow] histogram of its keys and its group sums (zero before the pool job)
   unsigned *list_A;              // [Hkv, T] keys of the boundary bin, segment s from slot s*kSegLen
   int *cnt_A;                    // [Hkv, total_segs] their number
   uint2 *rec_A;                  // [B, Hkv] boundary bin, the head's count above it
@@ -274,7 +282,6 @@ hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs
 // LDS of the final workgroup for budgets up to max_budget.
 size_t final_lds_bytes(int max_budget, int window);
 size_t alloc_lds_bytes(int hkv);
-int alloc_hist_words();
 // One job of the allocation in a launch of its own: 0 pool, 1 list, 2 pick.
 hipError_t launch_alloc(int stage, const AllocArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, const SeqTable &st, hipStream_t s);

@@ -523,7 +523,7 @@ __device__ __forceinline__ void pass_body(const PassArgs &a, const SeqTable &st,
     for (int p = t; p < ncnd; p += nt) atomicAdd(&hist[hbin(float_key(cb[p]))], 1u);
     __syncthreads();
     const int copy = (h * st.total_chunks + gchunk) % kHCopies;
-    unsigned *gh = a.hist_B + (((int64_t)b * a.Hkv + h) * kHCopies + copy) * kHBins;
+    unsigned *gh = a.hist_B + (((int64_t)b * a.Hkv + h) * kHCopies + copy) * kHRow;
     for (int q = blo + t; q <= bhi; q += nt) {
       const unsigned cnt = hist[q];
       if (cnt) atomicAdd(&gh[q], cnt);
@@ -1040,7 +1040,7 @@ __device__ __forceinline__ void krpass_body(const PassArgs &a, const SeqTable &s
     for (int p = t; p < ncnd; p += NT) atomicAdd(&hist[hbin(float_key(cb[p]))], 1u);
     __syncthreads();
     const int copy = (h * st.total_chunks + gchunk) % kHCopies;
-    unsigned *gh = a.hist_B + (((int64_t)b * a.Hkv + h) * kHCopies + copy) * kHBins;
+    unsigned *gh = a.hist_B + (((int64_t)b * a.Hkv + h) * kHCopies + copy) * kHRow;
     for (int q = blo + t; q <= bhi; q += NT) {
       const unsigned cnt = hist[q];
       if (cnt) atomicAdd(&gh[q], cnt);
@@ -1545,7 +1545,7 @@ __device__ __forceinline__ void wide_body(const PassArgs &a, const SeqTable &st,
     // bins, so that a wave's additions fall on few lines
     if (a.out_B) return;
     lds_barrier();
-    unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+    unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHRow;
     const unsigned short *h16 = reinterpret_cast<const unsigned short *>(hist);
     unsigned num[kHBins / NT];
 #pragma unroll
@@ -2109,7 +2109,7 @@ __global__ __launch_bounds__(64 * kKrWaves, 2) void k_single(PassArgs a, SeqTabl
     bhi = max(bhi, mm2[kKrWaves + w]);
   }
   const int copy = (h * st.total_chunks + gchunk) % kHCopies;
-  unsigned *gh = a.hist_B + (((int64_t)b * a.Hkv + h) * kHCopies + copy) * kHBins;
+  unsigned *gh = a.hist_B + (((int64_t)b * a.Hkv + h) * kHCopies + copy) * kHRow;
   for (int q = blo + t; q <= bhi; q += NT) {
     const unsigned cnt = hist[q];
     if (cnt) atomicAdd(&gh[q], cnt);
@@ -2858,6 +2858,7 @@ constexpr int kSegE = kSegWin + 2 * kMaxRadius;            // E over the window 
 constexpr int kSegEJ = (kSegE + kSegThreads - 1) / kSegThreads;
 constexpr int kAllPer = kMaxSelLen / kSegThreads;          // positions per thread of the register fallback
 constexpr int kHPer = kHBins / kSegThreads;                // histogram bins per thread
+constexpr int kAllocGroups = 64;                           // groups of bins of the allocation's histograms
 constexpr int kListPer = 4;                                // list entries per thread
 constexpr int kListSpec = 2;                               // of them loaded before the counts are known
 constexpr int kListCap = kListPer * kSegThreads;           // list entries of a (sequence, KV head)
@@ -2960,7 +2961,7 @@ __device__ __forceinline__ void load_bins(const unsigned *gh, unsigned *cb) {
   u32x4 v[COPIES][kHPer / 4];
 #pragma unroll
   for (int c = 0; c < COPIES; ++c) {
-    const u32x4 *hp = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHBins + kHPer * threadIdx.x);
+    const u32x4 *hp = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHRow + kHPer * threadIdx.x);
 #pragma unroll
     for (int q = 0; q < kHPer / 4; ++q) v[c][q] = hp[q];
   }
@@ -3156,12 +3157,12 @@ __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st
   // copies): loaded raw and summed once the window loads below are in flight
   u32x4 hv[kHCopies][kHPer / 4];
   {
-    const unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+    const unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHRow;
 #pragma unroll
     for (int c = 0; c < kHCopies; ++c)
 #pragma unroll
       for (int q = 0; q < kHPer / 4; ++q)
-        hv[c][q] = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHBins + kHPer * t)[q];
+        hv[c][q] = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHRow + kHPer * t)[q];
   }
   const float *re = a.ring + a.ring_slot * a.ring_stride + base;   // E of this layer
   {
@@ -3169,14 +3170,14 @@ __device__ __forceinline__ void segcal_body(const SegArgs &a, const SeqTable &st
     // accumulates next (its readers of the previous layer are done)
     const int nseg = st.seg_base[b + 1] - st.seg_base[b];
     const int sl = 4 * ((kHBins / 4 + nseg - 1) / nseg);
-    unsigned *hs = a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins;
+    unsigned *hs = a.hist_S + ((int64_t)b * a.Hkv + h) * kHRow;
     for (int q = sg * sl + 4 * t; q < min(kHBins, (sg + 1) * sl); q += 4 * NT)
       *reinterpret_cast<u32x4 *>(hs + q) = u32x4{0u, 0u, 0u, 0u};
     // ... and of the allocation's histogram, which this layer is done with
     if (ADAPT && a.hist_A) {
-      constexpr int HA = kHBins + 64;
+      constexpr int HA = kHBins + kAllocGroups;
       const int sa = 4 * ((HA / 4 + nseg - 1) / nseg);
-      unsigned *ha = a.hist_A + ((int64_t)b * a.Hkv + h) * HA;
+      unsigned *ha = a.hist_A + ((int64_t)b * a.Hkv + h) * kHRow;
       for (int q = sg * sa + 4 * t; q < min(HA, (sg + 1) * sa); q += 4 * NT)
         *reinterpret_cast<u32x4 *>(ha + q) = u32x4{0u, 0u, 0u, 0u};
     }
@@ -3583,7 +3584,7 @@ __device__ __forceinline__ void segscore_body(SegArgs a, const SeqTable &st, int
   const int i0 = sg * kSegLen;
   const int ncand = max(0, min(i0 + kSegLen, nc) - i0);
   const int64_t base = (int64_t)h * a.T + st.cu[b];
-  const int64_t hrow = ((int64_t)b * a.Hkv + h) * kHBins;
+  const int64_t hrow = ((int64_t)b * a.Hkv + h) * kHRow;
 
   // what the pooled score is made of does not depend on lambda: in flight
   // first.  Mean of S: the pooled B and V (pool(B + lambda V) = pool(B) +
@@ -3771,15 +3772,16 @@ __device__ __forceinline__ void segcand_body(SegArgs a, const SeqTable &st, int 
     // clear this segment's slice of the B histogram for the layer that takes
     // it next (its readers, the calibration and score jobs, are done)
     const int nseg = st.seg_base[b + 1] - st.seg_base[b];
-    const int sl = 4 * ((kHCopies * kHBins / 4 + nseg - 1) / nseg);
-    unsigned *hb = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
-    for (int q = sg * sl + 4 * t; q < min(kHCopies * kHBins, (sg + 1) * sl); q += 4 * NT)
+    constexpr int HB = (kHCopies - 1) * kHRow + kHBins;
+    const int sl = 4 * ((HB / 4 + nseg - 1) / nseg);
+    unsigned *hb = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHRow;
+    for (int q = sg * sl + 4 * t; q < min(HB, (sg + 1) * sl); q += 4 * NT)
       *reinterpret_cast<u32x4 *>(hb + q) = u32x4{0u, 0u, 0u, 0u};
   }
   const int kept = min(sel_head_budget(st, a.hb, a.Hkv, b, h, a.sb), nc);
   if (kept <= 0 || kept == nc) return;               // none or all kept: no list needed
   unsigned cb[kHPer];
-  load_bins<1>(a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins, cb);
+  load_bins<1>(a.hist_S + ((int64_t)b * a.Hkv + h) * kHRow, cb);
   unsigned key[PER];
 #pragma unroll
   for (int j = 0; j < PER; ++j) key[j] = a.vec_S[base + i0 + min(t + j * NT, max(ncand - 1, 0))];
@@ -3915,10 +3917,10 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
       }
     } else {
       if (nc > kAllPer * kSegThreads)
-        whole_topk_stream(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins,
+        whole_topk_stream(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHRow,
                           part == 0 ? idx : nullptr, tbl, ss);
       else
-        whole_topk<ONE>(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHBins, part == 0 ? idx : nullptr,
+        whole_topk<ONE>(a, base, nc, kept, a.hist_S + ((int64_t)b * a.Hkv + h) * kHRow, part == 0 ? idx : nullptr,
                  tbl, ss, ckey, cpos, pre);
     }
   }
@@ -3995,11 +3997,10 @@ __device__ __forceinline__ void final_body(SegArgs a, const SeqTable &st, int pa
 //    bits at a time, and the budgets.  Bin 0 also holds the keys of negative
 //    values (B of a caller's own): there it searches all 32 key bits over A.
 constexpr int kMaxAllocHeads = 32;
-constexpr int kAllocGroups = 64, kAllocGroupBins = kHBins / kAllocGroups;
-constexpr int kAllocRow = kHBins + kAllocGroups;        // words of a head's histogram
+constexpr int kAllocGroupBins = kHBins / kAllocGroups;
 constexpr int kAllocDigits = 512;                       // bins of a level of alloc_pick
 static_assert(kAllocGroupBins == 128 && kHPer == 8, "groups of 16 threads");
-int alloc_hist_words() { return kAllocRow; }
+static_assert(kHBins + kAllocGroups <= kHRow, "the groups' sums follow the bins");
 
 struct AllocPoolLds {
   unsigned hist[kHBins];
@@ -4055,7 +4056,7 @@ __device__ __forceinline__ void alloc_pool_body(const AllocArgs &a, const SeqTab
     }
   }
   lds_barrier();
-  unsigned *gh = a.hist_A + ((int64_t)b * a.Hkv + h) * kAllocRow;
+  unsigned *gh = a.hist_A + ((int64_t)b * a.Hkv + h) * kHRow;
 #pragma unroll
   for (int q = 0; q < kHBins / NT; ++q) {
     const unsigned c = lds.hist[t + q * NT];
@@ -4111,12 +4112,12 @@ __device__ __forceinline__ void alloc_list_body(const AllocArgs &a, const SeqTab
   const unsigned R = (unsigned)H * (unsigned)(K - f);
   const int64_t base = (int64_t)h * a.T + st.cu[b];
   const int i0 = sg * kSegLen, i1 = min(nc, i0 + kSegLen);
-  const unsigned *gh = a.hist_A + (int64_t)b * H * kAllocRow;
+  const unsigned *gh = a.hist_A + (int64_t)b * H * kHRow;
   float x[kSegPer];
 #pragma unroll
   for (int j = 0; j < kSegPer; ++j) x[j] = a.vec_A[base + min(i0 + t + j * NT, nc - 1)];
   for (int e = t; e < H * kAllocGroups; e += NT)
-    (&lds.coarse[0][0])[e] = gh[(int64_t)(e >> 6) * kAllocRow + kHBins + (e & 63)];
+    (&lds.coarse[0][0])[e] = gh[(int64_t)(e >> 6) * kHRow + kHBins + (e & 63)];
   if (t == 0) lds.cnt = 0u;
   lds_barrier();
   alloc_suffix<1>(&lds.coarse[0][0], H, [](int) { return 0u; });
@@ -4132,7 +4133,7 @@ __device__ __forceinline__ void alloc_list_body(const AllocArgs &a, const SeqTab
   lds_barrier();
   const int g = lds.ss.bc_i[0];
   for (int e = t; e < H * kAllocGroupBins; e += NT)
-    (&lds.fine[0][0])[e] = gh[(int64_t)(e >> 7) * kAllocRow + g * kAllocGroupBins + (e & 127)];
+    (&lds.fine[0][0])[e] = gh[(int64_t)(e >> 7) * kHRow + g * kAllocGroupBins + (e & 127)];
   lds_barrier();
   alloc_suffix<2>(&lds.fine[0][0], H,
                   [&](int q) { return g + 1 < kAllocGroups ? lds.coarse[q][g + 1] : 0u; });
@@ -4705,7 +4706,7 @@ __global__ __launch_bounds__(kSegThreads) void k_split_evidence(SplitArgs p, Seq
     }
   }
   lds_barrier();
-  unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+  unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHRow;
   for (int q = t; q < kHBins; q += NT) {
     const unsigned c = lds.hist[q];
     if (c) atomicAdd(&gh[q], c);
@@ -4724,12 +4725,12 @@ __global__ __launch_bounds__(kSegThreads) void k_split_lists(SplitArgs p, SeqTab
   const int M = max(0, min(scale_set_size(a.rho, sel_head_budget(st, a.hb, a.Hkv, b, h, a.sb)), nc));
   if (M <= 0 || !a.use_last_query) return;
   u32x4 hv[kHCopies][kHPer / 4];
-  const unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHBins;
+  const unsigned *gh = a.hist_B + ((int64_t)b * a.Hkv + h) * kHCopies * kHRow;
 #pragma unroll
   for (int c = 0; c < kHCopies; ++c)
 #pragma unroll
     for (int q = 0; q < kHPer / 4; ++q)
-      hv[c][q] = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHBins + kHPer * t)[q];
+      hv[c][q] = reinterpret_cast<const u32x4 *>(gh + (int64_t)c * kHRow + kHPer * t)[q];
   float xb[kSegPer], xv[kSegPer];
 #pragma unroll
   for (int j = 0; j < kSegPer; ++j) {
