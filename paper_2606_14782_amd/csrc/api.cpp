@@ -435,49 +435,114 @@ void ring_slots(const bacon_ctx *c, int layer, int *wr, int *cnt) {
   *wr = layer % c->L.slots;
 }
 
-// Whether a batch takes the wide passes, with how many row groups per
-// workgroup and chunks per workgroup.  The estimate of a launch that holds
-// both passes and the select jobs (us, from traces of 16 to 512 workgroups):
-// a workgroup takes 6 us plus 2.2 per further chunk and, per row tile of four
-// waves on a SIMD, 0.9 (bf16) or what its fp32 matrix instructions take; a select workgroup 8;
+// Compute units of the device.
+int device_cus(bacon_ctx *c) {
+  if (c->cus < 0) {
+    int dev = 0, n = 0;
+    c->cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+      c->cus = n;
+  }
+  return c->cus;
+}
+
+// Calls that plan the wide passes: the fused calls, the fused calls with the
+// normalisers given (no pass 1), bacon_score (no select).
+enum WideCall { WIDE_FUSED, WIDE_GIVEN, WIDE_SCORE };
+
+// A batch's grid on the wide passes with s row groups per workgroup.
+struct WideGrid {
+  double cus;
+  int nrt, rpad;
+  int chunks;             // of the longest sequence
+  double blocks, jobs;    // chunks and workgroups over the KV heads
+  double sel;             // select workgroups
+};
+
+// Estimates of a plan (the smaller the better).  The prompt call and the layer
+// calls must share the row groups, which decide how the normalisers' sums are
+// grouped: both return the same bits.
+//
+// bf16 (us, from traces of 16 to 512 workgroups): a workgroup takes 6 plus 2.2 per
+// further chunk and 0.9 per row tile of four waves on a SIMD; a select workgroup 8;
 // beyond one round of the CUs a launch takes the sum over the CUs and half a
-// workgroup more.
-bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) {
+// workgroup more.  A pass of a layer call counts beside the prompt's launch, more
+// beyond 128 rows, where one row group leaves a layer call well behind the
+// streaming passes (28/4 heads, 8K tokens, 12 layers: prompt 280 and layer calls
+// 742 us with one, 300 and 660 with two; 472 and 629 before).
+double wide_cost_bf16(const WideGrid &g, int s, int p) {
+  const double t = 6.0 + 2.2 * (p - 1) + p * 0.9 * std::max((double)g.nrt / s, 0.25 * ((g.nrt + s - 1) / s));
+  const double n = 2.0 * g.jobs + g.sel, t1 = t - (p - 1) * (t - 3.8) / 2;
+  return (n <= g.cus ? std::max(t, 8.0) : (2.0 * g.jobs * t + g.sel * 8.0) / g.cus + 0.5 * t) +
+         (g.nrt > 4 ? 1.3 : 0.5) * (g.blocks <= g.cus ? t1 : g.blocks * t1 / g.cus + 0.5 * t1);
+}
+// fp32: a workgroup takes 4.4, what its waves' key requests take (a 16-byte load
+// of a wave touches 32 rows: 0.027 us per load instruction) and 0.0149 d per row tile
+// of a SIMD (its matrix instructions); pass 2 1.5 and the merge of the normalisers more
+// (d 128, 8 rows, 700 tokens: pass 1 18.5, 12.0 and 7.7 us with one, two and four
+// row groups).  A layer of a six-layer prompt call then takes 7.3 + 1.1 (pass 2) in one
+// round of the CUs, else 8.3 + 0.97 (K passes over the CUs) + 7.2 (select) + 0.3
+// (pass 2), and a layer call 28 more than its passes, both within 6% over 38 shapes
+// of 8 to 128 rows and 700 to 13201 tokens.  The product weighs the two calls the
+// same: 4.5% off the prompt calls and 6.3% off the layer calls of these shapes (up to
+// 1.12 of the streaming passes' time without it).
+double wide_cost_fp32(const WideGrid &g, int d, WideCall call, int s, int p) {
+  const double unit = d / 8, chunk = 0.027 * (16 / s * std::min(s, g.nrt)) * unit + 0.0149 * d * 4 * g.nrt / s;
+  const double more = 1.5 + (call == WIDE_GIVEN ? 0.0 : 0.03 * g.chunks * g.rpad / 256);
+  const double first = call == WIDE_GIVEN ? 0.0 : 1.0;
+  const double passes = (first * (4.4 + chunk) + 4.4 + chunk + more) * (g.blocks <= g.cus ? 1.0 : g.blocks / g.cus + 0.3);
+  if (call == WIDE_SCORE) return passes;
+  const double t1 = 4.1 + p * (0.3 + chunk), t2 = t1 + more;
+  const double prompt = (1.0 + first) * g.jobs + g.sel <= g.cus
+                            ? std::max(16.5, 7.3 + 1.1 * t2)
+                            : 8.3 + (0.97 * g.jobs * (first * t1 + t2) + 7.2 * g.sel) / g.cus + 0.3 * t2;
+  return prompt * (28.0 + 1.07 * passes);
+}
+// The same of the streaming passes with fp32's 128 rows: 6.5 and 9.5 (d 128) per
+// stage that a CU takes, two passes, the merge, a select launch of 12.  (3344, 3127 and
+// 5213 tokens, 32/8 heads, six layers: prompt call 558 and layer calls 666 us, 605 and
+// 742 on the wide passes; 13201 tokens: 648 and 760, 599 and 752.)
+double stream_cost_fp32(const bacon_ctx *c, const bacon_batch *bt, double cus) {
+  const int d = c->shape.head_dim, tk = stage_keys(c->L.rpad / 32);
+  double stages = 0;
+  for (int b = 0; b < bt->batch; ++b) stages += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + tk - 1) / tk;
+  stages *= c->shape.num_kv_heads;
+  const double fit = std::max(1, kLdsBytes / pass_lds_bytes(PASS_FUSED, false, d, c->L.rpad, 4 * tk));
+  const double each = std::ceil(stages / (cus * fit));   // stages of a workgroup
+  const double t = 6.5 + 0.074 * d * each * std::ceil(stages / each / cus);
+  return (2 * t + 16.5) * (28.0 + 2 * t + 2.5);
+}
+
+// Whether a batch takes the wide passes, with how many row groups per
+// workgroup and chunks per workgroup.
+bool wide_plan(bacon_ctx *c, const bacon_batch *bt, WideCall call, int *split, int *cpw) {
   const bool bf16 = c->shape.dtype == BACON_BF16;
-  const int nrt = c->L.rpad / 32, hkv = c->shape.num_kv_heads;
-  const double tile = bf16 ? 0.9 : 0.053 * c->shape.head_dim;
-  int64_t segs = 0;
-  for (int b = 0; b < bt->batch; ++b) segs += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + kSegLen - 1) / kSegLen;
-  const double sel = (double)(3 * segs + bt->batch) * hkv;
+  const int hkv = c->shape.num_kv_heads, d = c->shape.head_dim;
+  WideGrid g{};
+  g.cus = device_cus(c);
+  g.rpad = c->L.rpad;
+  g.nrt = g.rpad / 32;
   // (more than 128 rows of fp32: a layer call of 13404 and 2013 tokens, 14/2 heads,
   // takes 111 us a layer here and 89 with the streaming passes)
-  if (!bf16 && nrt > 4) return false;
+  if (!bf16 && g.nrt > 4) return false;
+  for (int b = 0; b < bt->batch; ++b)
+    g.sel += 1 + 3 * ((bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + kSegLen - 1) / kSegLen);
+  g.sel *= hkv;
   double best = 1e30;
   for (int s = 1; s <= 4; s *= 2) {
-    if (!wide_supported(bf16, c->shape.head_dim, c->L.rpad, s)) continue;
-    int64_t blocks = 0;
-    int nch = 0;
-    for (int b = 0; b < bt->batch; ++b) {
-      const int k = (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s);
-      blocks += k;
-      nch = std::max(nch, k);
-    }
-    if (nch > wide_max_chunks(c->L.rpad) || blocks * hkv > (int64_t)c->wide_limit * s) continue;
+    if (!wide_supported(bf16, d, g.rpad, s)) continue;
     for (int p = 1; p <= 2; ++p) {
-      int64_t jobs = 0;
-      for (int b = 0; b < bt->batch; ++b)
-        jobs += ((bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s) + p - 1) / p;
-      const double t = 6.0 + 2.2 * (p - 1) + p * tile * std::max((double)nrt / s, 0.25 * ((nrt + s - 1) / s));
-      const double n = 2.0 * jobs * hkv + sel, cus = c->cus > 0 ? c->cus : 256;
-      // A pass of a layer call, one chunk per workgroup, counts too: the two kinds
-      // of call share the split, so that they give the same bits.  It weighs more
-      // beyond 128 rows, where one row group leaves a layer call well behind the
-      // streaming passes (28/4 heads, 8K tokens, 12 layers: prompt 280 and layer
-      // calls 742 us with one, 300 and 660 with two; 472 and 629 before).
-      const double layer_weight = nrt > 4 ? 1.3 : 0.5;
-      const double t1 = t - (p - 1) * (t - 3.8) / 2, n1 = (double)blocks * hkv;
-      const double est = (n <= cus ? std::max(t, 8.0) : (2.0 * jobs * hkv * t + sel * 8.0) / cus + 0.5 * t) +
-                         layer_weight * (n1 <= cus ? t1 : n1 * t1 / cus + 0.5 * t1);
+      g.chunks = 0;
+      g.blocks = g.jobs = 0;
+      for (int b = 0; b < bt->batch; ++b) {
+        const int k = (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + wide_keys(s) - 1) / wide_keys(s);
+        g.chunks = std::max(g.chunks, k);
+        g.blocks += (double)k * hkv;
+        g.jobs += (double)((k + p - 1) / p) * hkv;
+      }
+      if (g.chunks > wide_max_chunks(g.rpad) || g.blocks > (double)c->wide_limit * s) continue;
+      const double est = bf16 ? wide_cost_bf16(g, s, p) : wide_cost_fp32(g, d, call, s, p);
       if (est < best) {
         best = est;
         *split = s;
@@ -485,6 +550,8 @@ bool wide_plan(const bacon_ctx *c, const bacon_batch *bt, int *split, int *cpw) 
       }
     }
   }
+  // (within the estimates' error the wide passes stay)
+  if (!bf16 && g.nrt == 4 && call == WIDE_FUSED && 0.95 * best > stream_cost_fp32(c, bt, g.cus)) return false;
   return best < 1e30;
 }
 
@@ -638,7 +705,7 @@ bacon_status bacon_score(bacon_ctx *c, int32_t layer, const bacon_batch *bt, con
   TRY(check_lds(c, chunk));
   // small grids take the wide passes (with the streaming passes' sums)
   int split = 1, cpw = 1;
-  const bool wide = !c->kr_off && wide_plan(c, bt, &split, &cpw);
+  const bool wide = !c->kr_off && wide_plan(c, bt, WIDE_SCORE, &split, &cpw);
   if (wide) st = make_table(c, bt, &chunk, wide_keys(split));
   PassArgs a = pass_args(c, st, chunk, d_q_win, d_k);
   a.T = bt->cu_seqlens[bt->batch];
@@ -882,18 +949,10 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
     r.single = (int64_t)nmax * hkv <= c->single_cap &&
                (c->single_mode == 1 || (grid <= c->single_cap && 2 * grid >= c->single_cap));
   }
-  if (c->cus < 0) {
-    int dev = 0;
-    c->cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      int n = 0;
-      if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) c->cus = n;
-    }
-  }
   // small grids take the wide passes
   const bool kr_shape = kr_supported(r.bf16, c->shape.head_dim, c->L.rpad);
   int split = 1, cpw = 1;
-  if (!c->kr_off && !r.single) r.wide = wide_plan(c, bt, &split, &cpw);
+  if (!c->kr_off && !r.single) r.wide = wide_plan(c, bt, d_lse ? WIDE_GIVEN : WIDE_FUSED, &split, &cpw);
   if (r.wide) {
     r.kr = false;
     r.st = make_table(c, bt, &r.chunk, wide_keys(split));
@@ -989,14 +1048,14 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   // workgroups per CU): a batch whose other jobs fill it would take more
   // rounds with every part.
   {
-    const int hkv = c->shape.num_kv_heads, heads = std::max(1, bt->batch * hkv);
+    const int hkv = c->shape.num_kv_heads, heads = std::max(1, bt->batch * hkv), cus = device_cus(c);
     // calibration, scores and candidate lists (and the allocation's jobs)
     const int others = (r.adaptive ? 5 : 3) * r.st.total_segs * hkv;
-    auto rounds = [&](int p) { return (others + p * heads + 2 * c->cus - 1) / (2 * c->cus); };
-    int p = std::max(1, std::min(8, c->cus / heads));
+    auto rounds = [&](int p) { return (others + p * heads + 2 * cus - 1) / (2 * cus); };
+    int p = std::max(1, std::min(8, cus / heads));
     r.parts_alone = p;
     auto rounds_mega = [&](int q) {
-      return (others + 2 * r.a.wide_jobs * hkv + q * heads + c->cus - 1) / c->cus;
+      return (others + 2 * r.a.wide_jobs * hkv + q * heads + cus - 1) / cus;
     };
     int pm = p;
     while (pm > 1 && rounds_mega(pm) > rounds_mega(1)) --pm;
