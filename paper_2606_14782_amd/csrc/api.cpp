@@ -116,22 +116,15 @@ Layout layout_of(const bacon_shape *s, const bacon_params *p) {
   L.hist_b_stride = align256(hist * kHCopies);
   L.hist_s_stride = align256(hist);
   L.hist_b = off;   off += copies_hist_b(true, adaptive) * L.hist_b_stride;
-  // the allocation's histograms: cleared with them where a prompt uses them
-  // (bacon_allocate_heads clears its own copy)
+  // the allocation's histograms (bacon_allocate_heads clears its own copy)
   L.hist_a_stride = align256(hist);
-  if (adaptive) {
-    L.hist_a = off; off += kCopiesHistA * L.hist_a_stride;
-  }
+  L.hist_a = off;   off += (adaptive ? kCopiesHistA : 1) * L.hist_a_stride;
   // meeting words of the single-read pass (arrival and done counters per
   // (sequence, KV head) on lines of their own, the error word, the published
-  // row normalisers), right after the B histograms so that one clearing
-  // launch covers both
+  // row normalisers)
   L.sync_bytes = align256((size_t)(kSyncStride * s->max_batch * s->num_kv_heads + 1) * sizeof(unsigned)) +
                  align256((size_t)s->max_batch * s->num_kv_heads * L.rpad * sizeof(unsigned));
   L.sync = off;     off += L.sync_bytes;
-  if (!adaptive) {
-    L.hist_a = off; off += L.hist_a_stride;
-  }
   L.hist_s = off;   off += kCopiesS * L.hist_s_stride;
   // the lists of one copy lie one after the other: keys, positions, V for B
   // (3 vectors) and keys, positions for S (2 vectors)
@@ -676,12 +669,28 @@ bacon_status bacon_begin_prompt(bacon_ctx *c, const bacon_batch *bt, void *strea
   TRY(check_batch(c, bt));
   c->cu.assign(bt->cu_seqlens, bt->cu_seqlens + bt->batch + 1);
 
-  // layer 0 reads no history; the B histograms of the select start at zero
-  // (each layer's candidate job clears its copy for the layer that takes it
-  // next), and so do the meeting counters of the single-read pass
-  const hipError_t e = launch_zero(reinterpret_cast<unsigned *>(c->ws + c->L.hist_b),
-                                   (int64_t)((c->L.sync + c->L.sync_bytes - c->L.hist_b) / sizeof(unsigned)),
-                                   static_cast<hipStream_t>(stream));
+  // layer 0 reads no history; the histograms of the select and of the allocation
+  // start at zero (each layer's jobs clear their copy for the layer that takes it
+  // next), and so do the meeting counters of the single-read pass.  Only the
+  // batch's rows of each copy: 64 sequences of 32 KV heads have 302 MB of copies,
+  // 60 us to clear for a prompt of one.
+  const Layout &L = c->L;
+  const bool adaptive = c->params.head_alloc == BACON_ALLOC_ADAPTIVE;
+  const int64_t rows = (int64_t)bt->batch * c->shape.num_kv_heads;
+  auto at = [&](size_t off) { return reinterpret_cast<unsigned *>(c->ws + off); };
+  ClearArgs z{};
+  z.p[0] = at(L.hist_b);
+  z.words[0] = rows * kHCopies * kHRow;
+  z.stride[0] = (int64_t)(L.hist_b_stride / sizeof(unsigned));
+  z.copies[0] = copies_hist_b(true, adaptive);
+  z.p[1] = at(L.hist_a);
+  z.words[1] = rows * kHRow;
+  z.stride[1] = (int64_t)(L.hist_a_stride / sizeof(unsigned));
+  z.copies[1] = adaptive ? kCopiesHistA : 0;
+  z.p[2] = at(L.sync);
+  z.words[2] = (int64_t)(L.sync_bytes / sizeof(unsigned));
+  z.copies[2] = 1;
+  const hipError_t e = launch_clear(z, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "clear");
   c->prompt = true;
   c->next_layer = 0;

@@ -286,6 +286,15 @@ size_t alloc_lds_bytes(int hkv);
 hipError_t launch_alloc(int stage, const AllocArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_zero(unsigned *p, int64_t n, hipStream_t s);
+// Regions that one launch clears: `words` words of each of `copies` copies,
+// `stride` words apart (multiples of four words).
+constexpr int kClearRegions = 3;
+struct ClearArgs {
+  unsigned *p[kClearRegions];
+  int64_t words[kClearRegions], stride[kClearRegions];
+  int copies[kClearRegions];
+};
+hipError_t launch_clear(const ClearArgs &a, hipStream_t s);
 // Device address of the static scratch on the current device (looked up
 // once per device); kStaticScratchBytes long.
 hipError_t static_scratch(void **ptr);

@@ -4783,6 +4783,28 @@ hipError_t launch_zero(unsigned *p, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void k_clear(ClearArgs a) {
+  int c = blockIdx.y, r = 0;
+  while (r + 1 < kClearRegions && c >= a.copies[r]) c -= a.copies[r++];
+  unsigned *p = a.p[r] + c * a.stride[r];
+  for (int64_t q = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); q < a.words[r]; q += 4 * (int64_t)gridDim.x * 256)
+    *reinterpret_cast<u32x4 *>(p + q) = u32x4{0u, 0u, 0u, 0u};
+}
+
+hipError_t launch_clear(const ClearArgs &a, hipStream_t s) {
+  int64_t most = 0;
+  int copies = 0;
+  for (int r = 0; r < kClearRegions; ++r) {
+    if (a.words[r] % 4 || a.stride[r] % 4 || reinterpret_cast<uintptr_t>(a.p[r]) % 16) return hipErrorInvalidValue;
+    copies += a.copies[r];
+    if (a.copies[r]) most = std::max(most, a.words[r]);
+  }
+  if (!copies || most <= 0) return hipSuccess;
+  const int64_t blocks = std::min<int64_t>(1024, (most / 4 + 255) / 256);
+  hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks, copies), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- compaction
 // Rows of the compacted cache of a (sequence, KV head): the kept positions of
 // idx, the W window rows, then zero rows up to K + W.  Each thread moves

@@ -323,3 +323,33 @@ def test_calibrate_in_place(pool_mode, over):
         assert torch.equal(lam, want["lambda"])
         for n, t in dict(out, S=S).items():
             assert torch.equal(t, want[n]), (layer, n)
+
+
+@pytest.mark.parametrize("adaptive", [False, True])
+def test_prompts_of_changing_batches(adaptive):
+    """begin_prompt clears the rows of its batch in a workspace of any content:
+    prompts of one and three sequences in a context for five give what contexts
+    of their own give."""
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    lens, budgets = (900, 2100, 300), (20, 150, 9)
+    prm = dict(head_alloc=bacon.ALLOC_ADAPTIVE) if adaptive else {}
+    full = _wl(6, 4, 2, 64, 16, 5, "bf16", lens, budgets)
+    big = bacon.Context(6, 4, 2, 64, 16, 5, 2 * full.total_tokens, "bf16", P.params_for(full, **prm))
+    for n in (1, 3, 1, 2):
+        wl = _wl(6, 4, 2, 64, 16, 5, "bf16", lens[:n], budgets[:n])
+        big.workspace.fill_(0x7f)
+        batch = bacon.BatchLayout(wl.cu_seqlens, wl.budgets_arr)
+        xs = [inputs.layer_inputs(wl, l) for l in range(6)]
+        qs, ks, vs = ([P.to_dev(x[k], wl) for x in xs] for k in ("q_win", "k", "v"))
+        own = P.make_ctx(wl, P.params_for(wl, **prm))
+        for ctx in (own, big):
+            ctx.bacon_begin_prompt(batch)
+        want = own.bacon_compress_prompt(0, batch, qs, ks, vs)
+        got = big.bacon_compress_prompt(0, batch, qs, ks, vs)
+        torch.cuda.synchronize()
+        for l in range(6):
+            for x, y in zip(got[l], want[l]):
+                assert torch.equal(x, y), (n, l)
+        assert big.bacon_debug_device_errors() == 0
