@@ -95,25 +95,24 @@ def kernel_bytes(name, wl, persist_m=4):
                    for k in ("segment_calib", "segment_score", "segment_cand", "final_topk"))
     if name == "layer_stages":                          # every stage, one layer's worth of each
         return sum(kernel_bytes(k, wl, persist_m) for k in ("window_score_calib_wide", "segment_select"))
-    if name == "segment_calib_cand":                    # calibration, the previous layer's lists,
-        return sum(kernel_bytes(k, wl, persist_m)      # the next layer's normaliser merge
-                   for k in ("segment_calib", "segment_cand", "lse_merge"))
-    if name == "segment_score_final":                   # scores, the previous layer's top-K
-        return sum(kernel_bytes(k, wl, persist_m) for k in ("segment_score", "final_topk"))
     return 0.0
 
 
 def design_bytes(name, wl, persist_m=4):
     """Bytes a launch moves in this design at minimum (beside the algorithmic
-    ones): the dual launch reads two layers' K, pass 1 reads K again."""
+    ones): a launch with both passes reads two layers' K, pass 1 reads K again,
+    B goes to memory."""
     ab = algorithmic_bytes(wl, persist_m)
     vec = wl.total_tokens * wl.num_kv_heads * 4
     if name in ("window_score_calib_lse_kr", "window_score_calib_lse"):
         return 2 * (ab["k"] + ab["q"]) + 2 * vec
-    if name in ("window_lse_kr", "window_lse"):
+    if name in ("window_lse_kr", "window_lse", "window_lse_wide"):
         return ab["k"] + ab["q"]
-    if name in ("window_score_calib_kr", "window_score_calib", "window_score_single"):
+    if name in ("window_score_calib_kr", "window_score_calib", "window_score_single", "window_score_calib_wide"):
         return ab["k"] + ab["q"] + 2 * vec
+    if name == "layer_stages":
+        return (design_bytes("window_lse_wide", wl, persist_m) + design_bytes("window_score_calib_wide", wl, persist_m)
+                + kernel_bytes("segment_select", wl, persist_m))
     return kernel_bytes(name, wl, persist_m)
 
 

@@ -140,7 +140,7 @@ typedef struct {
   int32_t num_q_heads;
   int32_t num_kv_heads;      /* num_q_heads % num_kv_heads == 0              */
   int32_t head_dim;          /* 64 or 128                                    */
-  int32_t window;            /* W >= 1, and G*W <= 512                       */
+  int32_t window;            /* W >= 1, and G*W <= 256                       */
   int32_t max_batch;         /* 1..64                                        */
   int64_t max_total_tokens;  /* upper bound of T                             */
   bacon_dtype dtype;
@@ -148,7 +148,7 @@ typedef struct {
 
 /* A packed batch.  The arrays live in HOST memory and are copied by the call.
  * cu_seqlens[0] = 0 and W <= N_b = cu_seqlens[b+1]-cu_seqlens[b] <= 131072
- * (bacon_calibrate and bacon_select_topk, whose select holds a sequence in
+ * (bacon_calibrate and bacon_select_topk, whose top-K holds a sequence in
  * LDS: <= 32768, UNSUPPORTED beyond).
  * Budgets: `head_budgets` [batch][num_kv_heads], when not NULL, gives every
  * (sequence, KV head) its own budget K_{b,h} >= 1 (a head-wise allocation of
@@ -252,12 +252,13 @@ bacon_status bacon_compress_layer_lse(bacon_ctx *ctx, int32_t layer, const bacon
  * prompt (compression at the end of prefill, when every layer's cache is
  * there): the same results as bacon_compress_layer (or, when d_lse is not
  * NULL, bacon_compress_layer_lse) called for each layer in order, bit for
- * bit.  With every layer's inputs at hand, two layers are in flight: the K
- * pass that forms the next layer's normalisers runs in the launch of this
- * layer's scoring pass, their merge in this layer's calibration launch, and
- * this layer's candidate lists and final top-K and compaction in the next
- * layer's calibration and score launches: three launches per layer, all on
- * `stream`.  A layer's outputs are complete when the call's work on the
+ * bit.  With every layer's inputs at hand, several layers are in flight, all
+ * on `stream`: on grids that do not fill the GPU one launch per layer holds
+ * both K passes and the select stages, each of another layer; on larger ones
+ * a K launch (which also forms the next layer's normalisers, unless K is read
+ * once) and a select launch with the calibration, scores, candidate lists and
+ * final top-K and compaction of four consecutive layers.
+ * A layer's outputs are complete when the call's work on the
  * stream is.  The per-layer arguments are host arrays of num_layers device
  * pointers each, in the layouts of bacon_compress_layer; d_lse is NULL or
  * such an array.  layer_batch is NULL (every layer keeps `batch`'s budgets)

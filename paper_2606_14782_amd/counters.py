@@ -46,12 +46,6 @@ _NAMES = [
     (r"bacon::k_sel_one<1>", "final_topk"),
     (r"bacon::k_sel_one<2>", "segment_calib"),
     (r"bacon::k_sel_one<3>", "segment_cand"),
-    (r"bacon::k_sel_a\b", "segment_calib_cand"),
-    (r"bacon::k_sel_b\b", "segment_score_final"),
-    (r"bacon::k_segcal\b", "segment_calib"),
-    (r"bacon::k_segscore\b", "segment_score"),
-    (r"bacon::k_segcand\b", "segment_cand"),
-    (r"bacon::k_segfinal\b", "final_topk"),
     (r"bacon::k_compact\b", "compact"),
     (r"bacon::k_split_", "split_calib"),
     (r"bacon::k_select\b", "select_topk"),

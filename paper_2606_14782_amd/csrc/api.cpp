@@ -420,9 +420,9 @@ bacon_status seq_table(bacon_ctx *c, const SeqTable &st, hipStream_t s, const in
   return BACON_OK;
 }
 
-// History slots for layer `layer`: E of layer j lives in slot j % (m + 1), so
-// the previous cnt = min(m, layer) layers are the slots wr - cnt .. wr - 1
-// (mod m + 1), none of them wr.
+// History slots for layer `layer`: E of layer j lives in slot j % slots, with more
+// than m of them, so the previous cnt = min(m, layer) layers are the slots
+// wr - cnt .. wr - 1 (mod slots), none of them wr.
 void ring_slots(const bacon_ctx *c, int layer, int *wr, int *cnt) {
   *cnt = std::min(c->params.persist_m, layer);
   *wr = layer % c->L.slots;

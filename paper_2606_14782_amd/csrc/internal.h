@@ -124,8 +124,8 @@ struct SegArgs {
   unsigned *hist_A;              // the allocation's histogram, cleared by the calibration (may be NULL)
   unsigned *hist_B, *hist_S;     // key histograms of B [B, Hkv, kHCopies, kHRow] (the bin count is
                                  // the sum of the copies) and of the pooled score [B, Hkv, kHRow];
-                                 // the final kernel clears hist_B for the next layer, the
-                                 // calibration kernel clears hist_S
+                                 // the candidate job clears hist_B for the layer that takes
+                                 // the copy next, the calibration clears hist_S
   // per-segment lists at or above a boundary bin: segment s of a sequence
   // writes slots [s*kSegLen, ...) of the [Hkv, T] arrays, its count to cnt
   unsigned *listB_key, *listS_key;
@@ -269,7 +269,7 @@ struct SelJobs {
 };
 hipError_t launch_sel(const SelJobs &j, const SeqTable &st, hipStream_t s);
 // Wide passes (grids that do not fill the GPU): keys per workgroup, whether a
-// shape is covered, pass 1 (PASS_LSE) or the fused pass 2 (PASS_FUSED) alone,
+// shape fits them (rows and LDS; the host's plan takes fewer), pass 1 (PASS_LSE) or the fused pass 2 (PASS_FUSED) alone,
 // and a launch with any of the select jobs (no merge) beside pass 2 of one
 // layer and pass 1 of another (NULL: none).
 int wide_keys(int split);
@@ -281,7 +281,6 @@ hipError_t launch_mega(bool bf16, int head_dim, const SelJobs &j, const PassArgs
                        const SeqTable &st, hipStream_t s);
 // LDS of the final workgroup for budgets up to max_budget.
 size_t final_lds_bytes(int max_budget, int window);
-size_t alloc_lds_bytes(int hkv);
 // One job of the allocation in a launch of its own: 0 pool, 1 list, 2 pick.
 hipError_t launch_alloc(int stage, const AllocArgs &a, const SeqTable &st, hipStream_t s);
 hipError_t launch_compact(const CompactArgs &a, const SeqTable &st, hipStream_t s);

@@ -1125,11 +1125,12 @@ hipError_t launch_krpass(int mode, bool bf16, int head_dim, bool w32, const Pass
 }
 
 // ---------------------------------------------------------------- wide pass
-// The K passes of grids that do not fill the GPU (bf16 and fp32 keys, up to
-// 256 window rows): a workgroup of 16 waves takes 512 / S keys of one KV head, a
-// wave one 32-key tile and every S-th of the 32-row tiles (S = 1, 2 or 4; with
-// fewer row tiles than S the other waves only help with the loads), where the key-register passes give a wave four key tiles and all rows in turn.  On
-// such grids a launch takes as long as one of its workgroups.  The host picks S
+// The K passes of grids that do not fill the GPU (bf16 with up to 256 window
+// rows; the host keeps fp32 to 128): a workgroup of 16 waves takes 512 / S keys
+// of one KV head, a wave one 32-key tile and every S-th of the 32-row tiles
+// (S = 1, 2 or 4; with fewer row tiles than S the other waves only help with the
+// loads), where the key-register passes give a wave four key tiles and all rows
+// in turn.  On such grids a launch takes as long as one of its workgroups.  The host picks S
 // and the chunks per workgroup (wide_plan): more row tiles, or fp32's slower
 // matrix instructions, are spread over more workgroups as long as the GPU has
 // CUs for them.  The workgroup's threads are those of the select jobs, so that
@@ -1146,7 +1147,9 @@ hipError_t launch_krpass(int mode, bool bf16, int head_dim, bool w32, const Pass
 //    memory once per workgroup.
 // The sums follow the order of the pass that covers the shape on larger grids
 // (a.kr_sums: the key-register pass, else the streaming pass), so that B and Q
-// given the normalisers do not depend on the grid's size.
+// given the normalisers do not depend on the grid's size; but for Q in the
+// key-register order with S > 1 and a window other than 32 queries, which is
+// summed per row tile first (that pass chains one sum over all tiles).
 constexpr int kWideWavesLog = 4, kWideWaves = 1 << kWideWavesLog;
 static_assert(64 * kWideWaves == kSegThreads, "one tile per wave");
 constexpr int kWideKeys = 32 * kWideWaves;
@@ -4329,9 +4332,6 @@ static size_t alloc_lds(const AllocArgs *pool, const AllocArgs *list, const Allo
   if (list) lds = std::max(lds, sizeof(AllocListLds));
   if (pick) lds = std::max(lds, alloc_pick_lds(pick->Hkv));
   return lds;
-}
-size_t alloc_lds_bytes(int hkv) {
-  return std::max(std::max(sizeof(AllocPoolLds), sizeof(AllocListLds)), alloc_pick_lds(hkv));
 }
 static AllocSet<true> alloc_set(const SelJobs &j, const SeqTable &st) {
   AllocSet<true> r{};

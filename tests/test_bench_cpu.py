@@ -15,9 +15,9 @@ import bench  # noqa: E402
 from paper_2606_14782_amd import counters, inputs  # noqa: E402
 
 PROMPT_KERNELS = ["window_lse_kr", "lse_merge", "window_score_calib_kr",
-                  "window_score_calib_lse_kr", "window_score_calib_lse", "segment_calib",
-                  "segment_score", "segment_cand", "final_topk", "segment_calib_cand",
-                  "segment_score_final"]
+                  "window_score_calib_lse_kr", "window_score_calib_lse", "window_score_single",
+                  "window_lse_wide", "window_score_calib_wide", "segment_calib", "segment_score",
+                  "segment_cand", "final_topk", "segment_select", "layer_stages"]
 
 
 @pytest.mark.parametrize("name", PROMPT_KERNELS)
@@ -49,13 +49,18 @@ def test_score_pass_counts_one_layer_of_k():
 
 @pytest.mark.parametrize("idx", range(5))
 def test_launches_of_a_layer_add_up_to_its_algorithmic_bytes(idx):
-    """Prompt schedule: one score launch, the calibration launch and the
-    score/final launch per layer carry exactly the per-layer bytes (K once,
-    Q_win, the E history read and written, the gather, the indices)."""
+    """On each schedule a layer's launches carry exactly the per-layer bytes (K
+    once, Q_win, the E history read and written, the gather, the indices):
+    the K launch and the select launch of a prompt, the one launch of every
+    stage on small grids, and the launches of a layer call."""
     wl = inputs.workload(idx)
     kb = lambda n: bench.kernel_bytes(n, wl)
-    total = kb("window_score_calib_lse_kr") + kb("segment_calib_cand") + kb("segment_score_final")
-    assert total == pytest.approx(bench.algorithmic_bytes(wl)["layer_mean"], rel=1e-12)
+    want = pytest.approx(bench.algorithmic_bytes(wl)["layer_mean"], rel=1e-12)
+    select = ("segment_calib", "segment_score", "segment_cand", "final_topk")
+    for launches in (("window_score_calib_lse_kr", "segment_select"), ("window_score_single", "segment_select"),
+                     ("layer_stages",), ("window_lse_wide", "window_score_calib_wide") + select,
+                     ("window_lse_kr", "lse_merge", "window_score_calib_kr") + select):
+        assert sum(kb(n) for n in launches) == want
 
 
 def test_combined_launches_are_sums_of_their_jobs():
@@ -66,9 +71,13 @@ def test_combined_launches_are_sums_of_their_jobs():
     db = lambda n: bench.design_bytes(n, wl)
     assert db("window_score_calib_lse_kr") == pytest.approx(db("window_score_calib_kr")
                                                           + db("window_lse_kr"))
-    assert kb("segment_calib_cand") == pytest.approx(kb("segment_calib") + kb("segment_cand")
-                                                   + kb("lse_merge"))
-    assert kb("segment_score_final") == pytest.approx(kb("segment_score") + kb("final_topk"))
+    assert kb("segment_select") == pytest.approx(kb("segment_calib") + kb("segment_score")
+                                               + kb("segment_cand") + kb("final_topk"))
+    # every stage: both K passes (K read twice) and the select jobs
+    assert db("layer_stages") == pytest.approx(db("window_lse_wide") + db("window_score_calib_wide")
+                                             + kb("segment_select"))
+    K = 32768 * 8 * 128 * 2
+    assert db("layer_stages") - kb("layer_stages") == pytest.approx(K + 32 * 32 * 128 * 2 + 32768 * 8 * 4)
 
 
 @pytest.mark.parametrize("kernel,name", [
@@ -76,10 +85,18 @@ def test_combined_launches_are_sums_of_their_jobs():
      "window_score_calib_lse_kr"),
     ("void bacon::k_pass_dual<true, 128, true>(bacon::PassArgs, bacon::PassArgs, bacon::SeqTable)",
      "window_score_calib_lse"),
-    ("bacon::k_sel_a(bacon::SegArgs, bacon::SegArgs, bacon::PassArgs, bacon::SeqTable, int, int)",
-     "segment_calib_cand"),
-    ("bacon::k_sel_b(bacon::SegArgs, bacon::SegArgs, bacon::SeqTable, int)", "segment_score_final"),
-    ("bacon::k_segcal(bacon::SegArgs, bacon::SeqTable)", "segment_calib"),
+    ("void bacon::k_sel<false>(bacon::SegArgs, bacon::SegArgs, bacon::SegArgs, bacon::SegArgs, "
+     "bacon::PassArgs, bacon::SeqTable, int, int, int, int, int, bacon::AllocSet<false>)", "segment_select"),
+    ("void bacon::k_mega<true, 128, false>(bacon::SegArgs, bacon::SegArgs, bacon::SegArgs, bacon::SegArgs)",
+     "layer_stages"),
+    ("void bacon::k_wide<0, true, 128>(bacon::PassArgs, bacon::SeqTable)", "window_lse_wide"),
+    ("void bacon::k_wide<2, false, 64>(bacon::PassArgs, bacon::SeqTable)", "window_score_calib_wide"),
+    ("void bacon::k_sel_one<0>(bacon::SegArgs, bacon::SeqTable)", "segment_score"),
+    ("void bacon::k_sel_one<1>(bacon::SegArgs, bacon::SeqTable)", "final_topk"),
+    ("void bacon::k_sel_one<2>(bacon::SegArgs, bacon::SeqTable)", "segment_calib"),
+    ("void bacon::k_sel_one<3>(bacon::SegArgs, bacon::SeqTable)", "segment_cand"),
+    ("void bacon::k_alloc<1>(bacon::AllocArgs, bacon::SeqTable)", "head_alloc"),
+    ("bacon::k_split_evidence(bacon::SplitArgs, bacon::SeqTable)", "split_calib"),
 ])
 def test_counter_names(kernel, name):
     assert counters.library_name(kernel) == name
