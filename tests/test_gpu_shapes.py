@@ -38,7 +38,10 @@ def test_window_rows(hq, hkv, d, window, lens):
 
 @pytest.mark.parametrize("hq,hkv,d,window,dtype,lens", [
     (4, 4, 64, 8, "fp32", (512, 130)),           # one row tile: waves without a tile
-    (8, 1, 128, 32, "fp32", (700, 4099)),        # 256 rows of fp32 d 128: the largest LDS
+    (8, 1, 128, 32, "fp32", (700, 4099)),        # 256 rows of fp32: the streaming passes either way
+    (4, 1, 128, 32, "fp32", (700, 4099)),        # 128 rows of fp32 d 128: the most fp32 takes there
+    (8, 1, 128, 32, "bf16", (700, 4099)),        # 256 rows of bf16 d 128: the most rows
+    (6, 2, 128, 8, "fp32", (1030, 70)),          # one row tile, keys spread over the row groups
     (28, 4, 128, 32, "bf16", (513, 2049, 97)),   # seven row tiles over the row groups
     (6, 2, 128, 16, "bf16", (8191, 33)),         # two row tiles, two chunks per workgroup
     (5, 1, 64, 20, "bf16", (6145,)),             # rows that end inside the last tile
@@ -61,6 +64,8 @@ def test_small_grids(hq, hkv, d, window, dtype, lens, wide, monkeypatch):
     xs = [inputs.layer_inputs(wl, l) for l in range(wl.num_layers)]
     qs, ks, vs = ([P.to_dev(x[n], wl) for x in xs] for n in ("q_win", "k", "v"))
     a, b = P.make_ctx(wl), P.make_ctx(wl)
+    for ctx in (a, b):
+        ctx.bacon_profile_enable(True)
     a.bacon_begin_prompt(batch)
     want = [a.bacon_compress_layer(l, batch, qs[l], ks[l], vs[l]) for l in range(wl.num_layers)]
     b.bacon_begin_prompt(batch)
@@ -69,6 +74,10 @@ def test_small_grids(hq, hkv, d, window, dtype, lens, wide, monkeypatch):
     for l in range(wl.num_layers):
         for x, y in zip(got[l], want[l]):
             assert torch.equal(x, y), f"layer {l}"
+    # the launches are those of the passes that the case is for
+    wide = wide and not (dtype == "fp32" and hq // hkv * window > 128)
+    assert ("window_score_calib_wide" in a.bacon_profile_read()) == wide
+    assert ("layer_stages" in b.bacon_profile_read()) == wide
 
 
 @pytest.mark.parametrize("adaptive", [True, False])
@@ -95,6 +104,7 @@ def test_prompt_longer_than_its_schedule(adaptive, wide, lse, monkeypatch):
     qs, ks, vs = ([P.to_dev(x[n], wl) for x in xs] for n in ("q_win", "k", "v"))
     prm = P.params_for(wl, head_alloc=bacon.ALLOC_ADAPTIVE if adaptive else bacon.ALLOC_GIVEN, alloc_floor=0.2)
     a, b = P.make_ctx(wl, prm), P.make_ctx(wl, prm)
+    b.bacon_profile_enable(True)
     lses = [a.bacon_window_lse(batches[0], q, k) for q, k in zip(qs, ks)] if lse else None
     a.bacon_begin_prompt(batches[0])
     want = [a.bacon_compress_layer_lse(l, batches[l], qs[l], ks[l], vs[l], lses[l]) if lse else
@@ -106,6 +116,7 @@ def test_prompt_longer_than_its_schedule(adaptive, wide, lse, monkeypatch):
         for x, y in zip(got[l], want[l]):
             assert torch.equal(x, y), f"layer {l}"
     assert a.bacon_debug_device_errors() == 0 and b.bacon_debug_device_errors() == 0
+    assert ("layer_stages" in b.bacon_profile_read()) == wide
 
 
 def _budgets_by_counting(B, cu, W, budgets, half, alpha):
