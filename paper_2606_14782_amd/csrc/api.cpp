@@ -548,6 +548,21 @@ bool wide_plan(bacon_ctx *c, const bacon_batch *bt, WideCall call, int *split, i
   return best < 1e30;
 }
 
+// Whether a layer call with the normalisers given is faster on the streaming
+// pass 2, whose sums (B and Q given the normalisers) are those of the wide pass
+// where no key-register pass covers the shape: 128 rows of fp32 (3634 tokens, 32/8
+// heads, d 128, six layers: 288 us against 302; 13201: 471 and 466), and more than
+// 128 of bf16 as long as it runs one stage per workgroup and CU (3634 tokens, 28/4
+// heads, d 128: 228 and 240; 13201 tokens, d 64: 279 and 232).
+bool stream_given(bacon_ctx *c, const bacon_batch *bt) {
+  const int nrt = c->L.rpad / 32;
+  if (c->shape.dtype != BACON_BF16) return nrt == 4;
+  int64_t stages = 0;
+  for (int b = 0; b < bt->batch; ++b)
+    stages += (bt->cu_seqlens[b + 1] - bt->cu_seqlens[b] + stage_keys(nrt) - 1) / stage_keys(nrt);
+  return nrt > 4 && stages * c->shape.num_kv_heads <= device_cus(c);
+}
+
 // The wide passes' fields of a's arguments over the chunks of st.
 void wide_args(const bacon_ctx *c, PassArgs &a, int split, int cpw, const SeqTable &st) {
   a.wide_split_log = split >> 1;   // 1, 2, 4
@@ -962,6 +977,7 @@ bacon_status plan_layer(bacon_ctx *c, int32_t layer, const bacon_batch *bt, cons
   const bool kr_shape = kr_supported(r.bf16, c->shape.head_dim, c->L.rpad);
   int split = 1, cpw = 1;
   if (!c->kr_off && !r.single) r.wide = wide_plan(c, bt, d_lse ? WIDE_GIVEN : WIDE_FUSED, &split, &cpw);
+  if (r.wide && alone && d_lse && !kr_shape && stream_given(c, bt)) r.wide = false;
   if (r.wide) {
     r.kr = false;
     r.st = make_table(c, bt, &r.chunk, wide_keys(split));

@@ -4784,10 +4784,19 @@ hipError_t launch_zero(unsigned *p, int64_t n, hipStream_t s) {
 }
 
 __global__ __launch_bounds__(256) void k_clear(ClearArgs a) {
-  int c = blockIdx.y, r = 0;
-  while (r + 1 < kClearRegions && c >= a.copies[r]) c -= a.copies[r++];
-  unsigned *p = a.p[r] + c * a.stride[r];
-  for (int64_t q = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); q < a.words[r]; q += 4 * (int64_t)gridDim.x * 256)
+  const int y = blockIdx.y;
+  unsigned *p = a.p[0] + y * a.stride[0];
+  int64_t n = a.words[0];
+  int before = a.copies[0];
+#pragma unroll
+  for (int r = 1; r < kClearRegions; ++r) {            // (indexes known here: one round of argument loads)
+    if (y >= before) {
+      p = a.p[r] + (y - before) * a.stride[r];
+      n = a.words[r];
+    }
+    before += a.copies[r];
+  }
+  for (int64_t q = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); q < n; q += 4 * (int64_t)gridDim.x * 256)
     *reinterpret_cast<u32x4 *>(p + q) = u32x4{0u, 0u, 0u, 0u};
 }
 

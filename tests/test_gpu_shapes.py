@@ -364,3 +364,37 @@ def test_prompts_of_changing_batches(adaptive):
             for x, y in zip(got[l], want[l]):
                 assert torch.equal(x, y), (n, l)
         assert big.bacon_debug_device_errors() == 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,window,dtype,lens", [
+    (7, 1, 128, 32, "bf16", (513, 2049, 97)),        # 224 rows
+    (12, 1, 64, 16, "bf16", (4100, 33)),             # 192 rows, a window other than 32 queries
+    (4, 1, 128, 32, "fp32", (700, 3000)),            # 128 rows of fp32
+    (15, 1, 64, 8, "fp32", (2049, 64)),              # 120, in a padded row tile
+])
+def test_given_normalisers_on_either_pass(hq, hkv, d, window, dtype, lens):
+    """With the normalisers given, layer calls of many window rows take the
+    streaming pass 2 and the prompt call the wide one: the same bits."""
+    import torch
+    import parity as P
+    from paper_2606_14782_amd import bacon
+    wl = _wl(4, hq, hkv, d, window, 7, dtype, lens, [max(1, n // 10) for n in lens])
+    batch = bacon.BatchLayout(wl.cu_seqlens, wl.budgets_arr)
+    xs = [inputs.layer_inputs(wl, l) for l in range(4)]
+    qs, ks, vs = ([P.to_dev(x[n], wl) for x in xs] for n in ("q_win", "k", "v"))
+    a, b = P.make_ctx(wl), P.make_ctx(wl)
+    lses = [a.bacon_window_lse(batch, q, k) for q, k in zip(qs, ks)]
+    shape = (4, hkv, wl.total_tokens)
+    caps = [[torch.zeros(s, device="cuda") for s in (shape, shape, (4, wl.batch, hkv))] for _ in range(2)]
+    for ctx, cap in zip((a, b), caps):
+        ctx.bacon_profile_enable(True)
+        ctx.bacon_debug_capture(*cap)
+        ctx.bacon_begin_prompt(batch)
+    want = [a.bacon_compress_layer_lse(l, batch, qs[l], ks[l], vs[l], lses[l]) for l in range(4)]
+    got = b.bacon_compress_prompt(0, batch, qs, ks, vs, lses=lses)
+    torch.cuda.synchronize()
+    for l in range(4):
+        for x, y in zip(got[l], want[l]):
+            assert torch.equal(x, y), f"layer {l}"
+    assert torch.equal(caps[0][0], caps[1][0]) and torch.equal(caps[0][2], caps[1][2])   # B, lambda
+    assert "window_score_calib" in a.bacon_profile_read() and "layer_stages" in b.bacon_profile_read()
