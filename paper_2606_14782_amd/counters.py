@@ -126,7 +126,7 @@ def trace_summary(d: str, md: str, command: str, title: str) -> None:
              "|---|---|---|---|---|---|---|"]
     for tot, name, calls, avg, mn, mx in sorted(rows, reverse=True):
         short = name if len(name) <= 60 else name[:57] + "..."
-        lib = library_name(name) or "(torch / runtime)"
+        lib = library_name(name) or ("(untimed)" if "bacon::" in name else "(torch / runtime)")
         lines.append(f"| `{short}` | {lib} | {calls} | {avg / 1e3:.2f} | {mn / 1e3:.2f} | "
                      f"{mx / 1e3:.2f} | {100 * tot / total:.1f}% |")
     with open(md, "w") as fh:
